@@ -54,9 +54,10 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 // where the query side is the long one.
 
 // The work of one workgroup; `bid` of `nblocks` is its index among the blocks of this problem set.
-// PAD: the tensors' head dimension a.D is smaller than the kernel's D.
+// DP: 0 where the tensors' head dimension a.D is the kernel's D.  Where it is smaller (PAD), the columns
+// that are computed: at least a.D, a multiple of 16; rows keep the kernel's D elements in LDS.
 // REMAP: bid is a hardware block index (mapped to a logical one here); otherwise it is the logical index.
-template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT = false, bool PAD = false, bool REMAP = true>
+template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT = false, int DP = 0, bool REMAP = true>
 __device__ __forceinline__ void attn_bf16_body(const AttnArgs &a, int bid, int nblocks)
 {
     static_assert(!(RESIDENT && CAUSAL), "the resident variant is for unmasked attention");
@@ -68,8 +69,10 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs &a, int bid, int n
     constexpr int RPI = 1024 / ROWB;       // rows moved by one wave-wide direct load
     constexpr int NDMA = BN / RPI / NW;    // direct loads per wave per tensor per tile
     static_assert(BN % (RPI * NW) == 0 && NDMA >= 1, "tile does not divide over the waves");
-    constexpr int DS = D / 16;             // contraction steps of Q K^T
-    constexpr int DB = D / 32;             // 32-row blocks of O^T
+    constexpr bool PAD = DP != 0;
+    constexpr int DU = PAD ? DP : D;       // columns computed
+    constexpr int DS = DU / 16;            // contraction steps of Q K^T
+    constexpr int DB = (DU + 31) / 32;     // 32-row blocks of O^T
     constexpr int PD = NSTAGE - 1;         // prefetch distance in tiles
     static_assert(PD >= 1, "ring too shallow");
     static_assert(PD * 2 * NDMA < 64, "too many loads in flight for vmcnt");
@@ -354,8 +357,9 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs &a, int bid, int n
             }
     };
 
-    // A tile is skipped by a wave when it lies after every row the wave owns (causal only).
-    auto active = [&](int t) { return !CAUSAL || t * BN <= qrow0 + QB * 32 - 1; };
+    // A tile is skipped by a wave when it lies after every row the wave owns (causal), or when the wave
+    // owns no rows (the window's end lies before its first one).
+    auto active = [&](int t) { return qrow0 < Wq && (!CAUSAL || t * BN <= qrow0 + QB * 32 - 1); };
 
     // Ring protocol.  Before the loop the loads of tiles t0 .. t0+PD-1 are issued.  Iteration t
     // waits until this wave's loads of tile t have landed, meets the other waves at the barrier
@@ -489,25 +493,25 @@ constexpr bool use_pipe_body()
 }
 
 // NT (pipelined shapes only): the tile loads carry the non-temporal hint, see direct_load_1k.
-template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT = false, bool PAD = false, bool NT = false>
+template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT = false, int DP = 0, bool NT = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NSTAGE == 2 && NW < 8 ? 2 : 1, 8)))
 void attn_bf16_kernel(const AttnArgs a)
 {
     static_assert(!NT || use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>(), "only the pipelined body has a non-temporal variant");
-    if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) attn_bf16_pipe_body<D, NW, PAD, NT, CAUSAL>(a, blockIdx.x, gridDim.x);
-    else attn_bf16_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, PAD>(a, blockIdx.x, gridDim.x);
+    if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) attn_bf16_pipe_body<D, NW, DP, NT, CAUSAL>(a, blockIdx.x, gridDim.x);
+    else attn_bf16_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP>(a, blockIdx.x, gridDim.x);
 }
 
 // Resident key/value side with the in-wave pipeline (an even number T1 of key tiles).
-template <int D, int T1, int TMAX, bool PAD = false>
+template <int D, int T1, int TMAX, int DP = 0>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 8)))
 void attn_bf16_resident_pipe_kernel(const AttnArgs a)
 {
-    attn_bf16_resident_pipe_body<D, 8, PAD, T1, TMAX>(a, blockIdx.x, gridDim.x);
+    attn_bf16_resident_pipe_body<D, 8, DP, T1, TMAX>(a, blockIdx.x, gridDim.x);
 }
 
 // History partition blocks and window causal blocks of one call in a single launch.
-template <int D, int NW, int NSTAGE, bool PAD = false, bool NT = false>
+template <int D, int NW, int NSTAGE, int DP = 0, bool NT = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NSTAGE == 2 && NW < 8 ? 2 : 1, 8)))
 void attn_bf16_pair_kernel(const PairArgs f)
 {
@@ -516,7 +520,7 @@ void attn_bf16_pair_kernel(const PairArgs f)
     int win_block = (int)blockIdx.x < f.n_hist_blocks ? -1 : xcd_remap(blockIdx.x - f.n_hist_blocks, f.n_win_blocks);
     if ((int)blockIdx.x < f.n_hist_blocks) {
         if constexpr (use_pipe_body<D, NW, 1, false, NSTAGE, false>()) {
-            attn_bf16_pipe_body<D, NW, PAD, NT>(f.hist, blockIdx.x, f.n_hist_blocks);
+            attn_bf16_pipe_body<D, NW, DP, NT>(f.hist, blockIdx.x, f.n_hist_blocks);
             if (f.hist.fuse_window) {
                 // the workgroup of partition 0 goes on to the window's causal block of the same rows
                 // (causal blocks are numbered from the last query block down)
@@ -527,10 +531,10 @@ void attn_bf16_pair_kernel(const PairArgs f)
                 }
             }
         } else {
-            attn_bf16_body<D, NW, 1, false, NSTAGE, false, PAD>(f.hist, blockIdx.x, f.n_hist_blocks);
+            attn_bf16_body<D, NW, 1, false, NSTAGE, false, DP>(f.hist, blockIdx.x, f.n_hist_blocks);
         }
     }
-    if (win_block >= 0) attn_bf16_body<D, NW, 1, true, NSTAGE, false, PAD, false>(f.win, win_block, 0);
+    if (win_block >= 0) attn_bf16_body<D, NW, 1, true, NSTAGE, false, DP, false>(f.win, win_block, 0);
 }
 
 }  // namespace tlin

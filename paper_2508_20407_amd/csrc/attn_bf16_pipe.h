@@ -58,7 +58,7 @@ __device__ __forceinline__ void static_for(F &&f) { static_for_seq(f, std::make_
 // workgroup walks the key tiles up to its last row; a wave leaves the pipeline after the tile that
 // holds its own rows' diagonal (later tiles lie after every row it owns) and from then on only meets
 // the barriers and issues its share of the tile loads.
-template <int D, int NW, bool PAD, bool NT, bool CAUSAL = false>
+template <int D, int NW, int DP, bool NT, bool CAUSAL = false>
 __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, int nblocks)
 {
     constexpr int NSTAGE = 2;
@@ -70,8 +70,10 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
     constexpr int RPI = 1024 / ROWB;       // rows moved by one wave-wide direct load
     constexpr int NDMA = BN / RPI / NW;    // direct loads per wave per tensor per tile
     static_assert(BN % (RPI * NW) == 0 && NDMA >= 1, "tile does not divide over the waves");
-    constexpr int DS = D / 16;             // contraction steps of Q K^T
-    constexpr int DB = D / 32;             // 32-row blocks of O^T
+    constexpr bool PAD = DP != 0;          // see attn_bf16_body
+    constexpr int DU = PAD ? DP : D;       // columns computed
+    constexpr int DS = DU / 16;            // contraction steps of Q K^T
+    constexpr int DB = (DU + 31) / 32;     // 32-row blocks of O^T
     static_assert((2 * NSTAGE - 1) * TILE_B + 56 * ROWB + 256 <= 65536, "LDS offsets must fit the 16-bit immediate");
 
     char *const Ks = tlin_smem;
@@ -109,8 +111,9 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
     };
 
     const int qrow0 = qb * BM + wave * 32;
-    // the last tile this wave computes on (uniform over the wave): causal, the tile of its rows' diagonal
-    const int tl = CAUSAL ? min((qrow0 + 31) / BN, nt - 1) : nt - 1;
+    // the last tile this wave computes on (uniform over the wave): causal, the tile of its rows' diagonal;
+    // none where the window ends before the wave's first row (it still loads its share of the tiles)
+    const int tl = qrow0 >= Wq ? -1 : CAUSAL ? min((qrow0 + 31) / BN, nt - 1) : nt - 1;
     bf16x8 qf[DS];     // Q^T fragments (B operand): lane holds query j, contraction elements 16*s + 8*h .. +7
     {
         const int r = min(qrow0 + j, Wq - 1);
@@ -306,14 +309,14 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         wait_vmcnt<0>();
         scrub(KST);
         __builtin_amdgcn_s_barrier();
-        if (!PIPE_PACED || (CAUSAL && n + 1 > tl)) {
+        if (!PIPE_PACED || n + 1 > tl) {
 #pragma unroll
             for (int i = 0; i < 2 * NDMA; ++i) dma(i, n, VST, KST);
         }
-        if (CAUSAL && n + 1 > tl) {
+        if (n + 1 > tl) {
             // this wave has no further tile to score: tile n is its last one (weights and value
             // products, unpipelined) or already behind it
-            if (n == tl) {
+            if (CAUSAL && n == tl) {
                 weights(Sc, 0);
                 pv_half(0, VST);
                 weights(Sc, 1);
@@ -388,14 +391,16 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         else wait_vmcnt<NDMA>();
         scrub(0);
         __builtin_amdgcn_s_barrier();
-        qk_zero(S0);
+        if (tl >= 0) {
+            qk_zero(S0);
 #pragma unroll
-        for (int s = 0; s < DS; ++s) {
-            qk_step(S0, s, 0, 0);
-            qk_step(S0, s, 1, 0);
+            for (int s = 0; s < DS; ++s) {
+                qk_step(S0, s, 0, 0);
+                qk_step(S0, s, 1, 0);
+            }
+            if (needs_mask(0)) mask_ragged(S0, t0 * BN);
+            move_reference(row_max(S0));
         }
-        if (needs_mask(0)) mask_ragged(S0, t0 * BN);
-        move_reference(row_max(S0));
 
         // step n reads K(n+1) from stage (n+1) % 2 and V(n) from stage n % 2
         int n = 0;
@@ -412,8 +417,8 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         // last tile (n = nt - 1, in S0): weights and value products only
         wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
-        if (CAUSAL && tl < nt - 1) {
-            // this wave finished with an earlier tile
+        if (tl < nt - 1) {
+            // this wave finished with an earlier tile, or owns no rows
         } else if (n & 1) {
             weights(S0, 0);
             pv_half(0, 1);
@@ -477,12 +482,14 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
 // LDS for the lifetime of the workgroup, which walks over query blocks qb, qb + q_groups, ... without
 // any barrier, each block running the pipeline over the resident tiles (T1 is even, so the two score
 // accumulators keep their roles from block to block).  Direct output only (one partition).
-template <int D, int NW, bool PAD, int T1, int TMAX>
+template <int D, int NW, int DP, int T1, int TMAX>
 __device__ __forceinline__ void attn_bf16_resident_pipe_body(const AttnArgs &a, int bid, int nblocks)
 {
     static_assert(T1 % 2 == 0 && T1 >= 2 && T1 <= TMAX, "an even number of resident key tiles");
     constexpr int BN = 64, BM = NW * 32, ROWB = D * 2, TILE_B = BN * ROWB, CPR = ROWB / 16, RPI = 1024 / ROWB;
-    constexpr int NDMA = BN / RPI / NW, DS = D / 16, DB = D / 32;
+    constexpr bool PAD = DP != 0;          // see attn_bf16_body
+    constexpr int DU = PAD ? DP : D;
+    constexpr int NDMA = BN / RPI / NW, DS = DU / 16, DB = (DU + 31) / 32;
     static_assert(BN % (RPI * NW) == 0 && NDMA >= 1, "tile does not divide over the waves");
     static_assert((TMAX - 1) * TILE_B + 56 * ROWB + 256 <= 65536, "LDS offsets must fit the 16-bit immediate");
 

@@ -40,7 +40,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const MergeArgs a)
     const int64_t slot0 = ((int64_t)bh * (a.nchunks ? a.nchunks : 1) + chunk) * a.nparts;
     const int nhist = (a.nchunks && chunk == 0) ? 0 : a.nhist;
     const int64_t wslot = slot0 + a.nhist;             // the window partial's slot
-    const int njoint = live ? nhist + ((a.has_window && a.joint) ? 1 : 0) : 0;
+    // columns beyond the tensors' head dimension are neither in the partials nor stored
+    const int njoint = live && c4 < a.D ? nhist + ((a.has_window && a.joint) ? 1 : 0) : 0;
     // joint slots: the history partials, then (JOINT) the window partial
     auto slot_of = [&](int s) { return s < nhist ? slot0 + s : wslot; };
 
@@ -77,7 +78,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const MergeArgs a)
         }
         M = Mt;
     }
-    if (!live) return;
+    if (!live || c4 >= a.D) return;
 
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
     float lse2 = -INFINITY;
@@ -91,9 +92,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const MergeArgs a)
     }
 
     const int64_t off = (int64_t)b * a.o_sb + (int64_t)hd * a.o_sh + (int64_t)orow * a.o_sr + c4;
-    if (c4 >= a.D) {
-        // column beyond the tensors' head dimension: nothing to store
-    } else if (a.out_bf16) {
+    if (a.out_bf16) {
         bf16x4 ob;
 #pragma unroll
         for (int e = 0; e < 4; ++e) ob[e] = (__bf16)o[e];

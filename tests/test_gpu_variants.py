@@ -1,0 +1,34 @@
+"""GPU parity at the edges of the kernels' size classes: every kernel variant that the host's dispatch
+chooses by size, at the smallest and largest size of its class, against the fp64 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import tlin_inputs as ti
+import paper_2508_20407_amd as tl
+from helpers import assert_close
+from test_gpu_parity import padded
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [28, 32, 36, 48, 52, 68, 96, 100])
+@pytest.mark.parametrize("W,N", [(40, 1300), (161, 700), (257, 2100)])
+def test_columns_computed_and_waves_without_rows(D, W, N):
+    """bf16 at both sides of the column counts that have a kernel of their own (32, 48, 64, 96, 128), with
+    windows that leave the last waves of a workgroup without rows: history, window and both layers."""
+    w = ti.Workload(f"columns_{D}_{W}_{N}", 1, 2, D, N, W, ti.BF16, 1.0, 2468 + D + 7 * W + N)
+    host = ti.make(w)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True)
+    ro, rl = oracle.history(host["Q"], host["Kh"], host["Vh"], w.dtype, w.scale)
+    assert_close(o, ro, w.dtype, f"{w.name} history")
+    # a row sum of bf16-rounded weights is within 2^-8 of the exact one
+    np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-6, atol=4.5e-3)
+    o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
+    ro, _ = oracle.window_causal(host["Q"], host["Kw"], host["Vw"], w.dtype, w.scale)
+    assert_close(o, ro, w.dtype, f"{w.name} window")
+    for mode, omode in ((tl.TLIN_COMBINE_SUM, oracle.SUM), (tl.TLIN_COMBINE_JOINT, oracle.JOINT)):
+        o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=mode, scale=w.scale)
+        ro = oracle.layer(host["Q"], host["Kh"], host["Vh"], host["Kw"], host["Vw"], w.dtype, w.scale, omode)
+        assert_close(o, ro, w.dtype, f"{w.name} layer mode {mode}")
