@@ -86,6 +86,18 @@ Shape kernel_shape(int in_dtype, int W, int D)
     if (in_dtype == TLIN_BF16 && dpad(D) == 64 && s.nw == 8) return {4, 1};
     return s;
 }
+// A causal launch of its own in bf16 with fewer than four eight-wave workgroups per compute unit runs in
+// four-wave ones: two of them share a compute unit, so that the start of one (queries and first tiles
+// on the way), its diagonal tiles, where half of the waves have nothing to do, and its output are hidden
+// by the other's products (8 heads x 128, 1024 rows: 26.4 -> 18.6 us; 32 heads, 4096 rows: 162 -> 145 us).
+// Beyond that the starts no longer count and the larger workgroup's fewer tile loads are ahead (32 heads,
+// 8192 rows: 472 against 487 us).
+Shape causal_shape(const tlin_params *p)
+{
+    const Shape s = kernel_shape(p->in_dtype, p->W, p->D);
+    const int64_t blocks = (int64_t)p->B * p->H * ((p->W + s.bm() - 1) / s.bm());
+    return p->in_dtype == TLIN_BF16 && s.nw == 8 && blocks < 4 * kNumCU ? Shape{4, 1} : s;
+}
 int query_block(int in_dtype, int W, int D) { return kernel_shape(in_dtype, W, D).bm(); }
 
 // Workgroups the chip holds at once for a given kernel shape (LDS- and register-limited).
@@ -405,12 +417,11 @@ tlin_status launch_resident_pipe(const AttnArgs &a, int grid, hipStream_t st)
 template <int D, bool CAUSAL>
 tlin_status launch_bf16(const AttnArgs &a, Shape s, int grid, hipStream_t st)
 {
-    constexpr int NS = (CAUSAL && D != 128) ? 4 : 2;
     if constexpr (D == 128) {
-        if (s.nw == 8) return launch_bf16_shape<D, 8, 1, CAUSAL, NS>(a, grid, st);
+        if (s.nw == 8) return launch_bf16_shape<D, 8, 1, CAUSAL, 2>(a, grid, st);
     }
-    if (s.nw == 4) return launch_bf16_shape<D, 4, 1, CAUSAL, NS>(a, grid, st);
-    return launch_bf16_shape<D, 2, 1, CAUSAL, NS>(a, grid, st);
+    if (s.nw == 4) return launch_bf16_shape<D, 4, 1, CAUSAL, 2>(a, grid, st);
+    return launch_bf16_shape<D, 2, 1, CAUSAL, 2>(a, grid, st);
 }
 
 // fp32 kernel: a ring of two 32-key tiles of K and V (64 KB at D = 128, no attribute needed).
@@ -479,8 +490,8 @@ bool streams_once(const tlin_params *p, const AttnArgs &a, int nqb)
 // Launch one partial-attention kernel over `nsplit` key partitions (or the causal window).
 tlin_status launch_attn(const tlin_params *p, bool causal, AttnArgs a, hipStream_t st)
 {
-    const int qblk = query_block(p->in_dtype, p->W, p->D);
-    a.nqb = (p->W + qblk - 1) / qblk;
+    const Shape s = causal ? causal_shape(p) : kernel_shape(p->in_dtype, p->W, p->D);
+    a.nqb = (p->W + s.bm() - 1) / s.bm();
     a.stream_once = !causal && streams_once(p, a, a.nqb);
     if (use_resident(p, causal, a)) {
         // one workgroup per compute unit, spread evenly over the heads
@@ -502,8 +513,11 @@ tlin_status launch_attn(const tlin_params *p, bool causal, AttnArgs a, hipStream
     const int64_t grid64 = (int64_t)p->B * p->H * a.nqb * a.nsplit * (a.nchunks ? a.nchunks : 1);
     if (grid64 > 0x7fffffff) return TLIN_ERR_INVALID_ARG;
     const int grid = (int)grid64;
+    // every workgroup of a causal launch on the chip at once, up to two to a compute unit, whole heads to an
+    // XCD: see decode_problem
+    const int64_t heads = (int64_t)p->B * p->H;
+    a.causal_flip = causal && s.nw == 4 && grid > kNumCU && grid <= 2 * kNumCU && heads % kNumXCD == 0 ? (int)(heads / kNumXCD) : 0;
     LaunchTimer timer(causal ? KC_WINDOW : KC_HISTORY, st);
-    const Shape s = kernel_shape(p->in_dtype, p->W, p->D);
     if (p->in_dtype == TLIN_BF16) {
         if (dpad(p->D) == 128) return causal ? launch_bf16<128, true>(a, s, grid, st) : launch_bf16<128, false>(a, s, grid, st);
         return causal ? launch_bf16<64, true>(a, s, grid, st) : launch_bf16<64, false>(a, s, grid, st);

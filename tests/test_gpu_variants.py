@@ -32,3 +32,18 @@ def test_columns_computed_and_waves_without_rows(D, W, N):
         o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=mode, scale=w.scale)
         ro = oracle.layer(host["Q"], host["Kh"], host["Vh"], host["Kw"], host["Vw"], w.dtype, w.scale, omode)
         assert_close(o, ro, w.dtype, f"{w.name} layer mode {mode}")
+
+
+@pytest.mark.parametrize("B,H,D,W", [(1, 16, 64, 2050), (1, 16, 128, 2110), (2, 12, 36, 1409), (1, 8, 128, 4097), (1, 128, 128, 2049)])
+def test_causal_workgroup_shapes_and_order(B, H, D, W):
+    """Causal windows at both sides of the lines between workgroup shapes and block orders (two four-wave
+    workgroups per compute unit with the heads behind the first 32 of an XCD mirrored; more than two; eight
+    waves): every row of the first and last heads against the fp64 oracle."""
+    w = ti.Workload(f"causal_{B}_{H}_{D}_{W}", B, H, D, 1, W, ti.BF16, 1.0, 97531 + H + D + W)
+    host = ti.make(w)
+    dev = {k: padded(host[k], w.dtype) for k in ("Q", "Kw", "Vw")}
+    o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
+    for h in sorted({0, 1, H // 2, H - 1}):
+        sub = [np.ascontiguousarray(host[k][B - 1:, h:h + 1]) for k in ("Q", "Kw", "Vw")]
+        ro, _ = oracle.window_causal(*sub, w.dtype, w.scale)
+        assert_close(o[B - 1:, h:h + 1], ro, w.dtype, f"{w.name} head {h}")
