@@ -387,8 +387,8 @@ def main():
     roof["frac_hbm"] = hist_gbs / PEAK_HBM_GBS
     kname = "attn_f32" if w.dtype == ti.F32 else "attn_bf16"
     # (tlin_history_attn runs calls with few query rows over 1024 or more history rows in its
-    # streaming kernel: bf16 at head dimension 128 up to two rows, fp32 up to eight)
-    streaming = not layer and w.N >= 1024 and ((w.dtype == ti.BF16 and w.D == 128 and w.W <= 2) or
+    # streaming kernel: bf16 up to two rows, below head dimension 128 up to 2 GiB of keys and values; fp32 up to eight)
+    streaming = not layer and w.N >= 1024 and ((w.dtype == ti.BF16 and w.W <= 2 and (w.D == 128 or 4 * w.B * w.H * w.N * w.D < 2 << 30)) or
                                                (w.dtype == ti.F32 and w.W <= 8))
     roof["kernel"] = (f"{kname}_pair_kernel (history partitions + window blocks)" if paired else
                       "decode_kernel (history partitions, streamed through registers)" if streaming else

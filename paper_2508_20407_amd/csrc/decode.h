@@ -5,17 +5,18 @@
 // With one to four query rows the work is a matrix-vector product per head: every byte of K and V
 // is used once per query, nothing is reused, and the matrix cores have nothing to offer.  This
 // kernel therefore never touches LDS or the matrix cores on its main path: K and V rows stream
-// from HBM straight into registers (16 bytes per lane and load, 16 lanes to a row, a wave
-// instruction covers four rows or half rows), scores are sums over a lane's columns (v_dot2_f32_bf16 for bf16 inputs, fp32 FMAs
-// for fp32 inputs) reduced over the lanes of a row with DPP exchanges, the softmax is kept online
-// per lane group, and the value rows are accumulated per lane (bf16: v_dot2_f32_bf16 against the
-// bf16-rounded weight, the same rounding the matrix-core kernels apply; fp32: FMAs with the fp32
-// weight).  Several waves per SIMD, each with two chunks of loads in flight, keep enough bytes on
+// from HBM straight into registers (16 bytes per lane and load, 16 or 8 lanes to a row, a wave
+// instruction covers eight or four rows or half rows), scores are sums over a lane's columns
+// (v_dot2_f32_bf16 for bf16 inputs, fp32 FMAs for fp32 inputs) reduced over the lanes of a row with DPP
+// exchanges, the softmax is kept online per lane group, and the value rows are accumulated per lane with
+// FMAs in fp32 with the fp32 weight, which the row sum takes too: the stream leaves the vector units
+// enough time to widen the bf16 values (32 heads x 128 over 131072 rows: 0.314 ms per call, 6.8 TB/s, as
+// with bf16-rounded weights and v_dot2_f32_bf16).  Several waves per SIMD, each with two chunks of loads in flight, keep enough bytes on
 // the way to cover HBM latency.
 //
 // A workgroup of four waves takes one partition of one (batch, head): wave w works on the chunks
 // w, w + 4, ... of the partition, the row groups of a wave keep separate softmax states, and the
-// 16 states are joined through LDS at the end into one partial (O_part, m, l) in the format
+// 16 or 32 states are joined through LDS at the end into one partial (O_part, m, l) in the format
 // of the matrix-core kernels, which the merge kernel then joins exactly.
 #pragma once
 #include "common.h"
@@ -30,15 +31,17 @@ __device__ __forceinline__ float dpp_add(float x)
     return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
 }
 
-// sum over the 16 consecutive lanes that share a row, result in every one of them: neighbours
-// inside a quad, the other quad of a group of eight (mirror inside eight lanes: quads are uniform
-// by then), the other eight (mirror inside sixteen lanes)
-__device__ __forceinline__ float row16_allsum(float x)
+// sum over the LPR = 8 or 16 consecutive lanes that share a row, result in every one of them:
+// neighbours inside a quad, the other quad of a group of eight (mirror inside eight lanes: quads are
+// uniform by then), the other eight (mirror inside sixteen lanes)
+template <int LPR>
+__device__ __forceinline__ float row_allsum(float x)
 {
+    static_assert(LPR == 8 || LPR == 16, "lanes of a row");
     x = dpp_add<0xB1>(x);      // quad_perm [1,0,3,2]
     x = dpp_add<0x4E>(x);      // quad_perm [2,3,0,1]
     x = dpp_add<0x141>(x);     // row_half_mirror
-    x = dpp_add<0x140>(x);     // row_mirror
+    if (LPR == 16) x = dpp_add<0x140>(x);     // row_mirror
     return x;
 }
 
@@ -78,9 +81,8 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const StreamReadArgs a
     asm volatile("" ::"v"(acc));       // the folded value is "used": the loads stay
 }
 
-// T: element type of Q, K and V (__bf16 or float).  DK: the kernel's head dimension (a row of 256
-// or 512 bytes: 128 for bf16, 64 or 128 for fp32; shorter bf16 rows are as fast on the matrix-core
-// path, whose cost does not grow with the number of query rows);
+// T: element type of Q, K and V (__bf16 or float).  DK: the kernel's head dimension, 64 or 128 (a row
+// of 128, 256 or 512 bytes);
 // the tensors' a.D equals it, or is smaller when PAD (then a row's pieces past a.D are not read,
 // and what the last piece holds past a.D -- the caller's padding, possibly NaNs -- is cleared in K
 // and Q and lands in output columns that are not stored for V).  WQ: query rows computed
@@ -92,15 +94,15 @@ __global__ __launch_bounds__(256) void decode_kernel(const AttnArgs a)
     constexpr bool BF = sizeof(T) == 2;
     constexpr int EB = sizeof(T);               // bytes per element
     constexpr int EPP = 16 / EB;                // elements per 16-byte piece
-    constexpr int PIECES = DK * EB / 16;        // pieces per row: 16 or 32
-    constexpr int LPR = 16;                     // lanes that share a row
+    constexpr int PIECES = DK * EB / 16;        // pieces per row: 8, 16 or 32
+    constexpr int LPR = PIECES < 16 ? PIECES : 16;   // lanes that share a row
     constexpr int PPL = PIECES / LPR;           // pieces of a row per lane: 1, or 2 (fp32, 128 columns)
     constexpr int RPI = 64 / LPR;               // rows per wave-wide load
     constexpr int NI = 4 / PPL;                 // wave-wide row loads per chunk (a chunk is 4 loads of K, 4 of V)
-    constexpr int CH = NI * RPI;                // rows per chunk: 16 or 8
+    constexpr int CH = NI * RPI;                // rows per chunk: 32, 16 or 8
     constexpr int EL = PPL * EPP;               // columns per lane
     constexpr int NG = 4 * RPI;                 // softmax states per workgroup
-    static_assert(PIECES == 16 || PIECES == 32, "rows of 256 or 512 bytes");
+    static_assert(PIECES == 8 || PIECES == 16 || PIECES == 32, "rows of 128, 256 or 512 bytes");
 
     constexpr int WB = WQ < 4 ? WQ : 4;         // query rows joined through LDS at a time
     __shared__ float Osub[NG][WB][DK];
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(256) void decode_kernel(const AttnArgs a)
                         if (BF) acc = dot2_bf16(kk[j][e], q[w][j][e], acc);
                         else acc = fmaf(as_f32(kk[j][e]), as_f32(q[w][j][e]), acc);
                     }
-                s[ii][w] = row16_allsum(acc);
+                s[ii][w] = row_allsum<LPR>(acc);
             }
         }
         if (r0 - g + CH > row_hi) {          // ragged last chunk of the partition (uniform over the wave)
@@ -219,27 +221,19 @@ __global__ __launch_bounds__(256) void decode_kernel(const AttnArgs a)
 #pragma unroll
             for (int ii = 0; ii < NI; ++ii) {
                 const float p = fast_exp2(fmaf(s[ii][w], a.c, -mref));
-                if (BF) {
-                    // weight rounded to bf16: (p, 0) multiplies the even columns, (0, p) the odd ones; the
-                    // latter's bit pattern is the rounded weight as fp32, which is what the row sum takes
-                    const unsigned pe = (unsigned)f32_to_bf16_bits(p);
-                    const unsigned po = pe << 16;
-                    l[w] += __builtin_bit_cast(float, po);
+                l[w] += p;
 #pragma unroll
-                    for (int j = 0; j < PPL; ++j)
+                for (int j = 0; j < PPL; ++j)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            O[w][8 * j + 2 * e] = dot2_bf16(Vr[ii][j][e], pe, O[w][8 * j + 2 * e]);
-                            O[w][8 * j + 2 * e + 1] = dot2_bf16(Vr[ii][j][e], po, O[w][8 * j + 2 * e + 1]);
+                    for (int e = 0; e < 4; ++e) {
+                        const unsigned vv = Vr[ii][j][e];
+                        if (BF) {        // the weight stays fp32; a bf16 is the upper half of an fp32
+                            O[w][EPP * j + 2 * e] = fmaf(p, as_f32(vv << 16), O[w][EPP * j + 2 * e]);
+                            O[w][EPP * j + 2 * e + 1] = fmaf(p, as_f32(vv & 0xffff0000u), O[w][EPP * j + 2 * e + 1]);
+                        } else {
+                            O[w][EPP * j + e] = fmaf(p, as_f32(vv), O[w][EPP * j + e]);
                         }
-                } else {
-                    l[w] += p;
-#pragma unroll
-                    for (int j = 0; j < PPL; ++j)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            O[w][4 * j + e] = fmaf(p, as_f32(Vr[ii][j][e]), O[w][4 * j + e]);
-                }
+                    }
             }
         }
     };

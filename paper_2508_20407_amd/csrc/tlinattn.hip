@@ -256,10 +256,18 @@ int decode_max_rows(const tlin_params *p)
     // fp32 inputs: the matrix-core path pays for a whole 32-row tile of fp32 products whatever W is
     // (1.39 ms over 131072 rows of 32 heads x 128 against 0.62 ms here)
     if (p->in_dtype == TLIN_F32) return 8;
-    // bf16 at head dimension 128: three and four rows are a little faster in the two-wave matrix-core
-    // shape (0.309 against 0.323 ms over 131072 rows; both read at the rate of a plain non-temporal
-    // read stream), and so are shorter rows at any W
-    return p->D == 128 ? 2 : 0;
+    // bf16: three and four rows are a little faster in the two-wave matrix-core shape at head dimension
+    // 128 (0.309 against 0.323 ms over 131072 rows of 32 heads; both read at the rate of a plain
+    // non-temporal read stream) and much faster at the narrow ones (four rows over 99991 rows of 12 heads x
+    // 16: 40 against 48 us)
+    if (p->D == 128) return 2;
+    // Shorter rows leave some lanes of this kernel without a piece.  Below the rate of HBM it is still ahead
+    // (one row over 99991 rows of 12 heads x 36: 47 -> 37 us, x 80: 94 -> 63, x 100: 114 -> 79; over 131072
+    // rows of 32 heads x 16: 94 -> 62, x 36: 114 -> 103, x 64: 163 -> 160, x 96, 1.6 GB: 244 -> 239); where
+    // the stream is long enough to be limited by HBM alone the matrix-core path, whose loads leave out the
+    // missing chunks, is (300001 rows of 32 heads x 48, two rows: 274 against 284 us; x 100: 577 against 592)
+    const int64_t kv_bytes = 4 * (int64_t)p->B * p->H * p->N * p->D;
+    return kv_bytes < ((int64_t)2 << 30) ? 2 : 0;
 }
 bool use_decode(const tlin_params *p)
 {
@@ -276,7 +284,10 @@ Plan plan_decode(const tlin_params *p)
         want = p->num_splits;
     } else {
         const int64_t bh = (int64_t)p->B * p->H;
-        want = (int)((4 * (int64_t)kNumCU + bh - 1) / bh);
+        // rounded down where there are many per head: a last workgroup more than the compute units hold
+        // evenly would run beside four others that have finished
+        const int64_t all = 4 * (int64_t)kNumCU;
+        want = (int)(all >= 8 * bh ? all / bh : (all + bh - 1) / bh);
         const int cap = ntiles / 4 > 1 ? ntiles / 4 : 1;
         if (want > cap) want = cap;
     }
@@ -529,13 +540,17 @@ tlin_status launch_attn(const tlin_params *p, bool causal, AttnArgs a, hipStream
 template <typename T, int DK, bool PAD>
 const void *decode_kernel_for(int W)
 {
-    return W == 1 ? (const void *)decode_kernel<T, DK, 1, PAD> : W == 2 ? (const void *)decode_kernel<T, DK, 2, PAD>
-         : W <= 4 ? (const void *)decode_kernel<T, DK, 4, PAD> : (const void *)decode_kernel<T, DK, 8, PAD>;
+    if constexpr (sizeof(T) == 4) {          // bf16 calls have at most two rows (decode_max_rows)
+        if (W > 4) return (const void *)decode_kernel<T, DK, 8, PAD>;
+        if (W > 2) return (const void *)decode_kernel<T, DK, 4, PAD>;
+    }
+    return W == 1 ? (const void *)decode_kernel<T, DK, 1, PAD> : (const void *)decode_kernel<T, DK, 2, PAD>;
 }
-const void *decode_kernel_f32(int W, int D)
+template <typename T>
+const void *decode_kernel_for(int W, int D)
 {
-    if (dpad(D) == 128) return D == 128 ? decode_kernel_for<float, 128, false>(W) : decode_kernel_for<float, 128, true>(W);
-    return D == 64 ? decode_kernel_for<float, 64, false>(W) : decode_kernel_for<float, 64, true>(W);
+    if (dpad(D) == 128) return D == 128 ? decode_kernel_for<T, 128, false>(W) : decode_kernel_for<T, 128, true>(W);
+    return D == 64 ? decode_kernel_for<T, 64, false>(W) : decode_kernel_for<T, 64, true>(W);
 }
 
 tlin_status launch_decode(const tlin_params *p, const AttnArgs &a, hipStream_t st)
@@ -543,9 +558,7 @@ tlin_status launch_decode(const tlin_params *p, const AttnArgs &a, hipStream_t s
     const int64_t grid64 = (int64_t)p->B * p->H * a.nsplit;
     if (grid64 > 0x7fffffff || p->W > decode_max_rows(p)) return TLIN_ERR_INVALID_ARG;
     LaunchTimer timer(KC_HISTORY, st);
-    const void *kernel = p->in_dtype == TLIN_F32 ? decode_kernel_f32(p->W, p->D)
-                       : p->W == 1             ? (const void *)decode_kernel<__bf16, 128, 1, false>
-                                               : (const void *)decode_kernel<__bf16, 128, 2, false>;
+    const void *kernel = p->in_dtype == TLIN_F32 ? decode_kernel_for<float>(p->W, p->D) : decode_kernel_for<__bf16>(p->W, p->D);
     return launch_kernel(kernel, dim3((unsigned)grid64), dim3(256), 0, st, a);
 }
 

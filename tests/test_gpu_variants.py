@@ -47,3 +47,19 @@ def test_causal_workgroup_shapes_and_order(B, H, D, W):
         sub = [np.ascontiguousarray(host[k][B - 1:, h:h + 1]) for k in ("Q", "Kw", "Vw")]
         ro, _ = oracle.window_causal(*sub, w.dtype, w.scale)
         assert_close(o[B - 1:, h:h + 1], ro, w.dtype, f"{w.name} head {h}")
+
+
+@pytest.mark.parametrize("D", [8, 20, 36, 64, 68, 100, 124])
+@pytest.mark.parametrize("W,N", [(1, 1024), (2, 1087), (1, 5003)])
+def test_cache_hit_rows_of_every_length(D, W, N):
+    """The streaming kernel over bf16 rows shorter than its own (one piece, whole and cut last pieces),
+    with ragged partitions, against the fp64 oracle; its weights and row sums are fp32, so the
+    log-sum-exp holds to fp32 rounding of scores of this size."""
+    w = ti.Workload(f"cache_hit_{D}_{W}_{N}", 2, 3, D, N, W, ti.BF16, 1.0, 1357 + D + 7 * W + N)
+    host = ti.make(w)
+    dev = {k: padded(host[k], w.dtype) for k in ("Q", "Kh", "Vh")}
+    ro, rl = oracle.history(host["Q"], host["Kh"], host["Vh"], w.dtype, w.scale)
+    for splits in (0, 1, 5):
+        o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True, num_splits=splits)
+        assert_close(o, ro, w.dtype, f"{w.name} splits {splits}")
+        np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
