@@ -571,16 +571,18 @@ tlin_status launch_merge(const tlin_params *p, MergeArgs m, hipStream_t st)
     const int64_t total = (int64_t)p->B * p->H * (m.nchunks ? m.seq_rows : p->W);
     if (total > 0x7fffffff) return TLIN_ERR_INVALID_ARG;
     m.total_rows = (int)total;
-    // threads per (row, 4 columns) item: more when a row has many partials to walk
+    // threads per (row, 4 columns) item: more when a row has many partials to walk, and a block of 1024
+    // threads to itself when there are too few rows to fill the chip otherwise
     const int joint = m.nhist + (m.has_window && m.joint ? 1 : 0);
-    const int sl = joint > 16 ? 8 : joint > 6 ? 4 : 1;
-    const int rpb = 256 / (dpad(p->D) / 4 * sl);
+    const int tpr = dpad(p->D) / 4;
+    const int sl = joint <= 6 ? 1 : joint <= 16 ? 4 : joint > 32 && total <= 2 * kNumCU ? 1024 / tpr : 8;
+    const int nt = tpr * sl > 256 ? tpr * sl : 256, rpb = nt / (tpr * sl);
     const int grid = (int)((total + rpb - 1) / rpb);
     LaunchTimer timer(KC_MERGE, st);
     const void *kernel;
-    if (dpad(p->D) == 128) kernel = sl == 8 ? (const void *)merge_kernel<128, 8> : sl == 4 ? (const void *)merge_kernel<128, 4> : (const void *)merge_kernel<128, 1>;
-    else kernel = sl == 8 ? (const void *)merge_kernel<64, 8> : sl == 4 ? (const void *)merge_kernel<64, 4> : (const void *)merge_kernel<64, 1>;
-    return launch_kernel(kernel, dim3(grid), dim3(256), 0, st, m);
+    if (tpr == 32) kernel = sl == 32 ? (const void *)merge_kernel<128, 32> : sl == 8 ? (const void *)merge_kernel<128, 8> : sl == 4 ? (const void *)merge_kernel<128, 4> : (const void *)merge_kernel<128, 1>;
+    else kernel = sl == 64 ? (const void *)merge_kernel<64, 64> : sl == 8 ? (const void *)merge_kernel<64, 8> : sl == 4 ? (const void *)merge_kernel<64, 4> : (const void *)merge_kernel<64, 1>;
+    return launch_kernel(kernel, dim3(grid), dim3(nt), 0, st, m);
 }
 
 AttnArgs base_args(const tlin_params *p, const void *Q, const void *K, const void *V, const int64_t ks[3],

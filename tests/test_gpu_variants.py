@@ -63,3 +63,21 @@ def test_cache_hit_rows_of_every_length(D, W, N):
         o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True, num_splits=splits)
         assert_close(o, ro, w.dtype, f"{w.name} splits {splits}")
         np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("D,H,W", [(64, 3, 5), (128, 3, 5), (36, 16, 40), (128, 16, 40)])
+def test_merge_partition_counts(D, H, W):
+    """The merge at both sides of the lines between its thread counts (6, 16, 32 partials; few and many
+    rows), whole and cut batches of four: history with log-sum-exp and the joint layer."""
+    w = ti.Workload(f"merge_{D}_{H}_{W}", 1, H, D, 64 * 150, W, ti.F32, 1.0, 8642 + D + H + W)
+    host = ti.make(w)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    ro, rl = oracle.history(host["Q"], host["Kh"], host["Vh"], w.dtype, w.scale)
+    rj = oracle.layer(host["Q"], host["Kh"], host["Vh"], host["Kw"], host["Vw"], w.dtype, w.scale, oracle.JOINT)
+    for splits in (2, 5, 6, 7, 16, 17, 32, 33, 75, 150, 300):
+        o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True, num_splits=splits)
+        assert_close(o, ro, w.dtype, f"{w.name} history {splits}")
+        np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+        o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=tl.TLIN_COMBINE_JOINT,
+                               scale=w.scale, num_splits=splits)
+        assert_close(o, rj, w.dtype, f"{w.name} joint {splits}")
