@@ -136,9 +136,11 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
 #pragma unroll
     for (int db = 0; db < DB; ++db) vfrag[db] = 128 * (db ^ h) + 4 * j + 4 * h * ROWB;   // row 4h, chunk ^ 8h
 
-    // Causal: tiles after every row this wave owns are not computed by it, but the wave still
-    // loads its share of them for the others and meets them at the barriers (second loop).
-    const int t1w = CAUSAL ? min(t1, (qrow0 + 31) / BN + 1) : t1;
+    // Tiles after every row this wave owns (causal), and all tiles where the window ends before its first
+    // row, are not computed by it, but the wave still loads its share of them for the others and meets them
+    // at the barriers (second loop): the waves that have rows get the matrix cores for themselves (300
+    // rows, of which an eight-wave workgroup's second block holds 44: 300 causal rows of 12 heads x 128 86 -> 59 us).
+    const int t1w = qrow0 >= Wq ? t0 : CAUSAL ? min(t1, (qrow0 + 31) / BN + 1) : t1;
     if (t0 < t1) issue(t0, 0);
     for (int t = t0; t < t1w; ++t) {
         const int n = t - t0;
@@ -232,7 +234,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
         }
     }
 
-    for (int t = t1w; CAUSAL && t < t1; ++t) {
+    for (int t = max(t0, t1w); t < t1; ++t) {
         wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
         if (NSTAGE == 2 && t + 1 < t1) issue(t + 1, (t - t0 + 1) % NSTAGE);
