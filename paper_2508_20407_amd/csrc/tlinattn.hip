@@ -450,13 +450,18 @@ tlin_status launch_f32(const AttnArgs &a, Shape s, int grid, hipStream_t st)
 // a tail of their own (1.5 to 5 % of the larger workloads' kernel time).  Where the partitions are
 // long enough to absorb it, partition 0's workgroup computes the window block too and gets that
 // much less history (partition_tiles): every partition stays non-empty when the tiles number at
-// least nsplit^2 and a partition is at least four such blocks long.  BM, BN, quarters: the kernel's
+// least nsplit^2 and a partition is longer than such a block.  Below four blocks' length that is worth it
+// only where the chip does not hold the window blocks beside all of the history blocks anyway
+// (layer calls, 300 rows over 20000, 8 heads x 128: fp32 427 -> 343 us, bf16 66 -> 51; 512 rows over 8192,
+// 32 heads x 128: fp32 665 -> 585, bf16 95 -> 84).  BM, BN, quarters: the kernel's
 // query rows per workgroup, keys per tile and cost ratio (window_block_cost).
-bool fuses_window(const PairArgs &f, int BM, int BN, int quarters)
+bool fuses_window(int in_dtype, const PairArgs &f, int BM, int BN, int quarters)
 {
     const int tiles = (f.hist.NK + BN - 1) / BN, ns = f.hist.nsplit;
     const int cost = window_block_cost(f.hist.W, f.hist.nqb - 1, BM, BN, quarters);
-    return f.hist.nchunks == 0 && f.n_win_blocks > 0 && ns >= 2 && tiles >= ns * ns && tiles / ns >= 4 * cost;
+    if (f.hist.nchunks != 0 || f.n_win_blocks <= 0 || ns < 2 || tiles < ns * ns) return false;
+    const bool full = f.n_hist_blocks + f.n_win_blocks > resident_wgs(in_dtype, f.hist.W, f.hist.D);
+    return tiles / ns >= (full ? cost + 2 : 4 * cost);
 }
 
 template <int D>
@@ -464,7 +469,7 @@ tlin_status launch_f32_pair(const PairArgs &f, Shape s, hipStream_t st)
 {
     constexpr int lds_bytes = 2 * 2 * 32 * D * 4;
     PairArgs g = f;
-    if (fuses_window(f, s.nw * 32, 32, 4)) {
+    if (fuses_window(TLIN_F32, f, s.nw * 32, 32, 4)) {
         g.hist.fuse_window = 1;
         g.n_win_blocks = 0;
     }
@@ -641,7 +646,7 @@ tlin_status launch_pair_kernel(const PairArgs &f, hipStream_t st)
     static std::atomic<uint64_t> lds_allowed{0};
     if (allow_lds((const void *)kernel, lds_bytes, lds_allowed) != TLIN_OK) return TLIN_ERR_HIP;
     if constexpr (use_pipe_body<D, NW, 1, false, NSTAGE, false>()) {
-        if (fuses_window(f, NW * 32, 64, 5)) {
+        if (fuses_window(TLIN_BF16, f, NW * 32, 64, 5)) {
             PairArgs g = f;
             g.hist.fuse_window = 1;
             g.n_win_blocks = 0;

@@ -81,3 +81,20 @@ def test_merge_partition_counts(D, H, W):
         o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=tl.TLIN_COMBINE_JOINT,
                                scale=w.scale, num_splits=splits)
         assert_close(o, rj, w.dtype, f"{w.name} joint {splits}")
+
+
+@pytest.mark.parametrize("dtype,D,N", [(ti.F32, 128, 3400), (ti.F32, 64, 3400), (ti.BF16, 128, 5200), (ti.F32, 128, 3200), (ti.BF16, 64, 9000)])
+@pytest.mark.parametrize("W", [161, 257])
+def test_window_block_in_short_partitions(dtype, D, N, W):
+    """Layer calls around the shortest partition whose workgroup also takes the window block, with waves
+    (the last workgroup's) that own no rows."""
+    w = ti.Workload(f"short_partitions_{dtype}_{D}_{N}_{W}", 1, 16, D, N, W, dtype, 1.0, 7531 + D + N + W)
+    host = ti.make(w)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    sub = [np.ascontiguousarray(host[k][:, 5:7]) for k in ("Q", "Kh", "Vh", "Kw", "Vw")]
+    for mode, omode in ((tl.TLIN_COMBINE_SUM, oracle.SUM), (tl.TLIN_COMBINE_JOINT, oracle.JOINT)):
+        o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=mode, scale=w.scale)
+        assert_close(o[:, 5:7], oracle.layer(*sub, w.dtype, w.scale, omode), w.dtype, f"{w.name} mode {mode}")
+    o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
+    ro, _ = oracle.window_causal(sub[0], sub[3], sub[4], w.dtype, w.scale)
+    assert_close(o[:, 5:7], ro, w.dtype, f"{w.name} window")
