@@ -15,9 +15,15 @@ __all__ = ["tlin_history_attn", "tlin_window_causal_attn", "tlin_layer_attn", "t
            "binding"]
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _dtype_code(t):
@@ -30,9 +36,10 @@ def _dtype_code(t):
 
 
 def _strides(t):
-    if t.dim() != 4 or t.stride(3) != 1:
+    st = t.stride()
+    if len(st) != 4 or st[3] != 1:
         raise ValueError("expected a [B,H,rows,D] tensor whose last axis is contiguous")
-    return (t.stride(0), t.stride(1), t.stride(2))
+    return st[:3]
 
 
 def _require_gpu(*ts):
@@ -78,10 +85,10 @@ class Workspace:
 _default_ws = {}
 
 
-def _workspace_for(t, workspace):
+def _workspace_for(t, workspace, stream):
     if workspace is not None:
         return workspace
-    key = (t.device, _stream(t))
+    key = (t.device, stream)
     ws = _default_ws.get(key)
     if ws is None:
         ws = _default_ws[key] = Workspace()
@@ -96,10 +103,11 @@ def _out(q, out_dtype):
     """Output tensor [B,H,rows,D]; its rows are padded to whole 16-byte pieces when D is not."""
     torch = _torch()
     dt = q.dtype if out_dtype is None else out_dtype
-    per16 = 16 // torch.empty((), dtype=dt).element_size()
+    per16 = 16 // dt.itemsize
     B, H, R, D = q.shape
     row = (D + per16 - 1) // per16 * per16
-    return torch.empty((B, H, R, row), dtype=dt, device=q.device)[..., :D]
+    o = torch.empty((B, H, R, row), dtype=dt, device=q.device)
+    return o if row == D else o[..., :D]
 
 
 def tlin_history_attn(q_win, k_hist, v_hist, *, scale=None, out_dtype=None, num_splits=0, return_lse=False,
@@ -110,9 +118,10 @@ def tlin_history_attn(q_win, k_hist, v_hist, *, scale=None, out_dtype=None, num_
     o = _out(q_win, out_dtype)
     p = params_for(q_win, k_hist.shape[2], o.dtype, scale, num_splits, kh=k_hist, vh=v_hist, o=o)
     lse = torch.empty(q_win.shape[:3], dtype=torch.float32, device=q_win.device) if return_lse else None
-    ws, nb = _workspace_for(q_win, workspace).get(binding.workspace_bytes(p), q_win.device)
+    stream = _stream(q_win)
+    ws, nb = _workspace_for(q_win, workspace, stream).get(binding.workspace_bytes(p), q_win.device)
     st = binding.history_attn_raw(p, q_win.data_ptr(), k_hist.data_ptr(), v_hist.data_ptr(), o.data_ptr(),
-                                  lse.data_ptr() if return_lse else None, ws or None, nb, _stream(q_win))
+                                  lse.data_ptr() if return_lse else None, ws or None, nb, stream)
     binding._check(st, "tlin_history_attn")
     return (o, lse) if return_lse else o
 
@@ -138,10 +147,11 @@ def tlin_layer_attn(q_win, k_hist, v_hist, k_win, v_win, *, combine=TLIN_COMBINE
     o = _out(q_win, out_dtype)
     p = params_for(q_win, n, o.dtype, scale, num_splits, combine,
                    kh=k_hist if n else None, vh=v_hist if n else None, kw=k_win, vw=v_win, o=o)
-    ws, nb = _workspace_for(q_win, workspace).get(binding.workspace_bytes(p), q_win.device)
+    stream = _stream(q_win)
+    ws, nb = _workspace_for(q_win, workspace, stream).get(binding.workspace_bytes(p), q_win.device)
     st = binding.layer_attn_raw(p, q_win.data_ptr(), k_hist.data_ptr() if n else None,
                                 v_hist.data_ptr() if n else None, k_win.data_ptr(), v_win.data_ptr(),
-                                o.data_ptr(), ws or None, nb, _stream(q_win))
+                                o.data_ptr(), ws or None, nb, stream)
     binding._check(st, "tlin_layer_attn")
     return o
 
@@ -179,8 +189,9 @@ def tlin_slide_layer_attn(q, k_hist, v_hist, k_win, v_win, chunk, *, combine=TLI
     p = binding.make_params(B, H, int(chunk), L, D, code, oc, (D ** -0.5) if scale is None else scale, num_splits,
                             combine, q_stride=_strides(q), kh_stride=_strides(k_hist), vh_stride=_strides(v_hist),
                             kw_stride=_strides(k_win), vw_stride=_strides(v_win), o_stride=_strides(o))
-    ws, nb = _workspace_for(q, workspace).get(binding.slide_workspace_bytes(p), q.device)
+    stream = _stream(q)
+    ws, nb = _workspace_for(q, workspace, stream).get(binding.slide_workspace_bytes(p), q.device)
     st = binding.slide_layer_attn_raw(p, q.data_ptr(), k_hist.data_ptr(), v_hist.data_ptr(), k_win.data_ptr(),
-                                      v_win.data_ptr(), o.data_ptr(), ws or None, nb, _stream(q))
+                                      v_win.data_ptr(), o.data_ptr(), ws or None, nb, stream)
     binding._check(st, "tlin_slide_layer_attn")
     return o

@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libtlinattn.so")
@@ -29,6 +30,9 @@ class TlinParams(ctypes.Structure):
         ("q_stride", ctypes.c_int64 * 3), ("kh_stride", ctypes.c_int64 * 3), ("vh_stride", ctypes.c_int64 * 3),
         ("kw_stride", ctypes.c_int64 * 3), ("vw_stride", ctypes.c_int64 * 3), ("o_stride", ctypes.c_int64 * 3),
     ]
+
+
+_STRIDES = struct.Struct("=3q")
 
 
 class TlinError(RuntimeError):
@@ -90,14 +94,11 @@ def version() -> int:
 
 def make_params(B, H, W, N, D, in_dtype, out_dtype, scale, num_splits=0, combine=TLIN_COMBINE_SUM,
                 **strides) -> TlinParams:
-    p = TlinParams()
-    p.B, p.H, p.W, p.N, p.D = int(B), int(H), int(W), int(N), int(D)
-    p.in_dtype, p.out_dtype = int(in_dtype), int(out_dtype)
-    p.scale, p.num_splits, p.combine = float(scale), int(num_splits), int(combine)
+    p = TlinParams(int(B), int(H), int(W), int(N), int(D), int(in_dtype), int(out_dtype), float(scale),
+                   int(num_splits), int(combine))
+    # written as bytes: assigning an array field builds a temporary array
     for name, val in strides.items():
-        arr = getattr(p, name)
-        for i in range(3):
-            arr[i] = int(val[i])
+        _STRIDES.pack_into(p, getattr(TlinParams, name).offset, int(val[0]), int(val[1]), int(val[2]))
     return p
 
 
