@@ -236,6 +236,14 @@ Plan plan_history(const tlin_params *p)
         const int64_t base = (int64_t)p->B * p->H * ((p->W + query_block(p->in_dtype, p->W, p->D) - 1) / query_block(p->in_dtype, p->W, p->D));
         const int64_t target = resident_wgs(p->in_dtype, p->W, p->D);
         want = (int)((target + base - 1) / base);
+        // Rounded up, a few workgroups more than the chip holds would start when the others end and run a
+        // whole partition's time beside idle compute units.  With one workgroup per compute unit rounding
+        // down is ahead from two partitions on (1/f of the history against 2/(f + 1)); where several share one,
+        // whose last ones then run faster alone, from eight on, where rounding down costs little (12 heads x
+        // 100, 300 rows over 300000, 24 row blocks: 11 partitions 1077 us, 10: 750; fp32, 12
+        // heads x 128, 256 rows over 30000: 726 -> 412; bf16, 12 heads x 64, 300 rows over 60000: 101 -> 85).
+        const int64_t down = target / base;
+        if (base * want > target && down >= (target == kNumCU ? 2 : 8)) want = (int)down;
         // (a handful of (head, query block) items cannot fill the chip anyway: there the partials
         // are few in total and short partitions pay)
         const int min_tiles = base <= 4 ? 2 : 8;

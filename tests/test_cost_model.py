@@ -50,3 +50,13 @@ def test_library_flop_accounting_is_the_history_term_of_the_model():
     n_terms = parts["context_focused_over_history"] + parts["context_restoration"] + parts["generation_cross_over_history"]
     c1, _ = cm.slope_intercept(256, w.W, 2, D_model)
     assert n_terms == c1 * w.N
+
+
+def test_partitions_fill_the_chip_once():
+    """Twelve heads do not divide 256 compute units: the history workgroups stay within what the chip holds."""
+    from paper_2508_20407_amd import binding as b
+    for B, H, W, D, wgs in ((1, 12, 300, 128, 256), (4, 12, 256, 128, 256), (1, 12, 300, 64, 768), (2, 12, 100, 128, 512)):
+        n = b.num_splits(b.make_params(B, H, W, 300000, D, b.TLIN_BF16, b.TLIN_BF16, D ** -0.5))
+        rows = {128: 256 if W > 128 else 128, 64: 128}[D]
+        blocks = B * H * (-(-W // rows)) * n
+        assert 0.75 * wgs <= blocks <= wgs
