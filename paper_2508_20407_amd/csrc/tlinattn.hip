@@ -277,9 +277,15 @@ int decode_max_rows(const tlin_params *p)
     const int64_t kv_bytes = 4 * (int64_t)p->B * p->H * p->N * p->D;
     return kv_bytes < ((int64_t)2 << 30) ? 2 : 0;
 }
+// bf16 calls below head dimension 128 take the matrix-core path wherever the streaming kernel is not ahead.
+bool decode_optional(const tlin_params *p) { return p->in_dtype == TLIN_BF16 && p->D != 128; }
 bool use_decode(const tlin_params *p)
 {
-    return p->W <= decode_max_rows(p) && p->N >= 1024;
+    if (p->W > decode_max_rows(p) || p->N < 1024) return false;
+    // A history of one partition is one launch on the matrix-core path, which writes O itself and needs no
+    // workspace; here it would be partials and a merge (one row, 800 heads x 36, 1100 rows: 25.4 against 28.3 us
+    // here, 2048 heads x 64, 1024 rows: 83.3 against 88.5; 800 heads x 96, 1100 rows: 59.4 against 55.4).
+    return !decode_optional(p) || plan_history(p).nsplit > 1;
 }
 
 // One workgroup per partition; four per compute unit (they are small: four waves; more partitions
@@ -805,8 +811,10 @@ tlin_status tlin_history_attn(const tlin_params *p, const void *Q_win, const voi
     if (lse && !aligned(lse, 4)) return TLIN_ERR_INVALID_ARG;
     hipStream_t hs = (hipStream_t)stream;
     AttnArgs a = base_args(p, Q_win, K_hist, V_hist, p->kh_stride, p->vh_stride, p->N);
-    if (use_decode(p)) {
-        const Plan pd = plan_decode(p);
+    // (the streaming kernel's partitions may be more than the matrix-core path's: a workspace that only holds
+    // the latter's serves that one)
+    const Plan pd = use_decode(p) ? plan_decode(p) : Plan{0, 0};
+    if (pd.nsplit && !(decode_optional(p) && ws_bytes < ws_bytes_for(p, pd.nsplit))) {
         if ((st = check_ws(ws, ws_bytes, ws_bytes_for(p, pd.nsplit)))) return st;
         if ((st = check_device())) return st;
         const Workspace w = carve(ws, p, pd.nsplit);

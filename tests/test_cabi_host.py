@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2508_20407_amd import binding as b
 
@@ -115,6 +116,30 @@ def test_null_and_misaligned_pointers_and_workspace():
     assert b.layer_attn_raw(p, A, None, A, A, A, A, A, big, None) == b.TLIN_ERR_INVALID_ARG
     assert b.layer_attn_raw(P(combine=3), A, A, A, A, A, A, A, big, None) == b.TLIN_ERR_INVALID_ARG
     assert b.layer_attn_raw(P(N=-1), A, A, A, A, A, A, A, big, None) == b.TLIN_ERR_INVALID_ARG
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the accepted calls would run on fake addresses")
+@pytest.mark.parametrize("kw,bytes_for", [
+    (dict(H=8, W=1, N=4096, num_splits=1), 0),             # one partition, asked for
+    (dict(H=8, W=2, N=4096, D=96, num_splits=1), 0),
+    (dict(B=25, H=32, W=1, N=4096), 0),                    # one partition: the heads alone fill the chip
+    (dict(H=12, W=1, N=100000), 63),                       # the matrix-core path's partitions and no more
+])
+def test_history_calls_of_few_rows_keep_to_the_workspace_of_the_matrix_core_path(kw, bytes_for):
+    """One or two bf16 rows at head dimensions below 128: what the matrix-core path needs is enough (nothing
+    for a single partition), whichever kernel runs when the whole of tlin_workspace_bytes is there."""
+    p = P(**kw)
+    need = p.B * p.H * bytes_for * p.W * (64 * 4 + 8)
+    assert need < b.workspace_bytes(p)
+    ws = A if need else None
+    # every argument check is passed: the first thing that fails is the missing device
+    assert b.history_attn_raw(p, A, A, A, A, None, ws, need, None) == b.TLIN_ERR_HIP
+    if need:
+        assert b.history_attn_raw(p, A, A, A, A, None, ws, need - 1, None) == b.TLIN_ERR_WORKSPACE
+        assert b.history_attn_raw(p, A, A, A, A, None, None, need, None) == b.TLIN_ERR_WORKSPACE
+        assert b.history_attn_raw(p, A, A, A, A, None, A + 16, need, None) == b.TLIN_ERR_WORKSPACE
+    # where the streaming kernel is the only path its workspace is still asked for
+    assert b.history_attn_raw(P(D=128, W=1, N=4096, num_splits=1), A, A, A, A, None, None, 0, None) == b.TLIN_ERR_WORKSPACE
 
 
 def test_static_workspace_entry_point_checks_arguments_and_its_limit_on_the_host():

@@ -2,6 +2,7 @@
 chooses by size, at the smallest and largest size of its class, against the fp64 oracle."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import tlin_inputs as ti
@@ -98,3 +99,28 @@ def test_window_block_in_short_partitions(dtype, D, N, W):
     o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
     ro, _ = oracle.window_causal(sub[0], sub[3], sub[4], w.dtype, w.scale)
     assert_close(o[:, 5:7], ro, w.dtype, f"{w.name} window")
+
+
+@pytest.mark.parametrize("H,W,D,N,splits,parts", [(8, 1, 36, 4100, 1, 0), (8, 2, 96, 1500, 1, 0), (800, 1, 64, 1025, 0, 0),
+                                                 (12, 1, 36, 20000, 0, 35), (12, 1, 36, 20000, 7, 7)])
+def test_few_rows_with_the_workspace_of_the_matrix_core_path(H, W, D, N, splits, parts):
+    """History calls of one or two bf16 rows that bring no workspace (a single partition) or one that holds the
+    matrix-core path's partials only, with the log-sum-exp, against the oracle; nothing behind it is written."""
+    w = ti.Workload(f"few_rows_{H}_{W}_{D}_{N}", 1, H, D, N, W, ti.BF16, 1.0, 2244 + H + D + N)
+    host = ti.make(w)
+    dev = {k: padded(host[k], w.dtype) for k in ("Q", "Kh", "Vh")}
+    o = torch.empty((1, H, W, -(-D // 8) * 8), dtype=torch.bfloat16, device="cuda")[..., :D]
+    lse = torch.empty((1, H, W), dtype=torch.float32, device="cuda")
+    p = tl.params_for(dev["Q"], N, None, w.scale, splits, kh=dev["Kh"], vh=dev["Vh"], o=o)
+    need = H * parts * W * ((64 if D <= 64 else 128) * 4 + 8)
+    ws = torch.full((need + 512,), 0xA5, dtype=torch.uint8, device="cuda")
+    assert ws.data_ptr() % 256 == 0
+    st = tl.binding.history_attn_raw(p, dev["Q"].data_ptr(), dev["Kh"].data_ptr(), dev["Vh"].data_ptr(), o.data_ptr(),
+                                     lse.data_ptr(), ws.data_ptr() if need else None, need, torch.cuda.current_stream().cuda_stream)
+    assert st == tl.binding.TLIN_OK
+    sub = [0, H // 2, H - 1]
+    ro, rl = oracle.history(*(np.ascontiguousarray(host[k][:, sub]) for k in ("Q", "Kh", "Vh")), w.dtype, w.scale)
+    assert_close(o[:, sub], ro, w.dtype, w.name)
+    # fp32 weights and row sums: the log-sum-exp holds to fp32 rounding of scores of this size
+    np.testing.assert_allclose(lse[:, sub].cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+    assert bool((ws[need:] == 0xA5).all())
