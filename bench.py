@@ -387,10 +387,12 @@ def main():
     roof["frac_hbm"] = hist_gbs / PEAK_HBM_GBS
     kname = "attn_f32" if w.dtype == ti.F32 else "attn_bf16"
     # (tlin_history_attn runs calls with few query rows over 1024 or more history rows in its
-    # streaming kernel: bf16 up to two rows, below head dimension 128 up to 2 GiB of keys and values; fp32 up to eight)
-    streaming = not layer and w.N >= 1024 and ((w.dtype == ti.BF16 and w.W <= 2 and (w.D == 128 or 4 * w.B * w.H * w.N * w.D < 2 << 30)) or
-                                               (w.dtype == ti.F32 and w.W <= 8))
+    # streaming kernel: bf16 up to two rows, fp32 up to eight; bf16 below head dimension 128 where the library's
+    # rule on sizes says so)
+    streaming = not layer and w.N >= 1024 and w.W <= (2 if w.dtype == ti.BF16 else 8)
+    by_size = streaming and w.dtype == ti.BF16 and w.D != 128
     roof["kernel"] = (f"{kname}_pair_kernel (history partitions + window blocks)" if paired else
+                      f"decode_kernel or {kname}_kernel, by size (history partitions)" if by_size else
                       "decode_kernel (history partitions, streamed through registers)" if streaming else
                       f"{kname}_kernel (history partitions)")
     roof["kernel_ms"] = hist_ms

@@ -259,33 +259,42 @@ Plan plan_history(const tlin_params *p)
 
 // The cache-hit shape (a few query rows over a long history) runs in the streaming kernel of
 // decode.h when called through tlin_history_attn.
-int decode_max_rows(const tlin_params *p)
-{
-    // fp32 inputs: the matrix-core path pays for a whole 32-row tile of fp32 products whatever W is
-    // (1.39 ms over 131072 rows of 32 heads x 128 against 0.62 ms here)
-    if (p->in_dtype == TLIN_F32) return 8;
-    // bf16: three and four rows are a little faster in the two-wave matrix-core shape at head dimension
-    // 128 (0.309 against 0.323 ms over 131072 rows of 32 heads; both read at the rate of a plain
-    // non-temporal read stream) and much faster at the narrow ones (four rows over 99991 rows of 12 heads x
-    // 16: 40 against 48 us)
-    if (p->D == 128) return 2;
-    // Shorter rows leave some lanes of this kernel without a piece.  Below the rate of HBM it is still ahead
-    // (one row over 99991 rows of 12 heads x 36: 47 -> 37 us, x 80: 94 -> 63, x 100: 114 -> 79; over 131072
-    // rows of 32 heads x 16: 94 -> 62, x 36: 114 -> 103, x 64: 163 -> 160, x 96, 1.6 GB: 244 -> 239); where
-    // the stream is long enough to be limited by HBM alone the matrix-core path, whose loads leave out the
-    // missing chunks, is (300001 rows of 32 heads x 48, two rows: 274 against 284 us; x 100: 577 against 592)
-    const int64_t kv_bytes = 4 * (int64_t)p->B * p->H * p->N * p->D;
-    return kv_bytes < ((int64_t)2 << 30) ? 2 : 0;
-}
+//   fp32 inputs: the matrix-core path pays for a whole 32-row tile of fp32 products whatever W is
+// (1.39 ms over 131072 rows of 32 heads x 128 against 0.62 ms here).
+//   bf16: three and four rows are a little faster in the two-wave matrix-core shape at head dimension
+// 128 (0.309 against 0.323 ms over 131072 rows of 32 heads; both read at the rate of a plain
+// non-temporal read stream) and up to twice as fast at the narrow ones (four rows over 99991 rows of 12
+// heads x 16: 24 against 46 us, x 36: 35 against 48, x 96: 75 against 87).
+constexpr int kDecodeRowsF32 = 8, kDecodeRowsBf16 = 2;
 // bf16 calls below head dimension 128 take the matrix-core path wherever the streaming kernel is not ahead.
 bool decode_optional(const tlin_params *p) { return p->in_dtype == TLIN_BF16 && p->D != 128; }
 bool use_decode(const tlin_params *p)
 {
-    if (p->W > decode_max_rows(p) || p->N < 1024) return false;
+    if (p->N < 1024 || p->W > (p->in_dtype == TLIN_F32 ? kDecodeRowsF32 : kDecodeRowsBf16)) return false;
+    if (!decode_optional(p)) return true;
+    const int64_t bh = (int64_t)p->B * p->H, blocks = bh * plan_history(p).nsplit;
     // A history of one partition is one launch on the matrix-core path, which writes O itself and needs no
-    // workspace; here it would be partials and a merge (one row, 800 heads x 36, 1100 rows: 25.4 against 28.3 us
-    // here, 2048 heads x 64, 1024 rows: 83.3 against 88.5; 800 heads x 96, 1100 rows: 59.4 against 55.4).
-    return !decode_optional(p) || plan_history(p).nsplit > 1;
+    // workspace; here it would be partials and a merge.  That path is ahead where rows are short (one row, 800
+    // heads x 36, 1100 rows: 25.4 against 28.3 us here, 2048 heads x 64, 1024 rows: 83.3 against 88.5) and
+    // behind above 64 columns (800 heads x 96, 1100 rows: 59.7 against 55.6), where only the calls that ask for
+    // a single partition take it, or bring no workspace.
+    if (blocks == bh && (p->D <= 64 || p->num_splits == 1)) return false;
+    // Where the heads do not divide the matrix-core path's places and it would run a second round, this
+    // kernel's smaller workgroups are ahead (100 heads, one row, 0.5 GB: x 68 126 against 90 us, x 96 109
+    // against 85, x 48 92 against 86), with two rows only above 32 columns (250 heads x 16, 3000 rows: 15.5
+    // against 21.9; 100 heads x 68 126 against 94): a lane group of eight takes a row of few columns, whose
+    // scores and weights cost the same for each query.
+    if (blocks > resident_wgs(p->in_dtype, p->W, p->D)) return p->W == 1 || p->D > 32;
+    // Otherwise two rows are up to 19 % faster on the matrix-core path (99991 rows of 12 heads x 36: 35 against
+    // 39 us; 131072 rows of 32 heads x 80: 198 against 203).  One row: with up to 64 bytes of columns that
+    // path moves its tiles in pieces of lines and is behind (131072 rows of 32 heads x 16: 76 against 61 us; x
+    // 32 in 1.2 GB the same).  Wider rows are within 5 % either way as long as the last-level cache holds most
+    // of the keys and values (99991 rows of 12 heads x 36: 36 against 37; x 96: 75 against 74; calls of some
+    // 25 us up to 15 % behind, 128 heads x 64, 4096 rows: 25 against 28) and stay here, where weights are
+    // fp32; beyond, where HBM alone is the limit, that path's loads, which leave the missing chunks out, are
+    // up to 7 % ahead (1.6 GB of 32 heads x 48: 252 against 262, x 80: 251 against 263).
+    const int64_t kv_bytes = 4 * bh * p->N * p->D;
+    return p->W == 1 && (p->D <= 32 || kv_bytes < ((int64_t)384 << 20));
 }
 
 // One workgroup per partition; four per compute unit (they are small: four waves; more partitions
@@ -559,7 +568,7 @@ tlin_status launch_attn(const tlin_params *p, bool causal, AttnArgs a, hipStream
 template <typename T, int DK, bool PAD>
 const void *decode_kernel_for(int W)
 {
-    if constexpr (sizeof(T) == 4) {          // bf16 calls have at most two rows (decode_max_rows)
+    if constexpr (sizeof(T) == 4) {          // bf16 calls have at most two rows (kDecodeRowsBf16)
         if (W > 4) return (const void *)decode_kernel<T, DK, 8, PAD>;
         if (W > 2) return (const void *)decode_kernel<T, DK, 4, PAD>;
     }
@@ -575,7 +584,7 @@ const void *decode_kernel_for(int W, int D)
 tlin_status launch_decode(const tlin_params *p, const AttnArgs &a, hipStream_t st)
 {
     const int64_t grid64 = (int64_t)p->B * p->H * a.nsplit;
-    if (grid64 > 0x7fffffff || p->W > decode_max_rows(p)) return TLIN_ERR_INVALID_ARG;
+    if (grid64 > 0x7fffffff) return TLIN_ERR_INVALID_ARG;
     LaunchTimer timer(KC_HISTORY, st);
     const void *kernel = p->in_dtype == TLIN_F32 ? decode_kernel_for<float>(p->W, p->D) : decode_kernel_for<__bf16>(p->W, p->D);
     return launch_kernel(kernel, dim3((unsigned)grid64), dim3(256), 0, st, a);

@@ -122,14 +122,14 @@ def test_null_and_misaligned_pointers_and_workspace():
 @pytest.mark.parametrize("kw,bytes_for", [
     (dict(H=8, W=1, N=4096, num_splits=1), 0),             # one partition, asked for
     (dict(H=8, W=2, N=4096, D=96, num_splits=1), 0),
-    (dict(B=25, H=32, W=1, N=4096), 0),                    # one partition: the heads alone fill the chip
+    (dict(B=25, H=32, W=1, N=4096), 0), (dict(B=25, H=32, W=1, N=1100, D=96), 0),   # one partition: the heads alone fill the chip
     (dict(H=12, W=1, N=100000), 63),                       # the matrix-core path's partitions and no more
 ])
 def test_history_calls_of_few_rows_keep_to_the_workspace_of_the_matrix_core_path(kw, bytes_for):
     """One or two bf16 rows at head dimensions below 128: what the matrix-core path needs is enough (nothing
     for a single partition), whichever kernel runs when the whole of tlin_workspace_bytes is there."""
     p = P(**kw)
-    need = p.B * p.H * bytes_for * p.W * (64 * 4 + 8)
+    need = p.B * p.H * bytes_for * p.W * ((64 if p.D <= 64 else 128) * 4 + 8)
     assert need < b.workspace_bytes(p)
     ws = A if need else None
     # every argument check is passed: the first thing that fails is the missing device
@@ -140,6 +140,24 @@ def test_history_calls_of_few_rows_keep_to_the_workspace_of_the_matrix_core_path
         assert b.history_attn_raw(p, A, A, A, A, None, A + 16, need, None) == b.TLIN_ERR_WORKSPACE
     # where the streaming kernel is the only path its workspace is still asked for
     assert b.history_attn_raw(P(D=128, W=1, N=4096, num_splits=1), A, A, A, A, None, None, 0, None) == b.TLIN_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("H,W,N,D,matrix,stream,streams", [
+    (12, 1, 99991, 36, 63, 83, True), (12, 2, 99991, 36, 63, 83, False),           # one row, two rows
+    (32, 1, 300001, 48, 24, 32, False), (32, 1, 65000, 48, 24, 32, True),          # 1.8 GB, 0.4 GB
+    (32, 1, 300001, 32, 24, 32, True), (12, 2, 300001, 32, 64, 85, False),         # 64 bytes of columns
+    (100, 1, 19737, 68, 6, 10, True), (100, 2, 75005, 68, 6, 10, True),            # 600 workgroups on 512 places
+    (100, 2, 75005, 36, 8, 10, True), (100, 2, 75005, 32, 8, 10, False),           # 800 on 768
+    (128, 1, 30000, 68, 4, 8, False),                                              # 512 on 512
+])
+def test_streaming_kernel_of_short_bf16_rows_runs_where_it_is_ahead(H, W, N, D, matrix, stream, streams):
+    """Both sides of the lines between the two paths, seen by the number of partitions each cuts."""
+    row = -(-D // 8) * 8
+    st = lambda rows: (H * rows * row, rows * row, row)
+    p = P(H=H, W=W, N=N, D=D, q_stride=st(W), kh_stride=st(N), vh_stride=st(N), o_stride=st(W))
+    assert b.num_splits(p) == (stream if streams else matrix)
+    # layer calls never stream: their workspace holds the matrix-core path's partitions and the window's
+    assert b.workspace_bytes(p) == H * max(matrix + 1, stream if streams else 0) * W * ((64 if D <= 64 else 128) * 4 + 8)
 
 
 def test_static_workspace_entry_point_checks_arguments_and_its_limit_on_the_host():

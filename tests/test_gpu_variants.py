@@ -51,19 +51,23 @@ def test_causal_workgroup_shapes_and_order(B, H, D, W):
 
 
 @pytest.mark.parametrize("D", [8, 20, 36, 64, 68, 100, 124])
-@pytest.mark.parametrize("W,N", [(1, 1024), (2, 1087), (1, 5003)])
-def test_cache_hit_rows_of_every_length(D, W, N):
+@pytest.mark.parametrize("B,H,W,N,splits", [(2, 3, 1, 1024, 5), (2, 3, 1, 1087, 5), (2, 3, 1, 5003, 7), (4, 25, 1, 4099, 11), (4, 25, 2, 4099, 11)])
+def test_cache_hit_rows_of_every_length(D, B, H, W, N, splits):
     """The streaming kernel over bf16 rows shorter than its own (one piece, whole and cut last pieces),
-    with ragged partitions, against the fp64 oracle; its weights and row sums are fp32, so the
-    log-sum-exp holds to fp32 rounding of scores of this size."""
-    w = ti.Workload(f"cache_hit_{D}_{W}_{N}", 2, 3, D, N, W, ti.BF16, 1.0, 1357 + D + 7 * W + N)
+    with ragged partitions, against the fp64 oracle; its weights and row sums are fp32, so outputs and
+    log-sum-exp hold to fp32 rounding.  Two rows of up to 32 columns stay on the matrix-core path, whose
+    weights are bf16."""
+    w = ti.Workload(f"cache_hit_{D}_{B}_{H}_{W}_{N}", B, H, D, N, W, ti.BF16, 1.0, 1357 + D + 7 * W + N)
     host = ti.make(w)
     dev = {k: padded(host[k], w.dtype) for k in ("Q", "Kh", "Vh")}
-    ro, rl = oracle.history(host["Q"], host["Kh"], host["Vh"], w.dtype, w.scale)
-    for splits in (0, 1, 5):
-        o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True, num_splits=splits)
-        assert_close(o, ro, w.dtype, f"{w.name} splits {splits}")
-        np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+    sub = [0, H // 2, H - 1]
+    ro, rl = oracle.history(*(np.ascontiguousarray(host[k][B - 1:, sub]) for k in ("Q", "Kh", "Vh")), w.dtype, w.scale)
+    for s in (0, splits):
+        o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True, num_splits=s)
+        assert_close(o[B - 1:, sub], ro, w.dtype, f"{w.name} splits {s}")
+        np.testing.assert_allclose(lse[B - 1:, sub].cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+        o = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, out_dtype=torch.float32, num_splits=s)
+        assert_close(o[B - 1:, sub], ro, ti.F32 if W == 1 or D > 32 else w.dtype, f"{w.name} splits {s} f32 out")
 
 
 @pytest.mark.parametrize("D,H,W", [(64, 3, 5), (128, 3, 5), (36, 16, 40), (128, 16, 40)])
@@ -101,7 +105,7 @@ def test_window_block_in_short_partitions(dtype, D, N, W):
     assert_close(o[:, 5:7], ro, w.dtype, f"{w.name} window")
 
 
-@pytest.mark.parametrize("H,W,D,N,splits,parts", [(8, 1, 36, 4100, 1, 0), (8, 2, 96, 1500, 1, 0), (800, 1, 64, 1025, 0, 0),
+@pytest.mark.parametrize("H,W,D,N,splits,parts", [(8, 1, 36, 4100, 1, 0), (8, 2, 96, 1500, 1, 0), (800, 1, 64, 1025, 0, 0), (600, 2, 80, 1025, 0, 0),
                                                  (12, 1, 36, 20000, 0, 35), (12, 1, 36, 20000, 7, 7)])
 def test_few_rows_with_the_workspace_of_the_matrix_core_path(H, W, D, N, splits, parts):
     """History calls of one or two bf16 rows that bring no workspace (a single partition) or one that holds the
