@@ -492,13 +492,14 @@ constexpr bool use_pipe_body()
     return !RESIDENT && QB == 1 && NSTAGE == 2;
 }
 
-// NT (pipelined shapes only): the tile loads carry the non-temporal hint, see direct_load_1k.
-template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT = false, int DP = 0, bool NT = false>
+// NT (pipelined shapes only): the tile loads carry the non-temporal hint, see direct_load_1k.  LSE: the caller
+// asks for the log-sum-exp (a variant of its own where the normaliser is not the fp32 sum, see attn_bf16_pipe_body).
+template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT = false, int DP = 0, bool NT = false, bool LSE = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NSTAGE == 2 && NW < 8 ? 2 : 1, 8)))
 void attn_bf16_kernel(const AttnArgs a)
 {
     static_assert(!NT || use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>(), "only the pipelined body has a non-temporal variant");
-    if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) attn_bf16_pipe_body<D, NW, DP, NT, CAUSAL>(a, blockIdx.x, gridDim.x);
+    if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) attn_bf16_pipe_body<D, NW, DP, NT, CAUSAL, LSE>(a, blockIdx.x, gridDim.x);
     else attn_bf16_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP>(a, blockIdx.x, gridDim.x);
 }
 

@@ -31,6 +31,13 @@
 // between).  The normaliser is then the exact sum of the weights while the value product uses their
 // bf16 roundings, so a row is a convex combination only to within 2^-9 per weight; the difference
 // stays far inside the tolerance and the log-sum-exp output becomes exact to fp32 rounding.
+// The stand-alone causal kernel at head dimensions up to 64 (MATCHED) divides by the sum of the
+// rounded weights instead, in attn_bf16_body's order: rows of few keys, where nothing averages out,
+// are common there.  Largest |O - 1| over constant values 1.4e-3 -> 4e-7, 2-norm error over values of
+// mean 1, 4096 rows x 64, 1.3e-4 -> 9e-5.  With half as many products per tile as at head dimension 128
+// the dot2 costs no time here (32 heads x 64, 4096 rows: 104 us with the fp32 sum, 101 with this one).
+// The variant for callers that ask for the log-sum-exp (LSE) keeps the fp32 sum beside it, so that output
+// stays exact to fp32 rounding (109 us).
 //
 // Ring of two tiles for K and two for V; K runs one tile ahead of V.  Step n reads K(n+1) and
 // V(n); at its top (after the step's single barrier) every wave has finished K(n) and V(n-1),
@@ -60,9 +67,11 @@ __device__ __forceinline__ void static_for(F &&f) { static_for_seq(f, std::make_
 // the barriers and issues its share of the tile loads.  Leaving is the end of the wave's own loop, not a
 // branch inside the step: with the branch the causal kernel needed 256 registers and spilled, without
 // it takes 210 (4096 rows, 32 heads x 128: 0.179 -> 0.164 ms).
-template <int D, int NW, int DP, bool NT, bool CAUSAL = false>
+template <int D, int NW, int DP, bool NT, bool CAUSAL = false, bool LSE = false>
 __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, int nblocks)
 {
+    constexpr bool MATCHED = CAUSAL && D == 64;    // the normaliser is the sum of the rounded weights
+    static_assert(MATCHED || !LSE, "elsewhere the row sum is the fp32 one already");
     constexpr int NSTAGE = 2;
     constexpr int BN = 64;                 // keys per tile
     constexpr int BM = NW * 32;            // query rows per workgroup
@@ -182,6 +191,9 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
 
     f32x16 oacc[DB];
     float m = -INFINITY, l = 0.f;
+    float lr = 0.f;                        // MATCHED: rounded weights of the current tile
+    float l32 = 0.f;                       // LSE: fp32 sum
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -204,18 +216,22 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         S[kk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], S[kk], 0, 0, 0);
     };
     // weights of the 16 keys of quarter (kb, t2) from S (against mc), rounded to bf16 for the value
-    // product; their fp32 values are summed into l
+    // product; their fp32 values (MATCHED: the rounded ones, a tile at a time) are summed into l
     auto weights_q = [&](const f32x16 (&S)[2], int kb, int t2) __attribute__((always_inline)) {
         float ls = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
             const float p0 = fast_exp2(fmaf(S[kb][8 * t2 + e], a.c, -mc));
             const float p1 = fast_exp2(fmaf(S[kb][8 * t2 + e + 1], a.c, -mc));
-            pb[kb][t2][e] = (__bf16)p0;
-            pb[kb][t2][e + 1] = (__bf16)p1;
-            ls += p0 + p1;
+            const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
+            pb[kb][t2][e] = pp[0];
+            pb[kb][t2][e + 1] = pp[1];
+            if (MATCHED) lr = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, kb + t2 + e ? lr : 0.f, false);
+            if (!MATCHED || LSE) ls += p0 + p1;
         }
-        l += ls;
+        if (!MATCHED) l += ls;
+        else if (kb + t2 == 2) l += lr;
+        if (LSE) l32 += ls;
     };
     auto weights = [&](const f32x16 (&S)[2], int kb) __attribute__((always_inline)) {
         weights_q(S, kb, 0);
@@ -262,6 +278,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
             const float mn = fmaxf(m, mx);
             const float alpha = (mn == -INFINITY) ? 1.f : fast_exp2((m - mn) * a.c);
             l *= alpha;
+            if (LSE) l32 *= alpha;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -290,7 +307,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
     constexpr int PIPE_VPF = 2;       // V operands (two reads each) requested ahead of their product
     constexpr int PIPE_WA = 2;        // quarters of the tile's weights computed in phase A (the rest in phase B)
     constexpr bool PIPE_PACED = true; // tile loads spread over phase A instead of a burst behind the barrier
-    constexpr int VPQ = 29;           // vector instructions per quarter of a tile's weights: 8 fma, 8 exp2, 4 convert, 9 add
+    constexpr int VPQ = MATCHED ? (LSE ? 33 : 24) : 29;   // vector instructions per quarter of a tile's weights: 8 fma, 8 exp2, 4 convert, 9 add and/or 4 dot2
 
     // value product number i of a tile (i = 8 kb + 4 t2 + db): its V operand, and the product
     auto v_read = [&](int i, int vstage) __attribute__((always_inline)) {
@@ -332,7 +349,9 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         // the weights belong to this phase: without a use here they would sink behind the branch below
 #pragma unroll
         for (int q = 0; q < PIPE_WA; ++q) asm volatile("" : "+v"(pb[q >> 1][q & 1]));
-        asm volatile("" : "+v"(l));
+        if (MATCHED) asm volatile("" : "+v"(lr));
+        else asm volatile("" : "+v"(l));
+        if (LSE) asm volatile("" : "+v"(l32));
         // (tried and within noise: the first value operands of phase B requested at the end of this
         // phase; some of the vector instructions ahead of the first product)
 #pragma unroll
@@ -431,7 +450,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
     }
 
     // ---- epilogue.  Accumulator register v of block db is d = 32*db + 8*(v/4) + 4*h + v%4.
-    const float lt = xhalf_sum(l);
+    const float lt = xhalf_sum(l), lx = LSE ? xhalf_sum(l32) : lt;
     const int row = qrow0 + j;
     if (row >= Wq) return;
     if (a.direct) {
@@ -455,7 +474,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
                     *(f32x4 *)((float *)a.O + off + d) = o;
                 }
             }
-        if (a.lse && h == 0) a.lse[(int64_t)bh * a.W + row] = m * a.scale + logf(lt);
+        if (a.lse && h == 0) a.lse[(int64_t)bh * a.W + row] = m * a.scale + logf(lx);
     } else {
         const int64_t slot = pr.slot + a.part0 + (CAUSAL ? 0 : split);
         float *op = a.Opart + (slot * a.W + row) * D;

@@ -407,12 +407,12 @@ tlin_status with_columns(int dim, F &&f)
     return f(std::integral_constant<int, D>{});
 }
 
-template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT, int DP, bool NT>
+template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT, int DP, bool NT, bool LSE = false>
 tlin_status launch_bf16_kernel(const AttnArgs &a, int grid, hipStream_t st)
 {
     constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2;
     static_assert(lds_bytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a gfx950 compute unit");
-    auto kernel = attn_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, NT>;
+    auto kernel = attn_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, NT, LSE>;
     static std::atomic<uint64_t> lds_allowed{0};
     if (allow_lds((const void *)kernel, lds_bytes, lds_allowed) != TLIN_OK) return TLIN_ERR_HIP;
     return launch_kernel((const void *)kernel, dim3(grid), dim3(NW * 64), lds_bytes, st, a);
@@ -426,6 +426,9 @@ tlin_status launch_bf16_shape(const AttnArgs &a, int grid, hipStream_t st)
         constexpr int DP = decltype(dp)::value;
         if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) {
             if (a.stream_once) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, true>(a, grid, st);
+            if constexpr (CAUSAL && D == 64) {
+                if (a.lse) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, false, true>(a, grid, st);
+            }
         }
         return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, false>(a, grid, st);
     });

@@ -128,3 +128,30 @@ def test_few_rows_with_the_workspace_of_the_matrix_core_path(H, W, D, N, splits,
     # fp32 weights and row sums: the log-sum-exp holds to fp32 rounding of scores of this size
     np.testing.assert_allclose(lse[:, sub].cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
     assert bool((ws[need:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("D", [16, 32, 36, 48, 52, 64])
+@pytest.mark.parametrize("W", [50, 128, 300, 2049])
+def test_causal_rows_are_convex_combinations(D, W):
+    """Stand-alone causal attention in bf16 at head dimensions up to 64 divides by the sum of the weights it
+    multiplies the values with: over values of one all outputs are one, up to the rounding of two fp32 sums of
+    the same W terms (chains of at most 16 terms a tile and one addition per tile on either side: 2 (16 + 33)
+    2^-24 < 1e-5), whether the log-sum-exp is asked for or not; the log-sum-exp is that of the fp32 weights.
+    The same through the layer call without a history and the sliding schedule of a single chunk."""
+    w = ti.Workload(f"convex_{D}_{W}", 1, 8, D, 1, W, ti.BF16, 1.0, 9753 + D + W)
+    host = ti.make(w)
+    dev = {k: padded(host[k], w.dtype) for k in ("Q", "Kw", "Vw")}
+    ones = padded(np.full_like(host["Vw"], 0x3F80), w.dtype)
+    kw = dict(scale=w.scale, out_dtype=torch.float32)
+    o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], ones, **kw)
+    assert (o - 1).abs().max().item() <= 1e-5
+    o2, lse = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], ones, return_lse=True, **kw)
+    assert torch.equal(o, o2)
+    ro, rl = oracle.window_causal(host["Q"], host["Kw"], host["Vw"], w.dtype, w.scale)
+    np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+    assert_close(tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale), ro, w.dtype, w.name)
+    o = tl.tlin_layer_attn(dev["Q"], None, None, dev["Kw"], ones, **kw)
+    assert (o - 1).abs().max().item() <= 1e-5
+    for mode in (tl.TLIN_COMBINE_SUM, tl.TLIN_COMBINE_JOINT):
+        o = tl.tlin_slide_layer_attn(dev["Q"], dev["Kw"], ones, dev["Kw"], ones, W, combine=mode, **kw)
+        assert (o - 1).abs().max().item() <= 1e-5
