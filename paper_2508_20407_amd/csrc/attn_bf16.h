@@ -499,6 +499,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NSTAGE 
 void attn_bf16_kernel(const AttnArgs a)
 {
     static_assert(!NT || use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>(), "only the pipelined body has a non-temporal variant");
+    static_assert(!(NT && CAUSAL), "a window's keys and values are read by several workgroups");
     if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) attn_bf16_pipe_body<D, NW, DP, NT, CAUSAL, LSE>(a, blockIdx.x, gridDim.x);
     else attn_bf16_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP>(a, blockIdx.x, gridDim.x);
 }

@@ -418,15 +418,17 @@ tlin_status launch_bf16_kernel(const AttnArgs &a, int grid, hipStream_t st)
     return launch_kernel((const void *)kernel, dim3(grid), dim3(NW * 64), lds_bytes, st, a);
 }
 
-// The non-temporal variant exists for the pipelined shapes only.
+// The non-temporal variant exists for the pipelined shapes of a history only: causal launches never
+// stream (launch_attn).
 template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT = false>
 tlin_status launch_bf16_shape(const AttnArgs &a, int grid, hipStream_t st)
 {
     return with_columns<D>(a.D, [&](auto dp) {
         constexpr int DP = decltype(dp)::value;
         if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) {
-            if (a.stream_once) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, true>(a, grid, st);
-            if constexpr (CAUSAL && D == 64) {
+            if constexpr (!CAUSAL) {
+                if (a.stream_once) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, true>(a, grid, st);
+            } else if constexpr (D == 64) {
                 if (a.lse) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, false, true>(a, grid, st);
             }
         }

@@ -3,6 +3,8 @@ header declares, and rejects bad arguments before touching the device."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 import torch
@@ -196,6 +198,17 @@ def test_slide_planning_and_argument_checks():
     assert b.slide_layer_attn_raw(p, A, A, A, A, A + 4, A, A, big, None) == b.TLIN_ERR_INVALID_ARG
     assert b.slide_layer_attn_raw(p, A, A, A, A, A, A, None, 0, None) == b.TLIN_ERR_WORKSPACE
     assert b.slide_layer_attn_raw(p, A, A, A, A, A, A, A, 1 << 20, None) == b.TLIN_ERR_WORKSPACE
+
+
+@pytest.mark.skipif(shutil.which("nm") is None, reason="nm not found")
+def test_no_kernel_is_compiled_that_the_dispatch_cannot_reach():
+    """Non-temporal tile loads are for histories only, the log-sum-exp variants for causal kernels only."""
+    names = subprocess.run(["nm", "-C", b.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    kernels = {tuple(k.split(", ")) for k in re.findall(r"attn_bf16_kernel<([^>]*)>", names)}
+    assert len(kernels) >= 20
+    for d, nw, qb, causal, nstage, resident, columns, nt, lse in kernels:
+        assert not (causal == "true" and nt == "true"), (d, nw, columns)
+        assert lse == "false" or (causal == "true" and d == "64"), (d, nw, columns)
 
 
 def test_binding_fails_loudly_when_library_is_missing(monkeypatch):
