@@ -35,16 +35,31 @@ def test_columns_computed_and_waves_without_rows(D, W, N):
         assert_close(o, ro, w.dtype, f"{w.name} layer mode {mode}")
 
 
-@pytest.mark.parametrize("B,H,D,W", [(1, 16, 64, 2050), (1, 16, 128, 2110), (2, 12, 36, 1409), (1, 8, 128, 4097), (1, 128, 128, 2049)])
-def test_causal_workgroup_shapes_and_order(B, H, D, W):
+def mirrored_heads(heads, W):
+    """Heads (of batch * heads) whose blocks run from the short end, in four-wave workgroups of 128 rows: more
+    than one and up to two to a compute unit, whole heads to an XCD, those behind the XCD's first 32 blocks."""
+    blocks = -(-W // 128)
+    if not 256 < heads * blocks <= 512 or heads % 8:
+        return set()
+    return {h for h in range(heads) if (h % (heads // 8) * blocks) >> 5 & 1}
+
+
+@pytest.mark.parametrize("B,H,D,W,mirrored", [
+    (1, 16, 64, 2050, False), (1, 16, 128, 2110, False), (2, 12, 36, 1409, False), (1, 8, 128, 4097, False), (1, 128, 128, 2049, False),
+    (1, 16, 128, 4096, True), (1, 16, 64, 4001, True), (1, 32, 64, 2048, True), (1, 32, 36, 2000, True), (2, 12, 100, 2500, True),
+    (4, 16, 48, 1000, True)])
+def test_causal_workgroup_shapes_and_order(B, H, D, W, mirrored):
     """Causal windows at both sides of the lines between workgroup shapes and block orders (two four-wave
     workgroups per compute unit with the heads behind the first 32 of an XCD mirrored; more than two; eight
-    waves): every row of the first and last heads against the fp64 oracle."""
+    waves): every row of a few heads, mirrored ones and others among them, against the fp64 oracle."""
     w = ti.Workload(f"causal_{B}_{H}_{D}_{W}", B, H, D, 1, W, ti.BF16, 1.0, 97531 + H + D + W)
+    heads = sorted({0, 1, H // 2, H // 2 + 1, H - 1})
+    run_short = {(B - 1) * H + h for h in heads} & mirrored_heads(B * H, W)
+    assert (0 < len(run_short) < len(heads)) if mirrored else not mirrored_heads(B * H, W)
     host = ti.make(w)
     dev = {k: padded(host[k], w.dtype) for k in ("Q", "Kw", "Vw")}
     o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
-    for h in sorted({0, 1, H // 2, H - 1}):
+    for h in heads:
         sub = [np.ascontiguousarray(host[k][B - 1:, h:h + 1]) for k in ("Q", "Kw", "Vw")]
         ro, _ = oracle.window_causal(*sub, w.dtype, w.scale)
         assert_close(o[B - 1:, h:h + 1], ro, w.dtype, f"{w.name} head {h}")
