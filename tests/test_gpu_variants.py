@@ -24,8 +24,9 @@ def test_columns_computed_and_waves_without_rows(D, W, N):
     o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True)
     ro, rl = oracle.history(host["Q"], host["Kh"], host["Vh"], w.dtype, w.scale)
     assert_close(o, ro, w.dtype, f"{w.name} history")
-    # a row sum of bf16-rounded weights is within 2^-8 of the exact one
-    np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-6, atol=4.5e-3)
+    # these shapes sum the fp32 weights: exact to fp32 rounding of scores of this size (a key that is lost or
+    # counted twice among 2100 is 5e-4)
+    np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
     o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
     ro, _ = oracle.window_causal(host["Q"], host["Kw"], host["Vw"], w.dtype, w.scale)
     assert_close(o, ro, w.dtype, f"{w.name} window")
