@@ -86,22 +86,24 @@ def test_cache_hit_rows_of_every_length(D, B, H, W, N, splits):
         assert_close(o[B - 1:, sub], ro, ti.F32 if W == 1 or D > 32 else w.dtype, f"{w.name} splits {s} f32 out")
 
 
-@pytest.mark.parametrize("D,H,W", [(64, 3, 5), (128, 3, 5), (36, 16, 40), (128, 16, 40)])
-def test_merge_partition_counts(D, H, W):
-    """The merge at both sides of the lines between its thread counts (6, 16, 32 partials; few and many
-    rows), whole and cut batches of four: history with log-sum-exp and the joint layer."""
-    w = ti.Workload(f"merge_{D}_{H}_{W}", 1, H, D, 64 * 150, W, ti.F32, 1.0, 8642 + D + H + W)
+@pytest.mark.parametrize("D,H,W", [(64, 3, 5), (128, 3, 5), (36, 16, 40), (128, 16, 32), (64, 27, 19), (100, 19, 27)])
+@pytest.mark.parametrize("parts", [2, 5, 6, 7, 15, 16, 17, 31, 32, 33, 40, 75, 150])
+def test_merge_partition_counts(D, H, W, parts):
+    """The merge at both sides of the lines between its thread counts (6, 16 and 32 partials, the joint layer's
+    window being one more; 512 and 513 rows), whole and cut batches of four: history with log-sum-exp and
+    the joint layer."""
+    w = ti.Workload(f"merge_{D}_{H}_{W}_{parts}", 1, H, D, 64 * parts, W, ti.F32, 1.0, 8642 + D + H + W + parts)
+    assert tl.binding.num_splits(tl.binding.make_params(1, H, W, w.N, D, 0, 0, w.scale, parts)) == parts
     host = ti.make(w)
     dev = {k: padded(v, w.dtype) for k, v in host.items()}
     ro, rl = oracle.history(host["Q"], host["Kh"], host["Vh"], w.dtype, w.scale)
     rj = oracle.layer(host["Q"], host["Kh"], host["Vh"], host["Kw"], host["Vw"], w.dtype, w.scale, oracle.JOINT)
-    for splits in (2, 5, 6, 7, 16, 17, 32, 33, 75, 150, 300):
-        o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True, num_splits=splits)
-        assert_close(o, ro, w.dtype, f"{w.name} history {splits}")
-        np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
-        o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=tl.TLIN_COMBINE_JOINT,
-                               scale=w.scale, num_splits=splits)
-        assert_close(o, rj, w.dtype, f"{w.name} joint {splits}")
+    o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True, num_splits=parts)
+    assert_close(o, ro, w.dtype, f"{w.name} history")
+    np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+    o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=tl.TLIN_COMBINE_JOINT,
+                           scale=w.scale, num_splits=parts)
+    assert_close(o, rj, w.dtype, f"{w.name} joint")
 
 
 @pytest.mark.parametrize("dtype,D,N", [(ti.F32, 128, 3400), (ti.F32, 64, 3400), (ti.BF16, 128, 5200), (ti.F32, 128, 3200), (ti.BF16, 64, 9000)])
