@@ -106,21 +106,42 @@ def test_merge_partition_counts(D, H, W, parts):
     assert_close(o, rj, w.dtype, f"{w.name} joint")
 
 
-@pytest.mark.parametrize("dtype,D,N", [(ti.F32, 128, 3400), (ti.F32, 64, 3400), (ti.BF16, 128, 5200), (ti.F32, 128, 3200), (ti.BF16, 64, 9000)])
-@pytest.mark.parametrize("W", [161, 257])
-def test_window_block_in_short_partitions(dtype, D, N, W):
-    """Layer calls around the shortest partition whose workgroup also takes the window block, with waves
-    (the last workgroup's) that own no rows."""
-    w = ti.Workload(f"short_partitions_{dtype}_{D}_{N}_{W}", 1, 16, D, N, W, dtype, 1.0, 7531 + D + N + W)
-    host = ti.make(w)
-    dev = {k: padded(v, w.dtype) for k, v in host.items()}
-    sub = [np.ascontiguousarray(host[k][:, 5:7]) for k in ("Q", "Kh", "Vh", "Kw", "Vw")]
-    for mode, omode in ((tl.TLIN_COMBINE_SUM, oracle.SUM), (tl.TLIN_COMBINE_JOINT, oracle.JOINT)):
-        o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=mode, scale=w.scale)
-        assert_close(o[:, 5:7], oracle.layer(*sub, w.dtype, w.scale, omode), w.dtype, f"{w.name} mode {mode}")
-    o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
-    ro, _ = oracle.window_causal(sub[0], sub[3], sub[4], w.dtype, w.scale)
-    assert_close(o[:, 5:7], ro, w.dtype, f"{w.name} window")
+def rides_on_partition_0(dtype, D, heads, W, tiles, parts):
+    """The rule by which partition 0 of a layer call's history also takes the window block: the partitions are
+    longer than the block (where the chip does not hold the window blocks beside the history blocks; four
+    times as long otherwise), and number at most the square root of the tiles."""
+    rows = 128 if dtype == ti.BF16 and D <= 64 else 256                 # windows of more than 128 rows
+    places = 768 if rows == 128 else 256
+    blocks = -(-W // rows)
+    wt = -(-W // (64 if dtype == ti.BF16 else 32))
+    cost = (wt * 5 // 4 if dtype == ti.BF16 else wt) + 2
+    full = heads * blocks * (parts + 1) > places
+    return parts >= 2 and tiles >= parts * parts and tiles // parts >= (cost + 2 if full else 4 * cost)
+
+
+@pytest.mark.parametrize("dtype,D", [(ti.F32, 128), (ti.F32, 64), (ti.BF16, 128), (ti.BF16, 100), (ti.BF16, 64), (ti.BF16, 36)])
+@pytest.mark.parametrize("W,heads,parts", [(161, 96, 4), (257, 64, 5), (257, 4, 2)])
+def test_window_block_in_short_partitions(dtype, D, W, heads, parts):
+    """Layer calls around the shortest partition whose workgroup also takes the window block: the shortest
+    history for which it does and one key tile less, in ragged tiles, with waves (the last workgroup's) that own
+    no rows, for full and for mostly empty chips."""
+    tile = 64 if dtype == ti.BF16 else 32
+    tiles = next(t for t in range(parts, 10 ** 4) if rides_on_partition_0(dtype, D, heads, W, t, parts))
+    for t in (tiles, tiles - 1):
+        assert rides_on_partition_0(dtype, D, heads, W, t, parts) == (t == tiles)
+        w = ti.Workload(f"short_partitions_{dtype}_{D}_{t}_{W}", 1, heads, D, tile * t - 5, W, dtype, 1.0, 7531 + D + t + W)
+        p = tl.binding.make_params(1, heads, W, w.N, D, dtype, dtype, w.scale, parts)
+        assert tl.binding.num_splits(p) == parts
+        host = ti.make(w)
+        dev = {k: padded(v, w.dtype) for k, v in host.items()}
+        sub = [0, heads // 2, heads - 1]
+        cut = [np.ascontiguousarray(host[k][:, sub]) for k in ("Q", "Kh", "Vh", "Kw", "Vw")]
+        for mode, omode in ((tl.TLIN_COMBINE_SUM, oracle.SUM), (tl.TLIN_COMBINE_JOINT, oracle.JOINT)):
+            o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=mode, scale=w.scale, num_splits=parts)
+            assert_close(o[:, sub], oracle.layer(*cut, w.dtype, w.scale, omode), w.dtype, f"{w.name} mode {mode}")
+        o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
+        ro, _ = oracle.window_causal(cut[0], cut[3], cut[4], w.dtype, w.scale)
+        assert_close(o[:, sub], ro, w.dtype, f"{w.name} window")
 
 
 @pytest.mark.parametrize("H,W,D,N,splits,parts", [(8, 1, 36, 4100, 1, 0), (8, 2, 96, 1500, 1, 0), (800, 1, 64, 1025, 0, 0), (600, 2, 80, 1025, 0, 0),
