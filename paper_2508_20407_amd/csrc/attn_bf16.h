@@ -226,33 +226,30 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs &a, int bid, int n
         constexpr bool AHEAD = QB == 1 && !RESIDENT;
         if constexpr (AHEAD) {
             // Requests go out in the order the products consume them (contraction step outer,
-            // 32-key block inner), and every product waits only until its own operand has
-            // arrived: LDS reads complete in order, so operand number i of n is there once at most
-            // n-1-i reads are outstanding.  The reads and the waits are written as assembly because
-            // the compiler otherwise waits for all of them before the first product.  (Outstanding
-            // reads the compiler adds on its own can only make a wait longer, never too short.)
+            // 32-key block inner), and every product waits only until its own operand has arrived: LDS
+            // reads complete in order, and the scheduling barriers keep all requests in front and the
+            // products in that order, so that the compiler's waits count down one by one.
+            typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
             bf16x8 kf[2][DS];
             const unsigned kaddr = lds_offset(Kt) + j * ROWB;
             const int ksw = Swz<D>::k(j);                 // same for keys j and j + 32
 #pragma unroll
-            for (int s = 0; s < DS; ++s) {
-                const unsigned addr = kaddr + (((2 * s + h) ^ ksw) << 4);
-                asm volatile("ds_read_b128 %0, %1" : "=v"(kf[0][s]) : "v"(addr));
-                asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(kf[1][s]) : "v"(addr), "n"(32 * ROWB));
-            }
+            for (int s = 0; s < DS; ++s)
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk)
+                    kf[kk][s] = *(lds_bf16x8 *)(uintptr_t)(kaddr + (((2 * s + h) ^ ksw) << 4) + kk * (32 * ROWB));
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) sacc[0][kk][v] = 0.f;
 #pragma unroll
-            for (int s = 0; s < DS; ++s) {
-                asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(kf[0][s]) : "n"(2 * DS - 1 - 2 * s));
-                sacc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][s], qf[0][s], sacc[0][0], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);       // keep each product between its wait and the next
-                asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(kf[1][s]) : "n"(2 * DS - 2 - 2 * s));
-                sacc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][s], qf[0][s], sacc[0][1], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int s = 0; s < DS; ++s)
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) {
+                    sacc[0][kk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk][s], qf[0][s], sacc[0][kk], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);       // keep the products in the order of their operands
+                }
         } else {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {

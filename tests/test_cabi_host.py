@@ -211,6 +211,20 @@ def test_no_kernel_is_compiled_that_the_dispatch_cannot_reach():
         assert lse == "false" or (causal == "true" and d == "64"), (d, nw, columns)
 
 
+def test_inline_assembly_loads_no_registers():
+    """The compiler takes the output of an assembly load as there at once: only the direct loads into LDS,
+    whose arrival is waited for by hand, are written that way."""
+    csrc = os.path.join(ROOT, "paper_2508_20407_amd", "csrc")
+    found = 0
+    for name in sorted(os.listdir(csrc)):
+        source = open(os.path.join(csrc, name)).read().replace("\\n", " ").replace("\\t", " ")
+        for text in re.findall(r"asm volatile\((.*?)\);", source, flags=re.S):
+            for op in re.findall(r"\b(?:ds_read|ds_load|global_load|buffer_load|flat_load|scratch_load|s_load)\w*[^\"]*", text):
+                assert op.startswith("buffer_load") and op.rstrip().endswith(" lds"), (name, op)
+                found += 1
+    assert found == 2
+
+
 def test_binding_fails_loudly_when_library_is_missing(monkeypatch):
     monkeypatch.setattr(b, "_lib", None)
     monkeypatch.setattr(b, "LIB_PATH", "/nonexistent/libtlinattn.so")
