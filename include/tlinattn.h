@@ -36,12 +36,13 @@
  *     any HIP call, so it behaves the same on a machine without a GPU.
  *   - Each (b, h) is an independent attention problem; there is no positional term, bias,
  *     dropout or key/value head sharing.  Non-finite inputs give unspecified outputs.
- *   - Results are exact softmax attention up to rounding: bf16 inputs are multiplied with fp32
- *     accumulation (on the matrix cores; with the dot-product instructions of the vector unit
- *     where one or two query rows meet a long history), softmax weights are rounded to bf16
- *     before the second product; fp32 inputs use fp32 arithmetic throughout (fp32 matrix
- *     instructions, or fp32 multiply-adds of the vector unit for up to eight query rows over a
- *     long history; nothing is rounded below fp32).
+ *   - Results are exact softmax attention up to rounding.  bf16 inputs are multiplied with fp32
+ *     accumulation on the matrix cores, softmax weights rounded to bf16 before the second product.
+ *     Where one or two query rows meet a history of 1024 rows or more, tlin_history_attn may run on the
+ *     vector unit instead (always at head dimension 128, below it by size): its weights and sums
+ *     are fp32.  fp32 inputs use fp32 arithmetic throughout (fp32 matrix instructions, or fp32
+ *     multiply-adds of the vector unit for up to eight query rows over a long history; nothing is
+ *     rounded below fp32).
  *   - Accuracy envelope.  bf16 inputs: |O - exact| <= 2e-2 (mean <= 5e-3) for inputs of unit
  *     scale.  fp32 inputs: a logit is an fp32 sum of D products and carries an absolute error of
  *     a few 2^-24 of its own size, which the exponential turns into the same RELATIVE error of
@@ -102,8 +103,10 @@ typedef struct {
  * arithmetic.  Returns 0 if the parameters are invalid. */
 size_t tlin_workspace_bytes(const tlin_params *p);
 
-/* Number of history partitions the library will use for these parameters (>= 1), or 0 if the
- * parameters are invalid.  Pure host arithmetic. */
+/* Number of history partitions tlin_history_attn will use for these parameters (>= 1), or 0 if the
+ * parameters are invalid.  Pure host arithmetic.  A layer call uses the same number, except for windows
+ * of up to eight rows over 1024 or more history rows, which tlin_history_attn may run in a kernel that
+ * cuts the history differently; a num_splits that is given holds for both. */
 int32_t tlin_num_splits(const tlin_params *p);
 
 /* O[b,h,i,:] = sum_j softmax_j(scale * <Q[b,h,i,:], K_hist[b,h,j,:]>) * V_hist[b,h,j,:],
@@ -112,7 +115,9 @@ int32_t tlin_num_splits(const tlin_params *p);
  * their log-sum-exp statistics.
  *   Q_win [B,H,W,D], K_hist/V_hist [B,H,N,D] in in_dtype; O [B,H,W,D] in out_dtype.
  *   lse: nullable, dense fp32 [B,H,W]; receives log(sum_j exp(scale * <q_i, k_j>)).
- *   ws : workspace of at least tlin_workspace_bytes(p) bytes, 256-byte aligned. */
+ *   ws : workspace of at least tlin_workspace_bytes(p) bytes, 256-byte aligned; may be NULL where
+ *        num_splits is 1, except for fp32 inputs (up to eight rows) and bf16 inputs of head dimension
+ *        128 (up to two rows) over 1024 or more history rows. */
 tlin_status tlin_history_attn(const tlin_params *p, const void *Q_win, const void *K_hist,
                               const void *V_hist, void *O, float *lse, void *ws, size_t ws_bytes,
                               void *stream);

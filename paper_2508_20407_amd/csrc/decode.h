@@ -2,17 +2,18 @@
 // the history's keys and values cached, only the last token computes, and its attention over the N
 // cached rows is the one term that still grows with N).
 //
-// With one to four query rows the work is a matrix-vector product per head: every byte of K and V
-// is used once per query, nothing is reused, and the matrix cores have nothing to offer.  This
-// kernel therefore never touches LDS or the matrix cores on its main path: K and V rows stream
-// from HBM straight into registers (16 bytes per lane and load, 16 or 8 lanes to a row, a wave
-// instruction covers eight or four rows or half rows), scores are sums over a lane's columns
-// (v_dot2_f32_bf16 for bf16 inputs, fp32 FMAs for fp32 inputs) reduced over the lanes of a row with DPP
-// exchanges, the softmax is kept online per lane group, and the value rows are accumulated per lane with
-// FMAs in fp32 with the fp32 weight, which the row sum takes too: the stream leaves the vector units
-// enough time to widen the bf16 values (32 heads x 128 over 131072 rows: 0.314 ms per call, 6.8 TB/s, as
-// with bf16-rounded weights and v_dot2_f32_bf16).  Several waves per SIMD, each with two chunks of loads in flight, keep enough bytes on
-// the way to cover HBM latency.
+// With one or two query rows (fp32 inputs: up to eight, see use_decode) the work is a matrix-vector
+// product per head: every byte of K and V is used once per query, nothing is reused, and the matrix
+// cores have nothing to offer.  This kernel therefore never touches LDS or the matrix cores on its main
+// path: K and V rows stream from HBM straight into registers (16 bytes per lane and load, 16 or 8 lanes
+// to a row, a wave instruction covers eight or four rows or half rows), scores are sums over a lane's
+// columns (v_dot2_f32_bf16 for bf16 inputs, fp32 FMAs for fp32 inputs) reduced over the lanes of a row
+// with DPP exchanges, the softmax is kept online per lane group, and the value rows are accumulated per
+// lane with FMAs in fp32 with the fp32 weight, which the row sum takes too: the stream leaves the vector
+// units enough time to widen the bf16 values (32 heads x 128 over 131072 rows: 0.314 ms per call, 6.8
+// TB/s, as with bf16-rounded weights and v_dot2_f32_bf16; error of an fp32 output 1.5e-3 -> 3e-7).
+// Several waves per SIMD, each with two chunks of loads in flight, keep enough bytes on the way to
+// cover HBM latency.
 //
 // A workgroup of four waves takes one partition of one (batch, head): wave w works on the chunks
 // w, w + 4, ... of the partition, the row groups of a wave keep separate softmax states, and the
