@@ -774,6 +774,19 @@ tlin_status layer_attn(const tlin_params *p, const void *Q_win, const void *K_hi
     return launch_merge(p, merge_args(p, w, nparts, pl.nsplit, true, p->combine == TLIN_COMBINE_JOINT, O, nullptr), hs);
 }
 
+// The launches of a history call in the streaming kernel; arguments and workspace have been checked.
+tlin_status history_attn_streamed(const tlin_params *p, AttnArgs a, Plan pd, void *O, float *lse, void *ws, hipStream_t hs)
+{
+    tlin_status st;
+    if ((st = check_device())) return st;
+    const Workspace w = carve(ws, p, pd.nsplit);
+    a.nsplit = pd.nsplit;
+    a.tiles_per_split = pd.tiles_per_split;
+    set_partial(a, w, pd.nsplit, 0);
+    if ((st = launch_decode(p, a, hs))) return st;
+    return launch_merge(p, merge_args(p, w, pd.nsplit, pd.nsplit, false, true, O, lse), hs);
+}
+
 // Address of this device's copy of `scratch`, looked up once per device ordinal with that device
 // current (every GPU holds its own copy of the array at its own address).
 tlin_status static_scratch(void **out)
@@ -825,18 +838,13 @@ tlin_status tlin_history_attn(const tlin_params *p, const void *Q_win, const voi
     if (lse && !aligned(lse, 4)) return TLIN_ERR_INVALID_ARG;
     hipStream_t hs = (hipStream_t)stream;
     AttnArgs a = base_args(p, Q_win, K_hist, V_hist, p->kh_stride, p->vh_stride, p->N);
-    // (the streaming kernel's partitions may be more than the matrix-core path's: a workspace that only holds
-    // the latter's serves that one)
-    const Plan pd = use_decode(p) ? plan_decode(p) : Plan{0, 0};
-    if (pd.nsplit && !(decode_optional(p) && ws_bytes < ws_bytes_for(p, pd.nsplit))) {
-        if ((st = check_ws(ws, ws_bytes, ws_bytes_for(p, pd.nsplit)))) return st;
-        if ((st = check_device())) return st;
-        const Workspace w = carve(ws, p, pd.nsplit);
-        a.nsplit = pd.nsplit;
-        a.tiles_per_split = pd.tiles_per_split;
-        set_partial(a, w, pd.nsplit, 0);
-        if ((st = launch_decode(p, a, hs))) return st;
-        return launch_merge(p, merge_args(p, w, pd.nsplit, pd.nsplit, false, true, O, lse), hs);
+    if (use_decode(p)) {
+        const Plan pd = plan_decode(p);
+        // (its partitions may be more than the matrix-core path's, or that path's single one needs no workspace: a
+        // call that brings only what that path needs is served by it)
+        st = check_ws(ws, ws_bytes, ws_bytes_for(p, pd.nsplit));
+        if (st && !decode_optional(p)) return st;
+        if (!st) return history_attn_streamed(p, a, pd, O, lse, ws, hs);
     }
     const Plan pl = plan_history(p);
     a.nsplit = pl.nsplit;

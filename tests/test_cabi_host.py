@@ -136,6 +136,9 @@ def test_history_calls_of_few_rows_keep_to_the_workspace_of_the_matrix_core_path
     ws = A if need else None
     # every argument check is passed: the first thing that fails is the missing device
     assert b.history_attn_raw(p, A, A, A, A, None, ws, need, None) == b.TLIN_ERR_HIP
+    if not need:                # a workspace that is not used is not looked at
+        assert b.history_attn_raw(p, A, A, A, A, None, None, 1 << 30, None) == b.TLIN_ERR_HIP
+        assert b.history_attn_raw(p, A, A, A, A, None, A + 16, 1 << 30, None) == b.TLIN_ERR_HIP
     if need:
         assert b.history_attn_raw(p, A, A, A, A, None, ws, need - 1, None) == b.TLIN_ERR_WORKSPACE
         assert b.history_attn_raw(p, A, A, A, A, None, None, need, None) == b.TLIN_ERR_WORKSPACE
