@@ -192,7 +192,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
     f32x16 oacc[DB];
     float m = -INFINITY, l = 0.f;
     float lr = 0.f;                        // MATCHED: rounded weights of the current tile
-    float l32 = 0.f;                       // LSE: fp32 sum
+    float l32 = 0.f, ls32 = 0.f;           // LSE: fp32 sum
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -227,11 +227,12 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
             pb[kb][t2][e] = pp[0];
             pb[kb][t2][e + 1] = pp[1];
             if (MATCHED) lr = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, kb + t2 + e ? lr : 0.f, false);
-            if (!MATCHED || LSE) ls += p0 + p1;
+            if (LSE) ls32 = (kb + t2 + e ? ls32 : 0.f) + (p0 + p1);
+            else if (!MATCHED) ls += p0 + p1;
         }
         if (!MATCHED) l += ls;
         else if (kb + t2 == 2) l += lr;
-        if (LSE) l32 += ls;
+        if (LSE && kb + t2 == 2) l32 += ls32;
     };
     auto weights = [&](const f32x16 (&S)[2], int kb) __attribute__((always_inline)) {
         weights_q(S, kb, 0);
@@ -307,7 +308,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
     constexpr int PIPE_VPF = 2;       // V operands (two reads each) requested ahead of their product
     constexpr int PIPE_WA = 2;        // quarters of the tile's weights computed in phase A (the rest in phase B)
     constexpr bool PIPE_PACED = true; // tile loads spread over phase A instead of a burst behind the barrier
-    constexpr int VPQ = MATCHED ? (LSE ? 33 : 24) : 29;   // vector instructions per quarter of a tile's weights: 8 fma, 8 exp2, 4 convert, 9 add and/or 4 dot2
+    constexpr int VPQ = MATCHED ? (LSE ? 32 : 24) : 29;   // vector instructions per quarter of a tile's weights: 8 fma, 8 exp2, 4 convert, 9 add and/or 4 dot2
 
     // value product number i of a tile (i = 8 kb + 4 t2 + db): its V operand, and the product
     auto v_read = [&](int i, int vstage) __attribute__((always_inline)) {
@@ -351,7 +352,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         for (int q = 0; q < PIPE_WA; ++q) asm volatile("" : "+v"(pb[q >> 1][q & 1]));
         if (MATCHED) asm volatile("" : "+v"(lr));
         else asm volatile("" : "+v"(l));
-        if (LSE) asm volatile("" : "+v"(l32));
+        if (LSE) asm volatile("" : "+v"(ls32));
         // (tried and within noise: the first value operands of phase B requested at the end of this
         // phase; some of the vector instructions ahead of the first product)
 #pragma unroll
