@@ -138,9 +138,29 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
 
     // Tiles after every row this wave owns (causal), and all tiles where the window ends before its first
     // row, are not computed by it, but the wave still loads its share of them for the others and meets them
-    // at the barriers (second loop): the waves that have rows get the matrix cores for themselves (300
-    // rows, of which an eight-wave workgroup's second block holds 44: 300 causal rows of 12 heads x 128 86 -> 59 us).
-    const int t1w = qrow0 >= Wq ? t0 : CAUSAL ? min(t1, (qrow0 + 31) / BN + 1) : t1;
+    // at the barriers: the waves that have rows get the matrix cores for themselves (300 rows, of which an
+    // eight-wave workgroup's second block holds 44: 300 causal rows of 12 heads x 128 86 -> 59 us).
+    auto meet = [&](int t) __attribute__((always_inline)) {
+        wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+        if (NSTAGE == 2 && t + 1 < t1) issue(t + 1, (t - t0 + 1) % NSTAGE);
+        if (NSTAGE == 1 && t + 1 < t1) {
+            __builtin_amdgcn_s_barrier();
+            issue(t + 1, 0);
+        }
+    };
+    // A wave without rows does so in a loop of its own where that keeps the main loop's end apart from the
+    // tiles' end: in the two-wave shape at head dimension 64 a second bound made it 3 to 9 % slower, which
+    // windows of 33 to 64 rows, whose waves all have rows, paid for (32 heads x 36, 48 rows over 64000: 295 us
+    // without such waves, 318 with the second bound, 280 now).  At 128 the second bound is the faster form.
+    constexpr bool APART = NW == 2 && D == 64;
+    const bool rowless = qrow0 >= Wq;
+    if (APART && rowless) {
+        if (t0 < t1) issue(t0, 0);
+        for (int t = t0; t < t1; ++t) meet(t);
+        return;
+    }
+    const int t1w = !APART && rowless ? t0 : CAUSAL ? min(t1, (qrow0 + 31) / BN + 1) : t1;
     if (t0 < t1) issue(t0, 0);
     for (int t = t0; t < t1w; ++t) {
         const int n = t - t0;
@@ -234,15 +254,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
         }
     }
 
-    for (int t = max(t0, t1w); t < t1; ++t) {
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();
-        if (NSTAGE == 2 && t + 1 < t1) issue(t + 1, (t - t0 + 1) % NSTAGE);
-        if (NSTAGE == 1 && t + 1 < t1) {
-            __builtin_amdgcn_s_barrier();
-            issue(t + 1, 0);
-        }
-    }
+    for (int t = max(t0, t1w); (!APART || CAUSAL) && t < t1; ++t) meet(t);
 
     // ---- epilogue.  Accumulator register v of block db is d = 32*db + 8*(v/4) + 4*h + v%4.
     const float lt = xhalf_sum(l);
@@ -289,15 +301,18 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
     }
 }
 
+// Two waves, head dimension 64: three waves per SIMD instead of two (146 to 149 registers instead of 172).
 template <int D, int NW, bool CAUSAL>
-__global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnArgs a)
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && NW == 2 ? 3 : 1, 8)))
+void attn_f32_kernel(const AttnArgs a)
 {
     attn_f32_body<D, NW, CAUSAL>(a, blockIdx.x, gridDim.x);
 }
 
 // History partition blocks and window causal blocks of one call in a single launch.
 template <int D, int NW>
-__global__ __launch_bounds__(NW * 64) void attn_f32_pair_kernel(const PairArgs f)
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && NW == 2 ? 3 : 1, 8)))
+void attn_f32_pair_kernel(const PairArgs f)
 {
     // logical index of the window block this workgroup computes, or -1
     int win_block = (int)blockIdx.x < f.n_hist_blocks ? -1 : xcd_remap(blockIdx.x - f.n_hist_blocks, f.n_win_blocks);

@@ -7,7 +7,7 @@ import torch
 import oracle
 import tlin_inputs as ti
 import paper_2508_20407_amd as tl
-from helpers import assert_close
+from helpers import assert_close, f32_rel_bound
 from test_gpu_parity import padded
 
 pytestmark = pytest.mark.gpu
@@ -194,3 +194,30 @@ def test_causal_rows_are_convex_combinations(D, W):
     for mode in (tl.TLIN_COMBINE_SUM, tl.TLIN_COMBINE_JOINT):
         o = tl.tlin_slide_layer_attn(dev["Q"], dev["Kw"], ones, dev["Kw"], ones, W, combine=mode, **kw)
         assert (o - 1).abs().max().item() <= 1e-5
+
+
+@pytest.mark.parametrize("D", [36, 64, 100])
+@pytest.mark.parametrize("W", [9, 32, 33, 64])
+@pytest.mark.parametrize("N", [20, 1500, 9001])
+def test_two_wave_workgroups_in_fp32(D, W, N):
+    """fp32 windows of up to 64 rows, in workgroups whose second wave owns no row, one, or all of its rows:
+    history, window, both layers (over 9001 rows the window block rides on partition 0) and the sliding
+    schedule, whose last chunk is shorter."""
+    w = ti.Workload(f"two_waves_{D}_{W}_{N}", 1, 3, D, N, W, ti.F32, 1.0, 5454 + D + W + N)
+    host = ti.make(w)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    o = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale)
+    assert_close(o, oracle.history(host["Q"], host["Kh"], host["Vh"], w.dtype, w.scale)[0], w.dtype, f"{w.name} history")
+    o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
+    assert_close(o, oracle.window_causal(host["Q"], host["Kw"], host["Vw"], w.dtype, w.scale)[0], w.dtype, f"{w.name} window")
+    for mode, omode in ((tl.TLIN_COMBINE_SUM, oracle.SUM), (tl.TLIN_COMBINE_JOINT, oracle.JOINT)):
+        for splits in (0, 2):
+            o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=mode, scale=w.scale, num_splits=splits)
+            ro = oracle.layer(host["Q"], host["Kh"], host["Vh"], host["Kw"], host["Vw"], w.dtype, w.scale, omode)
+            assert_close(o, ro, w.dtype, f"{w.name} layer mode {mode} splits {splits}")
+    if N == 1500:
+        kh, vh = dev["Kh"], dev["Vh"]
+        o = tl.tlin_slide_layer_attn(kh, kh, vh, kh, vh, W, combine=tl.TLIN_COMBINE_JOINT, scale=w.scale)
+        nats = w.scale * float((host["Kh"].astype(np.float64) ** 2).sum(-1).max())      # a key row meets itself
+        assert_close(o, oracle.window_causal(host["Kh"], host["Kh"], host["Vh"], w.dtype, w.scale)[0], w.dtype, f"{w.name} slide",
+                     f32_rel=f32_rel_bound(nats))
