@@ -40,9 +40,10 @@
  *     accumulation on the matrix cores, softmax weights rounded to bf16 before the second product.
  *     Where one or two query rows meet a history of 1024 rows or more, tlin_history_attn may run on the
  *     vector unit instead (always at head dimension 128, below it by size): its weights and sums
- *     are fp32.  fp32 inputs use fp32 arithmetic throughout (fp32 matrix instructions, or fp32
- *     multiply-adds of the vector unit for up to eight query rows over a long history; nothing is
- *     rounded below fp32).
+ *     are fp32.  fp32 inputs: every operand of a product, the weights included, enters with its 24 bits (as three
+ *     bf16 parts on the matrix cores, six exact products of parts per product summed in fp32, the three below
+ *     2^-23 of it left out; or fp32 multiply-adds of the vector unit for up to eight query rows over a long history).
+ *     Parts below bf16's subnormals count as zero: values below 2^-110 keep an absolute precision of 2^-134.
  *   - Accuracy envelope.  bf16 inputs: |O - exact| <= 2e-2 (mean <= 5e-3) for inputs of unit
  *     scale.  fp32 inputs: a logit is an fp32 sum of D products and carries an absolute error of
  *     a few 2^-24 of its own size, which the exponential turns into the same RELATIVE error of

@@ -1,66 +1,79 @@
-// fp32 attention over one key partition on the gfx950 matrix cores, fp32 operands and fp32
-// accumulation throughout (v_mfma_f32_32x32x2_f32: no operand is rounded below fp32), for fp32
-// inputs.  Same online-softmax recurrence, same partial format and the same transposed mapping
-// as the bf16 kernel (Section 3 of the paper: softmax(scale * Q K^T) V; window keys masked with
-// j <= i).
+// fp32 attention over one key partition on the gfx950 matrix cores, for fp32 inputs.  Same online-softmax
+// recurrence, same partial format and the same transposed mapping as the bf16 kernel (Section 3 of the
+// paper: softmax(scale * Q K^T) V; window keys masked with j <= i).
 //
-// Mapping (wave64; a wave owns 32 query rows, lane = (query j = lane % 32, half h = lane / 32)):
-//   * A 32x32x2 product contracts over two indices, one per half-wave.  Which two is free as long
-//     as both operands agree, and the pairings are chosen so that no data ever moves between
-//     lanes:
-//       scores  S^T[key, query] = K Q^T : step (t, e) pairs d = 8t + e (h = 0) with d = 8t + 4 + e
-//               (h = 1).  A lane then needs K[key j][8t + 4h .. +3] - one 16-byte LDS read per four
-//               products - and Q[query j][8t + 4h .. +3], which it keeps in registers.
-//       values  O^T[d, query] += V^T P^T : the score accumulator leaves key 8g + 4h + e of the tile
-//               in register 4g + e of half h, so step (g, e) pairs key 8g + e with key 8g + 4 + e:
-//               the B operand is that accumulator register as it stands (after the exponential),
-//               and the A operand is V[key 8g + 4h + e][32 db + j], one 4-byte LDS read.
-//   * K/V tiles of 32 keys go HBM -> LDS directly (1 KB per wave instruction) through a ring of
-//     two tiles, one barrier per tile, as in the bf16 kernel (two-wave workgroups: one tile, two
-//     barriers).  LDS rows are XOR-swizzled per
-//     16-byte chunk on the source side of the load: K chunk ^ (row & 15), so that the 16 lanes of a
-//     128-bit read cover all 64 banks; V chunk ^ 8 for rows with bit 2 set, so that the two
-//     half-waves (rows 4 apart, same columns) read different halves of the bank sweep.
-//   * Tensors with a head dimension a.D below the kernel's D: a.D is a multiple of 4, so 16-byte
-//     chunks are either whole or absent; the places of absent chunks are cleared in LDS by the load
-//     (lane offsets beyond the tile descriptor's size: zeros, no memory request) and meet zero
-//     columns of Q, and output columns from a.D on are not stored.
+// Products.  A bf16 matrix instruction does sixteen times the work of an fp32 one, and an fp32 number is the
+// sum of three bf16 numbers without a remainder (8 + 8 + 8 bits of significand, the exponents have the same
+// range).  Every operand (Q, K, V and the weights) is split that way, and a product is the six bf16 products of
+// parts whose indices add up to at most two, exact in the fp32 accumulator; the three that are left out are
+// below 2^-23 of the product, of either sign, 2^-26 as a rule (the middle part is rounded to nearest).  Measured
+// against 64 bits the results are nearer than those of a chain of fp32 matrix instructions (32 heads x 128, 512
+// rows over 32768: 2-norm 1.3e-7 against 1.7e-7, largest 1.1e-6 against 1.6e-6; the same order at every size
+// tried): an accumulator is rounded once per sixteen products instead of once per two.
+//   32 heads x 128, 512 rows over 32768 history rows: 2398 -> 1395 us (199 TFLOP/s, 1.19 PFLOP/s of bf16
+//   products; the library's bf16 matrix product reaches 1.33 on this card, the power limit), 32 heads x 36, 64
+//   rows over 20000: 104 -> 72, causal, 16 heads x 128, 4096 rows: 1030 -> 436.
+//
+// Mapping (wave64; a wave owns 32 query rows; operand layouts as in attn_bf16_pipe_body):
+//   * Tiles of 32 keys.  A lane loads its share of a tile into registers (the tile after the next step's), splits
+//     it and writes three planes of bf16 rows to LDS, in the layout and swizzle of the bf16 kernels' K and V
+//     tiles: 48 KB of planes at D = 128.  The split costs 5.5 vector instructions per element, once per workgroup.
+//   * Two barriers per tile and a single buffer: while the score products read K(t), V(t) is split and written;
+//     while the value products read V(t), K(t+1) is.  The smaller workgroups share a compute unit, and one's
+//     softmax and barriers are hidden by the others' products.
+//   * Registers at D = 128: parts 0 and 1 of the queries 64, accumulator 64, scores 32 (leading and other
+//     products apart); part 2 of the queries, in one product of six, sits in LDS.
+//   * Tensors with a head dimension a.D below the kernel's D: see DP.  a.D is a multiple of 4, so 16-byte pieces of
+//     a row are whole or absent; absent ones lie beyond the tile descriptor's size (zeros, no memory request).
 #pragma once
-#include "common.h"
+#include "attn_bf16.h"
 
 namespace tlin {
 
-struct SwzF32 {
-    static __device__ __forceinline__ int k(int r) { return r & 15; }
-    static __device__ __forceinline__ int v(int r) { return ((r >> 2) & 1) << 3; }
-};
+// x = p[0] + p[1] + p[2] exactly, each part four bf16 values: the leading 8 bits as they stand, the next 8 rounded
+// to nearest (so that what lies below them carries no common sign), and the rest.
+__device__ __forceinline__ void split4(f32x4 x, u32x2 (&p)[3])
+{
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const float x0 = x[2 * e], x1 = x[2 * e + 1];
+        const unsigned u0 = __builtin_bit_cast(unsigned, x0), u1 = __builtin_bit_cast(unsigned, x1);
+        p[0][e] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+        const float r0 = x0 - __builtin_bit_cast(float, u0 & 0xffff0000u), r1 = x1 - __builtin_bit_cast(float, u1 & 0xffff0000u);
+        const bf16x2 b = {(__bf16)r0, (__bf16)r1};
+        const unsigned ub = __builtin_bit_cast(unsigned, b);
+        p[1][e] = ub;
+        const bf16x2 c = {(__bf16)(r0 - __builtin_bit_cast(float, ub << 16)), (__bf16)(r1 - __builtin_bit_cast(float, ub & 0xffff0000u))};
+        p[2][e] = __builtin_bit_cast(unsigned, c);
+    }
+}
 
 // The work of one workgroup; `bid` of `nblocks` is its index among the blocks of this problem set.
+// DP: 0 where the tensors' head dimension a.D is the kernel's D.  Where it is smaller, the columns that are
+// computed: at least a.D, a multiple of 16; rows keep the kernel's D elements in LDS.
 // REMAP: bid is a hardware block index (mapped to a logical one here); otherwise it is the logical index.
-template <int D, int NW, bool CAUSAL, bool REMAP = true>
+template <int D, int NW, bool CAUSAL, int DP, bool REMAP = true>
 __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nblocks)
 {
     constexpr int BN = 32;                 // keys per tile
     constexpr int BM = NW * 32;            // query rows per workgroup
-    constexpr int ROWB = D * 4;            // bytes per K/V row
-    constexpr int TILE_B = BN * ROWB;
-    constexpr int CPR = ROWB / 16;         // 16-byte chunks per row
-    constexpr int RPI = 1024 / ROWB;       // rows moved by one wave-wide direct load
-    constexpr int NDMA = BN / RPI / NW;    // direct loads per wave per tensor per tile
-    static_assert(BN % (RPI * NW) == 0 && NDMA >= 1, "tile does not divide over the waves");
-    // Two-wave workgroups (few query rows) keep a single tile in LDS, so that four of them share a
-    // compute unit and every SIMD has two waves: their loads are hidden by the other workgroups.
-    constexpr int NSTAGE = NW == 2 ? 1 : 2;
-    constexpr int DT = D / 8;              // 16-byte operand fragments per row and half-wave
-    constexpr int DB = D / 32;             // 32-row blocks of O^T
-    static_assert(2 * NDMA < 64, "too many loads in flight for vmcnt");
+    constexpr int ROWB = D * 2;            // bytes per row of a plane
+    constexpr int PLANE_B = BN * ROWB;
+    constexpr int DU = DP ? DP : D;        // columns computed
+    constexpr int DS = DU / 16;            // contraction steps of Q K^T
+    constexpr int DB = (DU + 31) / 32;     // 32-row blocks of O^T
+    constexpr int CPR = D / 4;             // 16-byte pieces of a row in memory
+    constexpr int NLD = BN * CPR / (NW * 64);   // pieces of a tile of K (and of V) that a lane loads and splits
+    constexpr int LROWS = NW * 64 / CPR;   // tile rows covered by one load of the workgroup
+    static_assert(NLD >= 1 && BN % LROWS == 0, "tile does not divide over the threads");
 
     char *const Ks = tlin_smem;
-    char *const Vs = tlin_smem + NSTAGE * TILE_B;
+    char *const Vs = Ks + 3 * PLANE_B;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 31, h = lane >> 5;
+    char *const Q2 = Vs + 3 * PLANE_B + wave * (DS * 1024);
 
     const int L = REMAP ? xcd_remap(bid, nblocks) : bid;
     const Problem pr = decode_problem<BM, BN, CAUSAL>(a, L, a.nqb);
@@ -77,45 +90,52 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
     const char *Kg = (const char *)((const float *)a.K + (int64_t)b * a.k_sb + (int64_t)hd * a.k_sh) + pr.krow_off * k_rb;
     const char *Vg = (const char *)((const float *)a.V + (int64_t)b * a.v_sb + (int64_t)hd * a.v_sh) + pr.krow_off * v_rb;
 
-    // ---- Q^T fragments (B operand of the score product), register resident
+    // ---- Q^T fragments (B operand of the score product): lane holds query j, columns 16 s + 8 h .. + 7.  Parts
+    // 0 and 1 stay in registers, part 2 (one product in six) in LDS, each wave its own.
     const int qrow0 = qb * BM + wave * 32;
-    f32x4 qf[DT];
+    bf16x8 q0[DS], q1[DS];
     {
         const int r = min(qrow0 + j, Wq - 1);
-        const float *qp = Qg + (int64_t)r * a.q_sr + 4 * h;
+        const float *qp = Qg + (int64_t)r * a.q_sr + 8 * h;
 #pragma unroll
-        for (int t = 0; t < DT; ++t)
-            qf[t] = 8 * t + 4 * h < a.D ? *(const f32x4 *)(qp + 8 * t) : f32x4{0.f, 0.f, 0.f, 0.f};
-        // consume the registers here, so that the wait for these loads sits before the tile loop
+        for (int s = 0; s < DS; ++s) {
+            u32x2 p[2][3];
 #pragma unroll
-        for (int t = 0; t < DT; ++t) asm volatile("" : "+v"(qf[t]));
+            for (int e = 0; e < 2; ++e)
+                split4(16 * s + 8 * h + 4 * e < a.D ? *(const f32x4 *)(qp + 16 * s + 4 * e) : f32x4{0.f, 0.f, 0.f, 0.f}, p[e]);
+            q0[s] = __builtin_bit_cast(bf16x8, u32x4{p[0][0][0], p[0][0][1], p[1][0][0], p[1][0][1]});
+            q1[s] = __builtin_bit_cast(bf16x8, u32x4{p[0][1][0], p[0][1][1], p[1][1][0], p[1][1][1]});
+            *(u32x4 *)(Q2 + s * 1024 + lane * 16) = u32x4{p[0][2][0], p[0][2][1], p[1][2][0], p[1][2][1]};
+        }
     }
 
-    // ---- direct loads: load i of this wave covers tile rows (wave*NDMA + i)*RPI .. +RPI-1; this lane
-    // lands on chunk position lane % CPR of row drow and fetches chunk (lane % CPR) ^ swz(row)
-    const int dchunks = a.D / 4;
-    unsigned koff[NDMA], voff[NDMA];
+    // ---- tile loads: load i of this lane is piece `lc` of tile row i * LROWS + lr, in memory and in LDS
+    const int lr = tid / CPR, lc = tid % CPR;
+    // pieces beyond the rows' end: an offset beyond every tile descriptor (a tile is below 2^30 bytes), zeros
+    const unsigned koff = 4 * lc < a.D ? (unsigned)(lr * k_rb) + 16 * lc : 0x80000000u;
+    const unsigned voff = 4 * lc < a.D ? (unsigned)(lr * v_rb) + 16 * lc : 0x80000000u;
+    const unsigned krow_step = (unsigned)(LROWS * k_rb), vrow_step = (unsigned)(LROWS * v_rb);
+    auto load_tile = [&](f32x4 (&x)[NLD], const char *base, int64_t rb, unsigned off, unsigned step, int t) __attribute__((always_inline)) {
+        const int key0 = t * BN, rows = min(BN, NK - key0);      // rows past the end of the tensor arrive as zeros
+        auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(base + key0 * rb), 0, (int)(rows * rb), 0x00020000);
 #pragma unroll
-    for (int i = 0; i < NDMA; ++i) {
-        const int drow = (wave * NDMA + i) * RPI + lane / CPR;
-        const int kc = (lane % CPR) ^ SwzF32::k(drow), vc = (lane % CPR) ^ SwzF32::v(drow);
-        koff[i] = kc >= dchunks ? kNoChunk : (unsigned)(drow * k_rb) + (kc << 4);
-        voff[i] = vc >= dchunks ? kNoChunk : (unsigned)(drow * v_rb) + (vc << 4);
-    }
-    auto issue = [&](int t, int stage) __attribute__((always_inline)) {
-        const int key0 = t * BN;
-        const unsigned kdst = __builtin_amdgcn_readfirstlane(lds_offset(Ks) + stage * TILE_B + wave * (NDMA * 1024));
-        const unsigned vdst = kdst + NSTAGE * TILE_B;
-        // rows past the end of the tensor lie beyond the descriptor's size and arrive as zeros
-        const int rows = min(BN, NK - key0);
-        const u32x4 kd = tile_descriptor(Kg + key0 * k_rb, (a.D < D || rows < BN) ? (unsigned)(rows * k_rb) : 0xffffffffu);
-        const u32x4 vd = tile_descriptor(Vg + key0 * v_rb, (a.D < D || rows < BN) ? (unsigned)(rows * v_rb) : 0xffffffffu);
-#pragma unroll
-        for (int i = 0; i < NDMA; ++i) {
-            direct_load_1k(kd, koff[i], kdst + i * 1024);
-            direct_load_1k(vd, voff[i], vdst + i * 1024);
-        }
+        for (int i = 0; i < NLD; ++i)
+            x[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + i * step, 0, 0));
     };
+    auto store_piece = [&](f32x4 x, char *planes, int row, int swz) __attribute__((always_inline)) {
+        u32x2 p[3];
+        split4(x, p);
+        char *dst = planes + row * ROWB + (((lc >> 1) ^ swz) << 4) + 8 * (lc & 1);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *(u32x2 *)(dst + k * PLANE_B) = p[k];
+    };
+    f32x4 kx[NLD], vx[NLD];
+    auto load_k = [&](int t) __attribute__((always_inline)) { load_tile(kx, Kg, k_rb, koff, krow_step, t); };
+    auto load_v = [&](int t) __attribute__((always_inline)) { load_tile(vx, Vg, v_rb, voff, vrow_step, t); };
+    auto put_k = [&](int i) __attribute__((always_inline)) { store_piece(kx[i], Ks, i * LROWS + lr, Swz<D>::k(i * LROWS + lr)); };
+    auto put_v = [&](int i) __attribute__((always_inline)) { store_piece(vx[i], Vs, i * LROWS + lr, Swz<D>::v(i * LROWS + lr)); };
+    // this wave's LDS writes are done, then every wave's are (and every wave is past its reads)
+    auto meet = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     // ---- state: running maximum (raw logit units), running sum, O^T accumulator
     float m = -INFINITY, l = 0.f;
@@ -129,70 +149,65 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
     // gives the same normalised result.
     const float thr = 8.0f / a.c;
 
-    // per-lane parts of the LDS addresses
-    const unsigned kfrag = j * ROWB;                       // + ((2t + h) ^ k(j)) * 16
-    const int ksw = SwzF32::k(j);
-    unsigned vfrag[DB];                                    // + key * ROWB
+    // LDS addresses: K fragment of step s, key j, columns 16 s + 8 h .. + 7; V operand of column block db, see
+    // attn_bf16_pipe_body
+    typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+    const int i16 = lane & 15, blk1 = (lane >> 4) & 1;
+    unsigned kaddr[DS], vaddr[DB];
 #pragma unroll
-    for (int db = 0; db < DB; ++db) vfrag[db] = 128 * (db ^ h) + 4 * j + 4 * h * ROWB;   // row 4h, chunk ^ 8h
+    for (int s = 0; s < DS; ++s) kaddr[s] = lds_offset(Ks) + j * ROWB + (((2 * s + h) ^ Swz<D>::k(j)) << 4);
+    {
+        const int r0 = 4 * h + (i16 >> 2);
+        const int sw = Swz<D>::v(r0) << 4;           // the same for rows r0 + 8 k
+#pragma unroll
+        for (int db = 0; db < DB; ++db) vaddr[db] = lds_offset(Vs) + r0 * ROWB + ((64 * db + 32 * blk1 + 8 * (i16 & 3)) ^ sw);
+    }
+    const unsigned q2addr = lds_offset(Q2) + lane * 16;
+    auto k_read = [&](int s, int plane) __attribute__((always_inline)) { return *(lds_bf16x8 *)(uintptr_t)(kaddr[s] + plane * PLANE_B); };
+    auto v_read = [&](int db, int t2, int plane) __attribute__((always_inline)) {
+        const unsigned ad = vaddr[db] + plane * PLANE_B + t2 * (16 * ROWB);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)ad);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)(ad + 8 * ROWB));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto mma = [](bf16x8 x, bf16x8 y, f32x16 c) __attribute__((always_inline)) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0); };
 
     // Tiles after every row this wave owns (causal), and all tiles where the window ends before its first
-    // row, are not computed by it, but the wave still loads its share of them for the others and meets them
-    // at the barriers: the waves that have rows get the matrix cores for themselves (300 rows, of which an
-    // eight-wave workgroup's second block holds 44: 300 causal rows of 12 heads x 128 86 -> 59 us).
-    auto meet = [&](int t) __attribute__((always_inline)) {
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();
-        if (NSTAGE == 2 && t + 1 < t1) issue(t + 1, (t - t0 + 1) % NSTAGE);
-        if (NSTAGE == 1 && t + 1 < t1) {
-            __builtin_amdgcn_s_barrier();
-            issue(t + 1, 0);
-        }
-    };
-    // A wave without rows does so in a loop of its own where that keeps the main loop's end apart from the
-    // tiles' end: in the two-wave shape at head dimension 64 a second bound made it 3 to 9 % slower, which
-    // windows of 33 to 64 rows, whose waves all have rows, paid for (32 heads x 36, 48 rows over 64000: 295 us
-    // without such waves, 318 with the second bound, 280 now).  At 128 the second bound is the faster form.
-    constexpr bool APART = NW == 2 && D == 64;
-    const bool rowless = qrow0 >= Wq;
-    if (APART && rowless) {
-        if (t0 < t1) issue(t0, 0);
-        for (int t = t0; t < t1; ++t) meet(t);
-        return;
+    // row, are not computed by it, but the wave still loads and splits its share of them for the others and meets
+    // them at the barriers: the waves that have rows get the matrix cores for themselves.
+    const int t1w = qrow0 >= Wq ? t0 : CAUSAL ? min(t1, (qrow0 + 31) / BN + 1) : t1;
+    if (t0 < t1) {
+        load_k(t0);
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) put_k(i);
+        load_v(t0);
+        meet();
     }
-    const int t1w = !APART && rowless ? t0 : CAUSAL ? min(t1, (qrow0 + 31) / BN + 1) : t1;
-    if (t0 < t1) issue(t0, 0);
-    for (int t = t0; t < t1w; ++t) {
-        const int n = t - t0;
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();      // tile t is complete, and (two stages) every wave has left tile t-1
-        if (NSTAGE == 2 && t + 1 < t1) issue(t + 1, (n + 1) % NSTAGE);
+    int t = t0;
+    for (; t < t1w; ++t) {
+        const int tn = min(t + 1, t1 - 1);     // behind the last tile it is loaded once more, and nobody reads it
         const int key0 = t * BN;
-        const char *Kt = Ks + (n % NSTAGE) * TILE_B;
-        const char *Vt = Vs + (n % NSTAGE) * TILE_B;
-
-        // ---- scores S^T = K Q^T
-        // The contraction over D runs as chains of 32 terms, each started from zero and added to
-        // the total when complete: the rounding error of an fp32 chain grows with its length, and
-        // the error of a score is what limits the accuracy of the weights (short rows most of all,
-        // where nothing averages out).
-        f32x16 s;
+        // ---- scores S^T = K Q^T, the tile's values split and written meanwhile.  The products of the leading
+        // parts and the others are summed apart: the latter are 2^-8 of the former and cost no accuracy.
+        load_k(tn);
+        f32x16 s, lo;
 #pragma unroll
-        for (int c4 = 0; c4 < DT / 4; ++c4) {
-            f32x16 part;
+        for (int v = 0; v < 16; ++v) s[v] = lo[v] = 0.f;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) part[v] = 0.f;
+        for (int c = 0; c < DS; ++c) {
+            const bf16x8 k0 = k_read(c, 0), k1 = k_read(c, 1), k2 = k_read(c, 2);
+            const bf16x8 q2 = *(lds_bf16x8 *)(uintptr_t)(q2addr + c * 1024);
+            lo = mma(k0, q1[c], lo);
+            s = mma(k0, q0[c], s);
+            lo = mma(k1, q0[c], lo);
+            lo = mma(k1, q1[c], lo);
+            lo = mma(k0, q2, lo);
+            lo = mma(k2, q0[c], lo);
 #pragma unroll
-            for (int t8 = 4 * c4; t8 < 4 * c4 + 4; ++t8) {
-                const f32x4 kf = *(const f32x4 *)(Kt + kfrag + (((2 * t8 + h) ^ ksw) << 4));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) part = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[t8][e], part, 0, 0, 0);
-            }
-            if (c4 == 0) s = part;
-            else
-#pragma unroll
-                for (int v = 0; v < 16; ++v) s[v] += part[v];
+            for (int i = c * NLD / DS; i < (c + 1) * NLD / DS; ++i) put_v(i);
         }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] += lo[v];
 
         // ---- mask: keys past the end of the tensor, and (causal) keys after the query row
         const int row = qrow0 + j;
@@ -222,39 +237,67 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
         // (s - m) * c rather than fma(s, c, -m*c): the key that holds the maximum gets weight exactly 1
         const float mref = (m == -INFINITY) ? 0.f : m;
         float ls = 0.f;
+        bf16x8 pw[2][3];      // weights, B-operand order, split
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            s[v] = fast_exp2((s[v] - mref) * a.c);
-            ls += s[v];
+        for (int t2 = 0; t2 < 2; ++t2) {
+            u32x2 p[2][3];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                f32x4 w;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    w[v] = fast_exp2((s[8 * t2 + 4 * e + v] - mref) * a.c);
+                    ls += w[v];
+                }
+                split4(w, p[e]);
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) pw[t2][k] = __builtin_bit_cast(bf16x8, u32x4{p[0][k][0], p[0][k][1], p[1][k][0], p[1][k][1]});
         }
         l += ls;
+        meet();
 
-        // ---- O^T += V^T P^T: register 4g + e of this half-wave is key 8g + 4h + e.  The tile's
-        // product is summed on its own and then added to the running accumulator: two short
-        // summation chains (16 steps, then one addition per tile) round less than one long one.
+        // ---- O^T += V^T P^T, the next tile's keys split and written meanwhile.  The tile's product is summed on
+        // its own, small parts first, and then added to the running accumulator: short summation chains round
+        // less than one long one.
+        load_v(tn);
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             f32x16 pv;
 #pragma unroll
             for (int v = 0; v < 16; ++v) pv[v] = 0.f;
+            bf16x8 v0[2];
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
+            for (int t2 = 0; t2 < 2; ++t2) {
+                const bf16x8 v1 = v_read(db, t2, 1), v2 = v_read(db, t2, 2);
+                v0[t2] = v_read(db, t2, 0);
+                pv = mma(v2, pw[t2][0], pv);
+                pv = mma(v1, pw[t2][1], pv);
+                pv = mma(v0[t2], pw[t2][2], pv);
+                pv = mma(v1, pw[t2][0], pv);
+                pv = mma(v0[t2], pw[t2][1], pv);
+            }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float vf = *(const float *)(Vt + vfrag[db] + (8 * g + e) * ROWB);
-                    pv = __builtin_amdgcn_mfma_f32_32x32x2f32(vf, s[4 * g + e], pv, 0, 0, 0);
-                }
+            for (int t2 = 0; t2 < 2; ++t2) pv = mma(v0[t2], pw[t2][0], pv);
 #pragma unroll
             for (int v = 0; v < 16; ++v) oacc[db][v] += pv[v];
-            __builtin_amdgcn_sched_barrier(0);     // keeps the next block's V reads (registers) behind this block
+#pragma unroll
+            for (int i = db * NLD / DB; i < (db + 1) * NLD / DB; ++i) put_k(i);
         }
-        if (NSTAGE == 1 && t + 1 < t1) {
-            __builtin_amdgcn_s_barrier();          // every wave has left the tile that is overwritten now
-            issue(t + 1, 0);
-        }
+        meet();
     }
-
-    for (int t = max(t0, t1w); (!APART || CAUSAL) && t < t1; ++t) meet(t);
+    // the remaining tiles of a wave that does not compute on them
+    for (; t < t1; ++t) {
+        const int tn = min(t + 1, t1 - 1);
+        load_k(tn);
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) put_v(i);
+        meet();
+        load_v(tn);
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) put_k(i);
+        meet();
+    }
 
     // ---- epilogue.  Accumulator register v of block db is d = 32*db + 8*(v/4) + 4*h + v%4.
     const float lt = xhalf_sum(l);
@@ -268,7 +311,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int d = 32 * db + 8 * g + 4 * h;
-                if (d >= a.D) continue;            // column beyond the tensors' head dimension
+                if (DP && d >= a.D) continue;      // column beyond the tensors' head dimension
                 f32x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = oacc[db][4 * g + e] * inv;
@@ -301,23 +344,26 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
     }
 }
 
-// Two waves, head dimension 64: three waves per SIMD instead of two (146 to 149 registers instead of 172).
-template <int D, int NW, bool CAUSAL>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && NW == 2 ? 3 : 1, 8)))
+// Waves per SIMD that the registers are cut for: at head dimension 128 the LDS of a two-wave workgroup allows no
+// more than one, and the others' 512 threads two; at 64 three, two in the two-wave shape, whose lanes hold more of a tile.
+constexpr int f32_waves_per_simd(int D, int NW) { return D == 128 ? (NW == 2 ? 1 : 2) : (NW == 4 ? 3 : 2); }
+
+template <int D, int NW, bool CAUSAL, int DP>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(f32_waves_per_simd(D, NW), 8)))
 void attn_f32_kernel(const AttnArgs a)
 {
-    attn_f32_body<D, NW, CAUSAL>(a, blockIdx.x, gridDim.x);
+    attn_f32_body<D, NW, CAUSAL, DP>(a, blockIdx.x, gridDim.x);
 }
 
 // History partition blocks and window causal blocks of one call in a single launch.
-template <int D, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && NW == 2 ? 3 : 1, 8)))
+template <int D, int NW, int DP>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(f32_waves_per_simd(D, NW), 8)))
 void attn_f32_pair_kernel(const PairArgs f)
 {
     // logical index of the window block this workgroup computes, or -1
     int win_block = (int)blockIdx.x < f.n_hist_blocks ? -1 : xcd_remap(blockIdx.x - f.n_hist_blocks, f.n_win_blocks);
     if ((int)blockIdx.x < f.n_hist_blocks) {
-        attn_f32_body<D, NW, false>(f.hist, blockIdx.x, f.n_hist_blocks);
+        attn_f32_body<D, NW, false, DP>(f.hist, blockIdx.x, f.n_hist_blocks);
         if (f.hist.fuse_window) {
             // the workgroup of partition 0 goes on to the window's causal block of the same rows
             // (causal blocks are numbered from the last query block down)
@@ -328,7 +374,7 @@ void attn_f32_pair_kernel(const PairArgs f)
             }
         }
     }
-    if (win_block >= 0) attn_f32_body<D, NW, true, false>(f.win, win_block, 0);
+    if (win_block >= 0) attn_f32_body<D, NW, true, DP, false>(f.win, win_block, 0);
 }
 
 }  // namespace tlin

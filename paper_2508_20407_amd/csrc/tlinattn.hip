@@ -76,27 +76,30 @@ int dpad(int D) { return D <= 64 ? 64 : 128; }
 // Keys per tile: 32 KB of K and V per tile in both kernels.  Query rows per workgroup: the same
 // shapes for both input types.
 int key_tile(int in_dtype, int) { return in_dtype == TLIN_F32 ? 32 : 64; }
-// bf16 at head dimension 64 and below stays with four waves for long windows too: its pipelined body
-// takes 153 registers, so three waves fit a SIMD, which is three four-wave workgroups per compute
-// unit but only one of eight waves (12 heads x 36, 256 window rows over 131072 / 999754 history
-// rows: 0.135 / 0.911 ms per step against 0.148 / 0.940 ms with eight-wave workgroups).
+// At head dimension 64 and below long windows stay with four waves too.  bf16: the pipelined body takes 153
+// registers, so three waves fit a SIMD, which is three four-wave workgroups per compute unit but only one
+// of eight waves (12 heads x 36, 256 window rows over 131072 / 999754 history rows: 0.135 / 0.911 ms per step
+// against 0.148 / 0.940 ms with eight-wave workgroups).  fp32, the same with 164 registers: long unmasked windows
+// take equal times (32 heads x 64, 512 rows over 20000: 482 us, eight waves 483), causal and ragged ones gain (16
+// heads, 4096 causal rows: 240 against 310; 300 rows over 20000: 330 against 415).
 Shape kernel_shape(int in_dtype, int W, int D)
 {
     const Shape s = wave_shape(W);
-    if (in_dtype == TLIN_BF16 && dpad(D) == 64 && s.nw == 8) return {4, 1};
+    if (dpad(D) == 64 && s.nw == 8) return {4, 1};
     return s;
 }
-// A causal launch of its own in bf16 with fewer than four eight-wave workgroups per compute unit runs in
+// A causal launch of its own with fewer than four eight-wave workgroups per compute unit runs in
 // four-wave ones: two of them share a compute unit, so that the start of one (queries and first tiles
 // on the way), its diagonal tiles, where half of the waves have nothing to do, and its output are hidden
 // by the other's products (8 heads x 128, 1024 rows: 26.4 -> 18.6 us; 32 heads, 4096 rows: 162 -> 145 us).
 // Beyond that the starts no longer count and the larger workgroup's fewer tile loads are ahead (32 heads,
-// 8192 rows: 472 against 487 us).
+// 8192 rows: 472 against 487 us).  fp32 the same: 16 heads x 128, 4096 rows 558 -> 436 us; 32 heads, 8192 rows
+// 2834 with eight waves, 2873 with four.
 Shape causal_shape(const tlin_params *p)
 {
     const Shape s = kernel_shape(p->in_dtype, p->W, p->D);
     const int64_t blocks = (int64_t)p->B * p->H * ((p->W + s.bm() - 1) / s.bm());
-    return p->in_dtype == TLIN_BF16 && s.nw == 8 && blocks < 4 * kNumCU ? Shape{4, 1} : s;
+    return s.nw == 8 && blocks < 4 * kNumCU ? Shape{4, 1} : s;
 }
 int query_block(int in_dtype, int W, int D) { return kernel_shape(in_dtype, W, D).bm(); }
 
@@ -104,12 +107,11 @@ int query_block(int in_dtype, int W, int D) { return kernel_shape(in_dtype, W, D
 int resident_wgs(int in_dtype, int W, int D)
 {
     if (in_dtype == TLIN_F32) {
-        // fp32 kernel: two waves per SIMD keep the matrix cores busy (8 waves per compute unit); its
-        // tile ring takes 64 KB of the 160 KB of LDS at D = 128 and 32 KB at D = 64 (half of that in
-        // the two-wave shape)
-        const int nw = wave_shape(W).nw;
-        const int by_waves = 8 / nw, by_lds = (dpad(D) == 128 ? 2 : 4) * (nw == 2 ? 2 : 1);
-        return kNumCU * (by_waves < by_lds ? by_waves : by_lds);
+        // fp32: LDS, 160 KB (D = 128: 48 KB of planes and 8 KB per wave, half of that at 64), and the registers
+        // (f32_waves_per_simd)
+        const int nw = kernel_shape(in_dtype, W, D).nw;
+        if (dpad(D) == 128) return kNumCU * (nw == 8 ? 1 : 2);
+        return kNumCU * (nw == 4 ? 3 : 4);
     }
     // head dimension 64: tiles and register sets are half as large, three workgroups share a
     // compute unit (measured best for few heads); 128: an eight-wave workgroup fills a compute unit
@@ -463,15 +465,29 @@ tlin_status launch_bf16(const AttnArgs &a, Shape s, int grid, hipStream_t st)
     return launch_bf16_shape<D, 2, 1, CAUSAL, 2>(a, grid, st);
 }
 
-// fp32 kernel: a ring of two 32-key tiles of K and V (64 KB at D = 128, no attribute needed).
+// fp32 kernel: three bf16 planes of a 32-key tile of K and of V, and part 2 of the waves' queries.
+template <int D, int DP> constexpr int f32_lds_bytes(int nw) { return 2 * 3 * 32 * D * 2 + nw * ((DP ? DP : D) / 16) * 1024; }
+
+template <int D, int NW, bool CAUSAL>
+tlin_status launch_f32_shape(const AttnArgs &a, int grid, hipStream_t st)
+{
+    return with_columns<D>(a.D, [&](auto dp) {
+        constexpr int DP = decltype(dp)::value, lds_bytes = f32_lds_bytes<D, DP>(NW);
+        static_assert(lds_bytes <= 160 * 1024, "fp32 planes exceed the 160 KB of a gfx950 compute unit");
+        static std::atomic<uint64_t> lds_allowed{0};
+        const void *kernel = (const void *)attn_f32_kernel<D, NW, CAUSAL, DP>;
+        if (allow_lds(kernel, lds_bytes, lds_allowed) != TLIN_OK) return TLIN_ERR_HIP;
+        return launch_kernel(kernel, dim3(grid), dim3(NW * 64), lds_bytes, st, a);
+    });
+}
 template <int D, bool CAUSAL>
 tlin_status launch_f32(const AttnArgs &a, Shape s, int grid, hipStream_t st)
 {
-    constexpr int lds_bytes = 2 * 2 * 32 * D * 4;    // the two-wave shape keeps one tile: half of it
-    static_assert(lds_bytes <= 64 * 1024, "fp32 tile ring must fit the default dynamic LDS limit");
-    if (s.nw == 8) return launch_kernel((const void *)attn_f32_kernel<D, 8, CAUSAL>, dim3(grid), dim3(512), lds_bytes, st, a);
-    if (s.nw == 4) return launch_kernel((const void *)attn_f32_kernel<D, 4, CAUSAL>, dim3(grid), dim3(256), lds_bytes, st, a);
-    return launch_kernel((const void *)attn_f32_kernel<D, 2, CAUSAL>, dim3(grid), dim3(128), lds_bytes / 2, st, a);
+    if constexpr (D == 128) {
+        if (s.nw == 8) return launch_f32_shape<D, 8, CAUSAL>(a, grid, st);
+    }
+    if (s.nw == 4) return launch_f32_shape<D, 4, CAUSAL>(a, grid, st);
+    return launch_f32_shape<D, 2, CAUSAL>(a, grid, st);
 }
 
 // Window blocks launched behind the history blocks run when the compute units are already taken, as
@@ -492,19 +508,30 @@ bool fuses_window(int in_dtype, const PairArgs &f, int BM, int BN, int quarters)
     return tiles / ns >= (full ? cost + 2 : 4 * cost);
 }
 
+template <int D, int NW>
+tlin_status launch_f32_pair_shape(const PairArgs &f, hipStream_t st)
+{
+    return with_columns<D>(f.hist.D, [&](auto dp) {
+        constexpr int DP = decltype(dp)::value, lds_bytes = f32_lds_bytes<D, DP>(NW);
+        static std::atomic<uint64_t> lds_allowed{0};
+        const void *kernel = (const void *)attn_f32_pair_kernel<D, NW, DP>;
+        if (allow_lds(kernel, lds_bytes, lds_allowed) != TLIN_OK) return TLIN_ERR_HIP;
+        return launch_kernel(kernel, dim3(f.n_hist_blocks + f.n_win_blocks), dim3(NW * 64), lds_bytes, st, f);
+    });
+}
 template <int D>
 tlin_status launch_f32_pair(const PairArgs &f, Shape s, hipStream_t st)
 {
-    constexpr int lds_bytes = 2 * 2 * 32 * D * 4;
     PairArgs g = f;
     if (fuses_window(TLIN_F32, f, s.nw * 32, 32, 4)) {
         g.hist.fuse_window = 1;
         g.n_win_blocks = 0;
     }
-    const dim3 grid(g.n_hist_blocks + g.n_win_blocks);
-    if (s.nw == 8) return launch_kernel((const void *)attn_f32_pair_kernel<D, 8>, grid, dim3(512), lds_bytes, st, g);
-    if (s.nw == 4) return launch_kernel((const void *)attn_f32_pair_kernel<D, 4>, grid, dim3(256), lds_bytes, st, g);
-    return launch_kernel((const void *)attn_f32_pair_kernel<D, 2>, grid, dim3(128), lds_bytes / 2, st, g);
+    if constexpr (D == 128) {
+        if (s.nw == 8) return launch_f32_pair_shape<D, 8>(g, st);
+    }
+    if (s.nw == 4) return launch_f32_pair_shape<D, 4>(g, st);
+    return launch_f32_pair_shape<D, 2>(g, st);
 }
 
 // Key tiles the resident variant keeps in LDS (128 KB of keys and values).

@@ -221,3 +221,26 @@ def test_two_wave_workgroups_in_fp32(D, W, N):
         nats = w.scale * float((host["Kh"].astype(np.float64) ** 2).sum(-1).max())      # a key row meets itself
         assert_close(o, oracle.window_causal(host["Kh"], host["Kh"], host["Vh"], w.dtype, w.scale)[0], w.dtype, f"{w.name} slide",
                      f32_rel=f32_rel_bound(nats))
+
+
+@pytest.mark.parametrize("D", [16, 36, 48, 64, 80, 96, 100, 128])
+@pytest.mark.parametrize("W", [32, 65, 129, 257])
+def test_fp32_operands_in_parts(D, W):
+    """fp32 operands are multiplied as three bf16 parts.  A part or a product of parts that got lost leaves 2^-17 of
+    single terms or more (2-norm above 2e-6); with all of them the 2-norm error is that of fp32 sums, a few 2^-24
+    (measured up to 2.2e-7, bound 2^-21).  And the split commutes with powers of two: inputs scaled by them, far up and
+    down the exponent range, give the same bits."""
+    w = ti.Workload(f"parts_{D}_{W}", 1, 2, D, 1111, W, ti.F32, 1.0, 6363 + D + W)
+    host = ti.make(w)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    q, kh, vh, kw, vw = (dev[k] for k in ("Q", "Kh", "Vh", "Kw", "Vw"))
+    for call, ref in ((lambda q, k, v: tl.tlin_history_attn(q, k, v, scale=w.scale), oracle.history),
+                      (lambda q, k, v: tl.tlin_window_causal_attn(q, k, v, scale=w.scale), oracle.window_causal)):
+        k, v, hk, hv = (kh, vh, "Kh", "Vh") if ref is oracle.history else (kw, vw, "Kw", "Vw")
+        o = call(q, k, v)
+        r = ref(host["Q"], host[hk], host[hv], w.dtype, w.scale)[0]
+        d = o.cpu().numpy().astype(np.float64) - r
+        assert np.sqrt((d * d).sum() / (r * r).sum()) <= 2.0 ** -21
+        for eq, ev in ((60, 90), (-60, -90), (20, 0)):
+            sq, sk, sv = padded(host["Q"] * np.float32(2.0 ** eq), w.dtype), padded(host[hk] * np.float32(2.0 ** -eq), w.dtype), padded(host[hv] * np.float32(2.0 ** ev), w.dtype)
+            assert torch.equal(call(sq, sk, sv), o * 2.0 ** ev), (eq, ev)
