@@ -412,7 +412,8 @@ tlin_status with_columns(int dim, F &&f)
 template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT, int DP, bool NT, bool LSE = false>
 tlin_status launch_bf16_kernel(const AttnArgs &a, int grid, hipStream_t st)
 {
-    constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2;
+    // the ring and, in the pipelined body, one word behind it
+    constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2 + (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>() ? 16 : 0);
     static_assert(lds_bytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a gfx950 compute unit");
     auto kernel = attn_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, NT, LSE>;
     static std::atomic<uint64_t> lds_allowed{0};
@@ -429,10 +430,10 @@ tlin_status launch_bf16_shape(const AttnArgs &a, int grid, hipStream_t st)
         constexpr int DP = decltype(dp)::value;
         if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) {
             if constexpr (!CAUSAL) {
-                if (a.stream_once) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, true>(a, grid, st);
-            } else if constexpr (D == 64) {
-                if (a.lse) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, false, true>(a, grid, st);
+                if (a.stream_once) return a.want_lse ? launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, true, true>(a, grid, st)
+                                                     : launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, true, false>(a, grid, st);
             }
+            if (a.want_lse) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, false, true>(a, grid, st);
         }
         return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, false>(a, grid, st);
     });
@@ -670,6 +671,7 @@ void set_direct(AttnArgs &a, const tlin_params *p, void *O, float *lse)
     a.direct = 1;
     a.O = O; a.o_sb = o.b; a.o_sh = o.h; a.o_sr = o.r;
     a.lse = lse;
+    a.want_lse = lse != nullptr;
     a.out_bf16 = p->out_dtype == TLIN_BF16;
 }
 
@@ -695,7 +697,7 @@ MergeArgs merge_args(const tlin_params *p, const Workspace &w, int nparts, int n
 template <int D, int NW, int NSTAGE, int DP, bool NT>
 tlin_status launch_pair_kernel(const PairArgs &f, hipStream_t st)
 {
-    constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2;
+    constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2 + (use_pipe_body<D, NW, 1, false, NSTAGE, false>() ? 16 : 0);
     static_assert(lds_bytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a gfx950 compute unit");
     auto kernel = attn_bf16_pair_kernel<D, NW, NSTAGE, DP, NT>;
     static std::atomic<uint64_t> lds_allowed{0};
@@ -885,6 +887,7 @@ tlin_status tlin_history_attn(const tlin_params *p, const void *Q_win, const voi
     if ((st = check_device())) return st;
     const Workspace w = carve(ws, p, pl.nsplit);
     set_partial(a, w, pl.nsplit, 0);
+    a.want_lse = lse != nullptr;
     if ((st = launch_attn(p, false, a, hs))) return st;
     return launch_merge(p, merge_args(p, w, pl.nsplit, pl.nsplit, false, true, O, lse), hs);
 }

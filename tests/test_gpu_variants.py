@@ -244,3 +244,42 @@ def test_fp32_operands_in_parts(D, W):
         for eq, ev in ((60, 90), (-60, -90), (20, 0)):
             sq, sk, sv = padded(host["Q"] * np.float32(2.0 ** eq), w.dtype), padded(host[hk] * np.float32(2.0 ** -eq), w.dtype), padded(host[hv] * np.float32(2.0 ** ev), w.dtype)
             assert torch.equal(call(sq, sk, sv), o * 2.0 ** ev), (eq, ev)
+
+
+@pytest.mark.parametrize("D", [36, 48, 64, 96, 128])
+@pytest.mark.parametrize("W", [40, 129, 300])
+@pytest.mark.parametrize("jump,vexp", [(6.0, 0), (12.0, 0), (60.0, 0), (12.0, 85)])
+def test_logits_far_above_the_first_tiles(D, W, jump, vexp):
+    """bf16 rows whose largest logits come late: keys from the fifth tile on are `jump` times as large, so that the
+    reference point of the first tile is left behind by some 20 (the row sum passes no threshold), 45 (it does)
+    and 200 nats (weights overflow), and values so large that the accumulator overflows although the weights do
+    not.  Unscaled outputs within the bf16 tolerance; scores of hundreds of nats are fp32 sums and carry their error
+    (2^-22 of them) into the weights."""
+    N = 700
+    w = ti.Workload(f"late_{D}_{W}_{jump}", 1, 2, D, N, W, ti.BF16, 1.0, 1357 + D + W + int(jump))
+    host = ti.make(w)
+
+    def late(a):
+        x = (a.astype(np.uint32) << 16).view(np.float32).copy()
+        x[:, :, 256:] *= np.float32(jump)
+        return (x.view(np.uint32) >> 16).astype(np.uint16)      # (jump has few bits; what is cut off is part of the input)
+
+    host["Kh"], host["Kw"] = late(host["Kh"]), late(host["Kw"])
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    big = {k: padded((((v.astype(np.uint32) << 16).view(np.float32) * np.float32(2.0 ** vexp)).view(np.uint32) >> 16).astype(np.uint16), w.dtype)
+           for k, v in host.items() if k in ("Vh", "Vw")}
+    for splits in (1, 2):
+        ro, rl = oracle.history(host["Q"], host["Kh"], host["Vh"], w.dtype, w.scale)
+        o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], big["Vh"], scale=w.scale, num_splits=splits, out_dtype=torch.float32, return_lse=True)
+        assert_close(o * 2.0 ** -vexp, ro, w.dtype, f"{w.name} history splits {splits}, both outputs")
+        np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+        o = tl.tlin_history_attn(dev["Q"], dev["Kh"], big["Vh"], scale=w.scale, num_splits=splits, out_dtype=torch.float32)
+        assert_close(o * 2.0 ** -vexp, ro, w.dtype, f"{w.name} history splits {splits}")
+        for mode, omode in ((tl.TLIN_COMBINE_SUM, oracle.SUM), (tl.TLIN_COMBINE_JOINT, oracle.JOINT)):
+            o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], big["Vh"], dev["Kw"], big["Vw"], combine=mode, scale=w.scale, num_splits=splits, out_dtype=torch.float32)
+            ro2 = oracle.layer(host["Q"], host["Kh"], host["Vh"], host["Kw"], host["Vw"], w.dtype, w.scale, omode)
+            assert_close(o * 2.0 ** -vexp, ro2, w.dtype, f"{w.name} layer mode {mode} splits {splits}")
+    for lse in (False, True):
+        o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], big["Vw"], scale=w.scale, out_dtype=torch.float32, return_lse=lse)
+        o = o[0] if lse else o
+        assert_close(o * 2.0 ** -vexp, oracle.window_causal(host["Q"], host["Kw"], host["Vw"], w.dtype, w.scale)[0], w.dtype, f"{w.name} window lse {lse}")
