@@ -104,20 +104,19 @@ Shape causal_shape(const tlin_params *p)
 int query_block(int in_dtype, int W, int D) { return kernel_shape(in_dtype, W, D).bm(); }
 
 // Workgroups the chip holds at once for a given kernel shape (LDS- and register-limited).
-int resident_wgs(int in_dtype, int W, int D)
+int resident_wgs(int in_dtype, Shape s, int D)
 {
     if (in_dtype == TLIN_F32) {
         // fp32: LDS, 160 KB (D = 128: 48 KB of planes and 8 KB per wave, half of that at 64), and the registers
         // (f32_waves_per_simd)
-        const int nw = kernel_shape(in_dtype, W, D).nw;
-        if (dpad(D) == 128) return kNumCU * (nw == 8 ? 1 : 2);
-        return kNumCU * (nw == 4 ? 3 : 4);
+        if (dpad(D) == 128) return kNumCU * (s.nw == 8 ? 1 : 2);
+        return kNumCU * (s.nw == 4 ? 3 : 4);
     }
     // head dimension 64: tiles and register sets are half as large, three workgroups share a
     // compute unit (measured best for few heads); 128: an eight-wave workgroup fills a compute unit
     // alone (registers), two of the smaller ones share it (two-tile LDS ring of 64 KB each)
     if (dpad(D) == 64) return kNumCU * 3;
-    return kNumCU * (kernel_shape(in_dtype, W, D).nw == 8 ? 1 : 2);
+    return kNumCU * (s.nw == 8 ? 1 : 2);
 }
 
 // ---- measurement aid: per-kernel timing with HIP events on the launch stream
@@ -224,7 +223,17 @@ tlin_status check_common(const tlin_params *p, bool need_history, bool allow_emp
 // Partition plan for the history axis.
 struct Plan { int nsplit, tiles_per_split; };
 
-Plan plan_history(const tlin_params *p)
+size_t ws_bytes_for(const tlin_params *p, int nparts)
+{
+    const size_t rows = (size_t)p->B * p->H * nparts * p->W;
+    return rows * dpad(p->D) * sizeof(float) + 2 * rows * sizeof(float);
+}
+
+// Work items along the query axis: (head, query block) pairs.
+int64_t query_items(const tlin_params *p, Shape s) { return (int64_t)p->B * p->H * ((p->W + s.bm() - 1) / s.bm()); }
+
+// round_down: partitions per item from which on a workgroup shape that shares a compute unit has them rounded down.
+Plan plan_for_shape(const tlin_params *p, Shape s, int round_down)
 {
     if (p->N < 1) return {0, 0};
     const int bn = key_tile(p->in_dtype, dpad(p->D));
@@ -235,22 +244,26 @@ Plan plan_history(const tlin_params *p)
     } else {
         // Enough workgroups to occupy every compute unit, but at least 8 tiles per partition: the
         // merge reads every partial, and with short partitions it would cost more than they save.
-        const int64_t base = (int64_t)p->B * p->H * ((p->W + query_block(p->in_dtype, p->W, p->D) - 1) / query_block(p->in_dtype, p->W, p->D));
-        const int64_t target = resident_wgs(p->in_dtype, p->W, p->D);
+        const int64_t base = query_items(p, s);
+        const int64_t target = resident_wgs(p->in_dtype, s, p->D);
         want = (int)((target + base - 1) / base);
         // Rounded up, a few workgroups more than the chip holds would start when the others end and run a
-        // whole partition's time beside idle compute units.  With one workgroup per compute unit rounding
-        // down is ahead from two partitions on (1/f of the history against 2/(f + 1)); where several share one,
-        // whose last ones then run faster alone, from eight on, where rounding down costs little (12 heads x
-        // 100, 300 rows over 300000, 24 row blocks: 11 partitions 1077 us, 10: 750; fp32, 12
-        // heads x 128, 256 rows over 30000: 726 -> 412; bf16, 12 heads x 64, 300 rows over 60000: 101 -> 85).
+        // whole partition's time beside idle compute units (1/f of the history against 2/(f + 1)).  Where several
+        // share a compute unit the last ones run faster alone, but rounding down is ahead there too (100 heads x
+        // 128, 64 rows over 28867, 6 -> 5 partitions: 306 -> 233 us; fp32, 80 heads x 96, 40 rows over 14338, 7 -> 6:
+        // 375 -> 257; 40 heads x 36, 260 rows over 64379, 7 -> 6: 263 -> 225; 100 heads x 36, 200 rows over 89222, 4 -> 3:
+        // 651 -> 626), only not from three to two where three or four share one (100 heads x 64, 260 rows over
+        // 7212: 86 -> 89; fp32, 100 heads x 36, 384 rows over 13767: 677 -> 719).
         const int64_t down = target / base;
-        if (base * want > target && down >= (target == kNumCU ? 2 : 8)) want = (int)down;
+        if (base * want > target && down >= (target == kNumCU ? 2 : round_down)) want = (int)down;
         // (a handful of (head, query block) items cannot fill the chip anyway: there the partials
         // are few in total and short partitions pay)
         const int min_tiles = base <= 4 ? 2 : 8;
         const int cap = ntiles / min_tiles > 1 ? ntiles / min_tiles : 1;
         if (want > cap) want = cap;
+        // (fp32 windows of many rows and heads, two partitions at most: their four-wave workgroups ask for more than
+        // one where a single one does, and a layer call stays in the library's own array)
+        while (p->in_dtype == TLIN_F32 && s.nw == 4 && p->W > 128 && want > 1 && ws_bytes_for(p, want + 1) > TLIN_STATIC_WS_BYTES) --want;
     }
     if (want < 1) want = 1;
     if (want > ntiles) want = ntiles;
@@ -258,6 +271,35 @@ Plan plan_history(const tlin_params *p)
     const int tps = (ntiles + want - 1) / want;
     return {(ntiles + tps - 1) / tps, tps};   // no partition is empty
 }
+
+Plan plan_for_shape(const tlin_params *p, Shape s)
+{
+    return plan_for_shape(p, s, resident_wgs(p->in_dtype, s, p->D) > 2 * kNumCU ? 3 : 2);
+}
+
+// Workgroup shape of a history.  At head dimensions above 64, of a window of 257 to 384 rows the second eight-wave
+// workgroup holds up to four waves' rows and still keeps a compute unit to itself; three four-wave workgroups, two to a
+// compute unit, leave nothing idle and cut the history into more partitions.  A tile takes the two 1.12 of an
+// eight-wave workgroup's time (each loads it for itself), one that has the compute unit to itself 0.8, and every
+// partition its partials' way out and back in: a tile is some 1.75 us at 128 columns (fp32, half as many keys: 5.2),
+// partials move at 5 TB/s.  Measured, eight waves -> four: 16 heads x 96, 300 rows over 50021: 146 -> 129 us; 32 heads x
+// 128, 300 rows over 32693: 220 -> 198; fp32, 48 heads x 96, 300 rows over 17905: 907 -> 701; 10 heads x 128, 350
+// rows over 2291: 27 -> 21; the other way round 64 heads x 128 (fp32), 300 rows over 2212: 143 against 150, 24 heads x 96,
+// 384 rows over 6280: 42.5 against 44.7.
+Shape history_shape(const tlin_params *p)
+{
+    const Shape s = kernel_shape(p->in_dtype, p->W, p->D), four = {4, 1};
+    if (s.nw != 8 || p->W <= 256 || p->W > 384 || p->N < 1) return s;
+    const Plan p8 = plan_for_shape(p, s), p4 = plan_for_shape(p, four);
+    if (ws_bytes_for(p, p4.nsplit + 1) > TLIN_STATIC_WS_BYTES) return s;
+    const double tile = (p->in_dtype == TLIN_F32 ? 5.2e-6 : 1.75e-6) * p->D / 128;
+    const double partial = p->B * p->H * (double)p->W * dpad(p->D) * 8 / 5e12;
+    const double factor = query_items(p, four) * p4.nsplit <= kNumCU ? 0.8 : 1.12;
+    const double t8 = p8.tiles_per_split * tile + p8.nsplit * partial, t4 = factor * p4.tiles_per_split * tile + p4.nsplit * partial;
+    return t4 < 0.96 * t8 ? four : s;
+}
+
+Plan plan_history(const tlin_params *p) { return plan_for_shape(p, history_shape(p)); }
 
 // The cache-hit shape (a few query rows over a long history) runs in the streaming kernel of
 // decode.h when called through tlin_history_attn.
@@ -274,7 +316,8 @@ bool use_decode(const tlin_params *p)
 {
     if (p->N < 1024 || p->W > (p->in_dtype == TLIN_F32 ? kDecodeRowsF32 : kDecodeRowsBf16)) return false;
     if (!decode_optional(p)) return true;
-    const int64_t bh = (int64_t)p->B * p->H, blocks = bh * plan_history(p).nsplit;
+    // (the lines below were measured with partitions rounded up: which calls weigh in fp32 stays with them)
+    const int64_t bh = (int64_t)p->B * p->H, blocks = bh * plan_for_shape(p, kernel_shape(p->in_dtype, p->W, p->D), 8).nsplit;
     // A history of one partition is one launch on the matrix-core path, which writes O itself and needs no
     // workspace; here it would be partials and a merge.  That path is ahead where rows are short (one row, 800
     // heads x 36, 1100 rows: 25.4 against 28.3 us here, 2048 heads x 64, 1024 rows: 83.3 against 88.5) and
@@ -286,7 +329,7 @@ bool use_decode(const tlin_params *p)
     // against 85, x 48 92 against 86), with two rows only above 32 columns (250 heads x 16, 3000 rows: 15.5
     // against 21.9; 100 heads x 68 126 against 94): a lane group of eight takes a row of few columns, whose
     // scores and weights cost the same for each query.
-    if (blocks > resident_wgs(p->in_dtype, p->W, p->D)) return p->W == 1 || p->D > 32;
+    if (blocks > resident_wgs(p->in_dtype, kernel_shape(p->in_dtype, p->W, p->D), p->D)) return p->W == 1 || p->D > 32;
     // Otherwise two rows are up to 19 % faster on the matrix-core path (99991 rows of 12 heads x 36: 35 against
     // 39 us; 131072 rows of 32 heads x 80: 198 against 203).  One row: with up to 64 bytes of columns that
     // path moves its tiles in pieces of lines and is behind (131072 rows of 32 heads x 16: 76 against 61 us; x
@@ -340,7 +383,7 @@ SlidePlan plan_slide(const tlin_params *p)
         // With many chunks the work items (head, chunk, query block) already outnumber the compute
         // units several times and the long ones start first; split only short sequences.
         const int64_t items = (int64_t)p->B * p->H * nqb * (nchunks > 1 ? nchunks - 1 : 1);
-        const int64_t target = 2 * (int64_t)resident_wgs(p->in_dtype, p->W, p->D);
+        const int64_t target = 2 * (int64_t)resident_wgs(p->in_dtype, kernel_shape(p->in_dtype, p->W, p->D), p->D);
         want = (int)((target + items - 1) / items);
     }
     // at least 4 tiles per partition in the longest history
@@ -355,12 +398,6 @@ SlidePlan plan_slide(const tlin_params *p)
 size_t slide_ws_bytes(const tlin_params *p, const SlidePlan &pl)
 {
     const size_t rows = (size_t)p->B * p->H * pl.nchunks * pl.nparts * p->W;
-    return rows * dpad(p->D) * sizeof(float) + 2 * rows * sizeof(float);
-}
-
-size_t ws_bytes_for(const tlin_params *p, int nparts)
-{
-    const size_t rows = (size_t)p->B * p->H * nparts * p->W;
     return rows * dpad(p->D) * sizeof(float) + 2 * rows * sizeof(float);
 }
 
@@ -498,14 +535,14 @@ tlin_status launch_f32(const AttnArgs &a, Shape s, int grid, hipStream_t st)
 // least nsplit^2 and a partition is longer than such a block.  Below four blocks' length that is worth it
 // only where the chip does not hold the window blocks beside all of the history blocks anyway
 // (layer calls, 300 rows over 20000, 8 heads x 128: fp32 427 -> 343 us, bf16 66 -> 51; 512 rows over 8192,
-// 32 heads x 128: fp32 665 -> 585, bf16 95 -> 84).  BM, BN, quarters: the kernel's
-// query rows per workgroup, keys per tile and cost ratio (window_block_cost).
-bool fuses_window(int in_dtype, const PairArgs &f, int BM, int BN, int quarters)
+// 32 heads x 128: fp32 665 -> 585, bf16 95 -> 84).  BN, quarters: the kernel's
+// keys per tile and cost ratio (window_block_cost).
+bool fuses_window(int in_dtype, const PairArgs &f, Shape s, int BN, int quarters)
 {
     const int tiles = (f.hist.NK + BN - 1) / BN, ns = f.hist.nsplit;
-    const int cost = window_block_cost(f.hist.W, f.hist.nqb - 1, BM, BN, quarters);
+    const int cost = window_block_cost(f.hist.W, f.hist.nqb - 1, s.bm(), BN, quarters);
     if (f.hist.nchunks != 0 || f.n_win_blocks <= 0 || ns < 2 || tiles < ns * ns) return false;
-    const bool full = f.n_hist_blocks + f.n_win_blocks > resident_wgs(in_dtype, f.hist.W, f.hist.D);
+    const bool full = f.n_hist_blocks + f.n_win_blocks > resident_wgs(in_dtype, s, f.hist.D);
     return tiles / ns >= (full ? cost + 2 : 4 * cost);
 }
 
@@ -524,7 +561,7 @@ template <int D>
 tlin_status launch_f32_pair(const PairArgs &f, Shape s, hipStream_t st)
 {
     PairArgs g = f;
-    if (fuses_window(TLIN_F32, f, s.nw * 32, 32, 4)) {
+    if (fuses_window(TLIN_F32, f, s, 32, 4)) {
         g.hist.fuse_window = 1;
         g.n_win_blocks = 0;
     }
@@ -562,7 +599,7 @@ bool streams_once(const tlin_params *p, const AttnArgs &a, int nqb)
 // Launch one partial-attention kernel over `nsplit` key partitions (or the causal window).
 tlin_status launch_attn(const tlin_params *p, bool causal, AttnArgs a, hipStream_t st)
 {
-    const Shape s = causal ? causal_shape(p) : kernel_shape(p->in_dtype, p->W, p->D);
+    const Shape s = causal ? causal_shape(p) : a.nchunks ? kernel_shape(p->in_dtype, p->W, p->D) : history_shape(p);
     a.nqb = (p->W + s.bm() - 1) / s.bm();
     a.stream_once = !causal && streams_once(p, a, a.nqb);
     if (use_resident(p, causal, a)) {
@@ -703,7 +740,7 @@ tlin_status launch_pair_kernel(const PairArgs &f, hipStream_t st)
     static std::atomic<uint64_t> lds_allowed{0};
     if (allow_lds((const void *)kernel, lds_bytes, lds_allowed) != TLIN_OK) return TLIN_ERR_HIP;
     if constexpr (use_pipe_body<D, NW, 1, false, NSTAGE, false>()) {
-        if (fuses_window(TLIN_BF16, f, NW * 32, 64, 5)) {
+        if (fuses_window(TLIN_BF16, f, Shape{NW, 1}, 64, 5)) {
             PairArgs g = f;
             g.hist.fuse_window = 1;
             g.n_win_blocks = 0;
@@ -728,8 +765,8 @@ tlin_status launch_pair_shape(const PairArgs &f, hipStream_t st)
 // History partials and window partial of the same rows: one launch for both problem sets.
 tlin_status launch_partials(const tlin_params *p, const AttnArgs &ah, const AttnArgs &aw, hipStream_t hs)
 {
-    const int qblk = query_block(p->in_dtype, p->W, p->D);
-    const int nqb = (p->W + qblk - 1) / qblk;
+    const Shape s = ah.nchunks ? kernel_shape(p->in_dtype, p->W, p->D) : history_shape(p);
+    const int nqb = (p->W + s.bm() - 1) / s.bm();
     const int64_t per_set = (int64_t)p->B * p->H * nqb * (ah.nchunks ? ah.nchunks : 1);
     const int64_t nh = per_set * ah.nsplit, nw = per_set;
     if (nh + nw <= 0x7fffffff) {
@@ -740,7 +777,6 @@ tlin_status launch_partials(const tlin_params *p, const AttnArgs &ah, const Attn
         f.hist.stream_once = streams_once(p, ah, nqb);
         f.n_hist_blocks = (int)nh;
         f.n_win_blocks = (int)nw;
-        const Shape s = kernel_shape(p->in_dtype, p->W, p->D);
         LaunchTimer timer(KC_HISTORY, hs);
         if (p->in_dtype == TLIN_F32) return dpad(p->D) == 128 ? launch_f32_pair<128>(f, s, hs) : launch_f32_pair<64>(f, s, hs);
         if (dpad(p->D) == 128) {

@@ -283,3 +283,26 @@ def test_logits_far_above_the_first_tiles(D, W, jump, vexp):
         o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], big["Vw"], scale=w.scale, out_dtype=torch.float32, return_lse=lse)
         o = o[0] if lse else o
         assert_close(o * 2.0 ** -vexp, oracle.window_causal(host["Q"], host["Kw"], host["Vw"], w.dtype, w.scale)[0], w.dtype, f"{w.name} window lse {lse}")
+
+
+@pytest.mark.parametrize("dtype,D", [(ti.BF16, 128), (ti.BF16, 84), (ti.F32, 128), (ti.F32, 72)])
+@pytest.mark.parametrize("H,W,N", [(3, 256, 2600), (3, 257, 2600), (3, 384, 2600), (3, 385, 2600), (24, 384, 1200), (2, 300, 40)])
+def test_workgroup_shapes_of_ragged_windows(dtype, D, H, W, N):
+    """Windows at both sides of the lines between eight-wave and four-wave workgroups (257 and 384 rows; 24 heads x 384
+    over a short history stay with eight waves, one partition over 40 rows): history, both layers, and the array of the
+    library, whose capacity no plan may exceed where 32 heads' partials fit."""
+    w = ti.Workload(f"ragged_{D}_{H}_{W}_{N}", 1, H, D, N, W, dtype, 1.0, 2121 + D + H + W + N)
+    host = ti.make(w)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    heads = sorted({0, H - 1})
+    sub = {k: np.ascontiguousarray(v[:, heads]) for k, v in host.items()}
+    o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True)
+    ro, rl = oracle.history(sub["Q"], sub["Kh"], sub["Vh"], w.dtype, w.scale)
+    assert_close(o[:, heads], ro, w.dtype, f"{w.name} history")
+    np.testing.assert_allclose(lse[:, heads].cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+    for mode, omode in ((tl.TLIN_COMBINE_SUM, oracle.SUM), (tl.TLIN_COMBINE_JOINT, oracle.JOINT)):
+        ro = oracle.layer(sub["Q"], sub["Kh"], sub["Vh"], sub["Kw"], sub["Vw"], w.dtype, w.scale, omode)
+        o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=mode, scale=w.scale)
+        assert_close(o[:, heads], ro, w.dtype, f"{w.name} layer mode {mode}")
+        o = tl.tlin_layer_attn_static_ws(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=mode)
+        assert_close(o[:, heads], ro, w.dtype, f"{w.name} layer mode {mode}, the library's array")
