@@ -482,7 +482,7 @@ namespace tlin {
 // slower), and the stand-alone causal kernel (head dimension 128: 5 % faster at 4096 rows; 64 and below:
 // 4096 rows, 32 heads x 64: 127 -> 102 us, 16384 rows 1385 -> 1127 us, 3001 rows, 32 heads x 48: 78 -> 52 us).
 // The causal window blocks that ride in a layer call's launch, the resident variant for odd tile counts
-// and the deeper rings keep the classic body.
+// keep the classic body.
 template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT>
 constexpr bool use_pipe_body()
 {

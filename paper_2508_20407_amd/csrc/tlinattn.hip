@@ -232,8 +232,9 @@ size_t ws_bytes_for(const tlin_params *p, int nparts)
 // Work items along the query axis: (head, query block) pairs.
 int64_t query_items(const tlin_params *p, Shape s) { return (int64_t)p->B * p->H * ((p->W + s.bm() - 1) / s.bm()); }
 
-// round_down: partitions per item from which on a workgroup shape that shares a compute unit has them rounded down.
-Plan plan_for_shape(const tlin_params *p, Shape s, int round_down)
+// target: workgroups to aim at; round_down: partitions per item from which on a shape that shares a compute unit
+// has them rounded down.
+Plan plan_for_shape(const tlin_params *p, Shape s, int64_t target, int round_down)
 {
     if (p->N < 1) return {0, 0};
     const int bn = key_tile(p->in_dtype, dpad(p->D));
@@ -245,7 +246,6 @@ Plan plan_for_shape(const tlin_params *p, Shape s, int round_down)
         // Enough workgroups to occupy every compute unit, but at least 8 tiles per partition: the
         // merge reads every partial, and with short partitions it would cost more than they save.
         const int64_t base = query_items(p, s);
-        const int64_t target = resident_wgs(p->in_dtype, s, p->D);
         want = (int)((target + base - 1) / base);
         // Rounded up, a few workgroups more than the chip holds would start when the others end and run a
         // whole partition's time beside idle compute units (1/f of the history against 2/(f + 1)).  Where several
@@ -274,7 +274,12 @@ Plan plan_for_shape(const tlin_params *p, Shape s, int round_down)
 
 Plan plan_for_shape(const tlin_params *p, Shape s)
 {
-    return plan_for_shape(p, s, resident_wgs(p->in_dtype, s, p->D) > 2 * kNumCU ? 3 : 2);
+    // (two-wave workgroups of at most 32 columns, half of whose tiles' places are not loaded: a fourth one per
+    // compute unit; 12 heads x 16, 40 rows over 999754: 225 -> 181 us, 100 heads, 40 rows over 9000: 25.8 -> 23.2; 36 and
+    // more columns lose up to 4 % with it)
+    const bool narrow = p->in_dtype == TLIN_BF16 && s.nw == 2 && p->D <= 32;
+    const int64_t target = narrow ? 4 * kNumCU : resident_wgs(p->in_dtype, s, p->D);
+    return plan_for_shape(p, s, target, target > 2 * kNumCU ? 3 : 2);
 }
 
 // Workgroup shape of a history.  At head dimensions above 64, of a window of 257 to 384 rows the second eight-wave
@@ -317,7 +322,8 @@ bool use_decode(const tlin_params *p)
     if (p->N < 1024 || p->W > (p->in_dtype == TLIN_F32 ? kDecodeRowsF32 : kDecodeRowsBf16)) return false;
     if (!decode_optional(p)) return true;
     // (the lines below were measured with partitions rounded up: which calls weigh in fp32 stays with them)
-    const int64_t bh = (int64_t)p->B * p->H, blocks = bh * plan_for_shape(p, kernel_shape(p->in_dtype, p->W, p->D), 8).nsplit;
+    const int64_t bh = (int64_t)p->B * p->H, places = resident_wgs(p->in_dtype, kernel_shape(p->in_dtype, p->W, p->D), p->D);
+    const int64_t blocks = bh * plan_for_shape(p, kernel_shape(p->in_dtype, p->W, p->D), places, 8).nsplit;
     // A history of one partition is one launch on the matrix-core path, which writes O itself and needs no
     // workspace; here it would be partials and a merge.  That path is ahead where rows are short (one row, 800
     // heads x 36, 1100 rows: 25.4 against 28.3 us here, 2048 heads x 64, 1024 rows: 83.3 against 88.5) and
@@ -329,7 +335,7 @@ bool use_decode(const tlin_params *p)
     // against 85, x 48 92 against 86), with two rows only above 32 columns (250 heads x 16, 3000 rows: 15.5
     // against 21.9; 100 heads x 68 126 against 94): a lane group of eight takes a row of few columns, whose
     // scores and weights cost the same for each query.
-    if (blocks > resident_wgs(p->in_dtype, kernel_shape(p->in_dtype, p->W, p->D), p->D)) return p->W == 1 || p->D > 32;
+    if (blocks > places) return p->W == 1 || p->D > 32;
     // Otherwise two rows are up to 19 % faster on the matrix-core path (99991 rows of 12 heads x 36: 35 against
     // 39 us; 131072 rows of 32 heads x 80: 198 against 203).  One row: with up to 64 bytes of columns that
     // path moves its tiles in pieces of lines and is behind (131072 rows of 32 heads x 16: 76 against 61 us; x
@@ -785,7 +791,10 @@ tlin_status launch_partials(const tlin_params *p, const AttnArgs &ah, const Attn
             return launch_pair_shape<128, 2, 2>(f, hs);
         }
         if (s.nw == 4) return launch_pair_shape<64, 4, 2>(f, hs);
-        return launch_pair_shape<64, 2, 3>(f, hs);
+        // (a ring of three tiles in the classic body was ahead of this one only until it lost its maxima and row
+        // sums: 32 heads x 64, 64 rows over 60000: 102 -> 86 us, 12 heads x 36, 40 rows over 999754: 401 -> 306, sliding
+        // schedule of 8 heads x 64, 8000 rows in chunks of 64: 131 -> 96)
+        return launch_pair_shape<64, 2, 2>(f, hs);
     }
     tlin_status st;
     if ((st = launch_attn(p, false, ah, hs))) return st;
