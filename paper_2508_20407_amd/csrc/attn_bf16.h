@@ -481,8 +481,8 @@ namespace tlin {
 // wave and a ring of two tiles (measured against attn_bf16_body on every such shape: faster, none
 // slower), and the stand-alone causal kernel (head dimension 128: 5 % faster at 4096 rows; 64 and below:
 // 4096 rows, 32 heads x 64: 127 -> 102 us, 16384 rows 1385 -> 1127 us, 3001 rows, 32 heads x 48: 78 -> 52 us).
-// The causal window blocks that ride in a layer call's launch, the resident variant for odd tile counts
-// keep the classic body.
+// The causal window blocks that ride in a layer call's launch and the resident variant at head dimensions up to
+// 64 and, for odd tile counts, below 128 keep the classic body.
 template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT>
 constexpr bool use_pipe_body()
 {
@@ -501,12 +501,12 @@ void attn_bf16_kernel(const AttnArgs a)
     else attn_bf16_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP>(a, blockIdx.x, gridDim.x);
 }
 
-// Resident key/value side with the in-wave pipeline (an even number T1 of key tiles).
-template <int D, int T1, int TMAX, int DP = 0>
+// Resident key/value side with the in-wave pipeline (T1 key tiles, an even number; ODD: one less).
+template <int D, int T1, int TMAX, int DP = 0, bool ODD = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 8)))
 void attn_bf16_resident_pipe_kernel(const AttnArgs a)
 {
-    attn_bf16_resident_pipe_body<D, 8, DP, T1, TMAX>(a, blockIdx.x, gridDim.x);
+    attn_bf16_resident_pipe_body<D, 8, DP, T1, TMAX, ODD>(a, blockIdx.x, gridDim.x);
 }
 
 // History partition blocks and window causal blocks of one call in a single launch.

@@ -489,8 +489,17 @@ tlin_status launch_resident_pipe(const AttnArgs &a, int grid, hipStream_t st)
     constexpr int lds_bytes = 2 * TMAX * 64 * D * 2 + 8 * 4096;
     static_assert(lds_bytes <= 160 * 1024, "resident tiles exceed the 160 KB of a gfx950 compute unit");
     return with_columns<D>(a.D, [&](auto dp) {
+        constexpr int DP = decltype(dp)::value;
+        if constexpr (DP == 0) {
+            if (a.NK <= (T1 - 1) * 64) {
+                static std::atomic<uint64_t> lds_allowed_odd{0};
+                const void *kernel = (const void *)attn_bf16_resident_pipe_kernel<D, T1, TMAX, DP, true>;
+                if (allow_lds(kernel, lds_bytes, lds_allowed_odd) != TLIN_OK) return TLIN_ERR_HIP;
+                return launch_kernel(kernel, dim3(grid), dim3(512), lds_bytes, st, a);
+            }
+        }
         static std::atomic<uint64_t> lds_allowed{0};
-        const void *kernel = (const void *)attn_bf16_resident_pipe_kernel<D, T1, TMAX, decltype(dp)::value>;
+        const void *kernel = (const void *)attn_bf16_resident_pipe_kernel<D, T1, TMAX, DP>;
         if (allow_lds(kernel, lds_bytes, lds_allowed) != TLIN_OK) return TLIN_ERR_HIP;
         return launch_kernel(kernel, dim3(grid), dim3(512), lds_bytes, st, a);
     });
@@ -578,9 +587,6 @@ tlin_status launch_f32_pair(const PairArgs &f, Shape s, hipStream_t st)
     return launch_f32_pair_shape<D, 2>(g, st);
 }
 
-// Key tiles the resident variant keeps in LDS (128 KB of keys and values).
-int resident_tiles(int D) { return D == 128 ? 4 : 8; }
-
 // The resident variant pays when the key/value side fits in LDS as a whole and every workgroup
 // has several query blocks to walk over: long query side, short unsplit key side.
 bool use_resident(const tlin_params *p, bool causal, const AttnArgs &a)
@@ -589,7 +595,11 @@ bool use_resident(const tlin_params *p, bool causal, const AttnArgs &a)
     if (p->W <= 128) return false;
     const int ntiles = (a.NK + 63) / 64;
     const int64_t blocks = (int64_t)p->B * p->H * ((p->W + 255) / 256);      // the resident kernels are eight-wave ones
-    return ntiles <= resident_tiles(dpad(p->D)) && blocks >= 4 * (int64_t)kNumCU;
+    // Head dimensions up to 64 run the unpipelined body here, which the pipelined ring has passed where a block has more
+    // than two tiles (four above 48 columns) to hide its start behind: 32 heads, 131072 rows over 400 keys, x 64 675
+    // -> 619 us, x 36 633 -> 538, over 200 keys x 36 391 -> 368, but x 64 419 -> 439, and over 128 x 36 250 -> 286.
+    const int most = dpad(p->D) == 128 || p->D > 48 ? 4 : 2;
+    return ntiles <= most && blocks >= 4 * (int64_t)kNumCU;
 }
 
 // K/V rows of a history are read by exactly one workgroup when the window is a single query block,
@@ -612,18 +622,21 @@ tlin_status launch_attn(const tlin_params *p, bool causal, AttnArgs a, hipStream
         // one workgroup per compute unit, spread evenly over the heads
         a.nqb = (p->W + 255) / 256;
         const int64_t bh = (int64_t)p->B * p->H;
-        int64_t g = (kNumCU + bh - 1) / bh;
+        // (rounded down: twelve heads in 264 workgroups left eight for a second round; 50000 rows over 256 keys of 12
+        // heads x 128: 125 -> 66 us)
+        int64_t g = kNumCU / bh;
+        if (g < 1) g = 1;
         if (g > a.nqb) g = a.nqb;
         a.q_groups = (int)g;
         const int64_t grid64 = bh * g;
         if (grid64 > 0x7fffffff) return TLIN_ERR_INVALID_ARG;
         LaunchTimer timer(KC_HISTORY, st);
-        // an even number of key tiles at head dimension 128: the pipelined variant
         const int ntiles = (a.NK + 63) / 64;
-        if (dpad(p->D) == 128 && ntiles == 4) return launch_resident_pipe<128, 4, 4>(a, (int)grid64, st);
-        if (dpad(p->D) == 128 && ntiles == 2) return launch_resident_pipe<128, 2, 4>(a, (int)grid64, st);
-        return dpad(p->D) == 128 ? launch_bf16_shape<128, 8, 1, false, 4, true>(a, (int)grid64, st)
-                                 : launch_bf16_shape<64, 8, 1, false, 8, true>(a, (int)grid64, st);
+        // (three tiles pay for the masked fourth one where a workgroup has a dozen blocks or more: 32 heads, 131072
+        // rows over 180 keys 657 -> 632 us, 8200 rows 43 -> 46)
+        const bool odd = p->D == 128 && (ntiles == 1 || a.nqb >= 12 * a.q_groups);
+        if (dpad(p->D) == 128 && (ntiles % 2 == 0 || odd)) return ntiles > 2 ? launch_resident_pipe<128, 4, 4>(a, (int)grid64, st) : launch_resident_pipe<128, 2, 4>(a, (int)grid64, st);
+        return dpad(p->D) == 128 ? launch_bf16_shape<128, 8, 1, false, 4, true>(a, (int)grid64, st) : launch_bf16_shape<64, 8, 1, false, 4, true>(a, (int)grid64, st);
     }
     const int64_t grid64 = (int64_t)p->B * p->H * a.nqb * a.nsplit * (a.nchunks ? a.nchunks : 1);
     if (grid64 > 0x7fffffff) return TLIN_ERR_INVALID_ARG;

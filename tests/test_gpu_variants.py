@@ -306,3 +306,22 @@ def test_workgroup_shapes_of_ragged_windows(dtype, D, H, W, N):
         assert_close(o[:, heads], ro, w.dtype, f"{w.name} layer mode {mode}")
         o = tl.tlin_layer_attn_static_ws(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=mode)
         assert_close(o[:, heads], ro, w.dtype, f"{w.name} layer mode {mode}, the library's array")
+
+
+@pytest.mark.parametrize("D,N", [(128, 1), (128, 40), (128, 64), (128, 65), (128, 128), (128, 129), (128, 180), (128, 192), (128, 193), (128, 256),
+                                 (96, 60), (96, 180), (64, 128), (64, 200), (64, 256), (64, 300), (36, 128), (36, 129)])
+def test_long_query_sides_over_few_keys(D, N):
+    """Queries of twelve heads, which do not divide the compute units, over keys that stay in LDS: odd and even tile
+    counts, ragged last tiles, and both sides of the lines where the ring kernel takes over; with log-sum-exp."""
+    W = 22050
+    w = ti.Workload(f"few_keys_{D}_{N}", 1, 12, D, N, W, ti.BF16, 1.0, 808 + D + N)
+    host = ti.make(w)
+    dev = {k: padded(host[k], w.dtype) for k in ("Q", "Kh", "Vh")}
+    rows = np.unique(np.concatenate([np.arange(0, 300), np.arange(W - 300, W), np.arange(300, W - 300, 97)]))
+    o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True)
+    for h in (0, 11):
+        sub = [np.ascontiguousarray(host["Q"][:, h:h + 1, rows]), np.ascontiguousarray(host["Kh"][:, h:h + 1]), np.ascontiguousarray(host["Vh"][:, h:h + 1])]
+        ro, rl = oracle.history(*sub, w.dtype, w.scale)
+        assert_close(o[:, h:h + 1, torch.from_numpy(rows).cuda()], ro, w.dtype, f"{w.name} head {h}")
+        # (the classic body sums rounded weights: 2^-8)
+        np.testing.assert_allclose(lse[:, h:h + 1, torch.from_numpy(rows).cuda()].cpu().numpy(), rl, rtol=0, atol=4.5e-3)
