@@ -26,7 +26,9 @@ if ROOT not in sys.path:
 
 PEAK_BF16_MFMA_TFLOPS = 2500.0   # MI355X dense bf16
 PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
-PEAK_F32_MFMA_TFLOPS = 157.3    # MI355X dense fp32 matrix (the fp32 vector rate is the same figure)
+# fp32 inputs: six bf16 products per fp32 product on the bf16 matrix cores (the fp32 matrix instructions' own
+# peak is 157.3)
+PEAK_F32_MFMA_TFLOPS = 2500.0 / 6
 
 
 def parse():

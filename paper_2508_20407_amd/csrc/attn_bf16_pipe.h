@@ -10,19 +10,16 @@
 // wave keeps TWO score accumulators and works on two tiles at once:
 //
 //     step n:   A   S(n+1)  = K(n+1) Q^T              16 matrix instructions
-//                   P(n)[keys 0..31]  = 2^(c S(n) - c m), rounded to bf16, row sum       vector
-//               B1  O += V(n)[keys 0..31]^T P(n)       8 matrix instructions
-//                   P(n)[keys 32..63] likewise                                           vector
-//               B2  O += V(n)[keys 32..63]^T P(n)      8 matrix instructions
-//                   row maximum of S(n+1), reference point test                          vector
+//                   P(n)[keys 0..31]  = 2^(c S(n) - c m), rounded to bf16                 vector
+//               B1  O += V(n)[keys 0..31]^T P(n)       8 matrix instructions, 2 small ones for the row sums
+//                   P(n)[keys 32..63] likewise                                            vector
+//               B2  O += V(n)[keys 32..63]^T P(n)      8 matrix instructions, 2 small ones
 //               (rare) the reference point m moves: O and l are rescaled
 //
 // In every phase the matrix instructions and the vector instructions are independent of each
 // other, and they are issued interleaved (one matrix instruction, its operand's LDS read a few
 // slots ahead, a few vector instructions), so both pipes of the SIMD are busy at the same time
-// within one wave, and the second wave of the SIMD fills what is left.  The weights of tile n are
-// taken against the reference point that was fixed at the end of step n-1, which is the same
-// point the classic order uses.
+// within one wave, and the second wave of the SIMD fills what is left.
 //
 // Vector instructions are what these loops are short of (head dimensions up to 64) or pay for in clock (128: the
 // chip is at its power limit), so a step holds none that can be had otherwise:

@@ -308,8 +308,9 @@ Plan plan_history(const tlin_params *p) { return plan_for_shape(p, history_shape
 
 // The cache-hit shape (a few query rows over a long history) runs in the streaming kernel of
 // decode.h when called through tlin_history_attn.
-//   fp32 inputs: the matrix-core path pays for a whole 32-row tile of fp32 products whatever W is
-// (1.39 ms over 131072 rows of 32 heads x 128 against 0.62 ms here).
+//   fp32 inputs: the matrix-core path pays for a whole 32-row tile of products, and for splitting every key and
+// value, whatever W is (16 rows over 32768 rows of 32 heads x 128: 221 us; eight rows over four times as many take
+// 655 us here, one row 610).
 //   bf16: three and four rows are a little faster in the two-wave matrix-core shape at head dimension
 // 128 (0.309 against 0.323 ms over 131072 rows of 32 heads; both read at the rate of a plain
 // non-temporal read stream) and up to twice as fast at the narrow ones (four rows over 99991 rows of 12
