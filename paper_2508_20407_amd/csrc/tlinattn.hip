@@ -220,6 +220,9 @@ tlin_status check_common(const tlin_params *p, bool need_history, bool allow_emp
     return TLIN_OK;
 }
 
+// Most query rows of a streaming call (use_decode).
+constexpr int kDecodeRowsF32 = 8, kDecodeRowsBf16 = 2;
+
 // Partition plan for the history axis.
 struct Plan { int nsplit, tiles_per_split; };
 
@@ -279,6 +282,8 @@ Plan plan_for_shape(const tlin_params *p, Shape s)
     // more columns lose up to 4 % with it)
     const bool narrow = p->in_dtype == TLIN_BF16 && s.nw == 2 && p->D <= 32;
     const int64_t target = narrow ? 4 * kNumCU : resident_wgs(p->in_dtype, s, p->D);
+    // (one and two bf16 rows keep the plan by which the lines of use_decode were measured)
+    if (p->in_dtype == TLIN_BF16 && p->W <= kDecodeRowsBf16) return plan_for_shape(p, s, resident_wgs(p->in_dtype, s, p->D), 8);
     return plan_for_shape(p, s, target, target > 2 * kNumCU ? 3 : 2);
 }
 
@@ -315,7 +320,6 @@ Plan plan_history(const tlin_params *p) { return plan_for_shape(p, history_shape
 // 128 (0.309 against 0.323 ms over 131072 rows of 32 heads; both read at the rate of a plain
 // non-temporal read stream) and up to twice as fast at the narrow ones (four rows over 99991 rows of 12
 // heads x 16: 24 against 46 us, x 36: 35 against 48, x 96: 75 against 87).
-constexpr int kDecodeRowsF32 = 8, kDecodeRowsBf16 = 2;
 // bf16 calls below head dimension 128 take the matrix-core path wherever the streaming kernel is not ahead.
 bool decode_optional(const tlin_params *p) { return p->in_dtype == TLIN_BF16 && p->D != 128; }
 bool use_decode(const tlin_params *p)
