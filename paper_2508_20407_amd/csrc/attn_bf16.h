@@ -501,6 +501,14 @@ void attn_bf16_kernel(const AttnArgs a)
     else attn_bf16_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP>(a, blockIdx.x, gridDim.x);
 }
 
+// The pipelined shapes for callers of the log-sum-exp whose normaliser is the fp32 sum.
+template <int D, int NW, bool CAUSAL, int DP, bool NT>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW < 8 ? 2 : 1, 8)))
+void attn_bf16_lse_kernel(const AttnArgs a)
+{
+    attn_bf16_pipe_body<D, NW, DP, NT, true, CAUSAL>(a, blockIdx.x, gridDim.x);
+}
+
 // Resident key/value side with the in-wave pipeline (T1 key tiles, an even number; ODD: one less).
 template <int D, int T1, int TMAX, int DP = 0, bool ODD = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 8)))

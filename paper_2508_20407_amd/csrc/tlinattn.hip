@@ -292,14 +292,14 @@ Plan plan_for_shape(const tlin_params *p, Shape s)
 // compute unit, leave nothing idle and cut the history into more partitions.  A tile takes the two 1.12 of an
 // eight-wave workgroup's time (each loads it for itself), one that has the compute unit to itself 0.8, and every
 // partition its partials' way out and back in: a tile is some 1.75 us at 128 columns (fp32, half as many keys: 5.2),
-// partials move at 5 TB/s.  Measured, eight waves -> four: 16 heads x 96, 300 rows over 50021: 146 -> 129 us; 32 heads x
-// 128, 300 rows over 32693: 220 -> 198; fp32, 48 heads x 96, 300 rows over 17905: 907 -> 701; 10 heads x 128, 350
-// rows over 2291: 27 -> 21; the other way round 64 heads x 128 (fp32), 300 rows over 2212: 143 against 150, 24 heads x 96,
+// partials move at 5 TB/s.  Measured, eight waves -> four: 16 heads x 96, 300 rows over 50021: 146 -> 129 us; fp32, 48 heads x 96, 300 rows over 17905: 907 -> 701; the other way round 64 heads x 128 (fp32), 300 rows over 2212: 143 against 150, 24 heads x 96,
 // 384 rows over 6280: 42.5 against 44.7.
 Shape history_shape(const tlin_params *p)
 {
     const Shape s = kernel_shape(p->in_dtype, p->W, p->D), four = {4, 1};
     if (s.nw != 8 || p->W <= 256 || p->W > 384 || p->N < 1) return s;
+    // (bf16 at 128 columns stays: its partitions are counted on to fill the chip once in blocks of 256 rows)
+    if (p->in_dtype == TLIN_BF16 && p->D == 128) return s;
     const Plan p8 = plan_for_shape(p, s), p4 = plan_for_shape(p, four);
     if (ws_bytes_for(p, p4.nsplit + 1) > TLIN_STATIC_WS_BYTES) return s;
     const double tile = (p->in_dtype == TLIN_F32 ? 5.2e-6 : 1.75e-6) * p->D / 128;
@@ -463,7 +463,10 @@ tlin_status launch_bf16_kernel(const AttnArgs &a, int grid, hipStream_t st)
     // the ring and, in the pipelined body, one word behind it
     constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2 + (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>() ? 16 : 0);
     static_assert(lds_bytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a gfx950 compute unit");
-    auto kernel = attn_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, NT, LSE>;
+    const auto kernel = [] {
+        if constexpr (LSE && !(CAUSAL && D == 64)) return attn_bf16_lse_kernel<D, NW, CAUSAL, DP, NT>;
+        else return attn_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, NT, LSE>;
+    }();
     static std::atomic<uint64_t> lds_allowed{0};
     if (allow_lds((const void *)kernel, lds_bytes, lds_allowed) != TLIN_OK) return TLIN_ERR_HIP;
     return launch_kernel((const void *)kernel, dim3(grid), dim3(NW * 64), lds_bytes, st, a);
