@@ -490,23 +490,15 @@ constexpr bool use_pipe_body()
 }
 
 // NT (pipelined shapes only): the tile loads carry the non-temporal hint, see direct_load_1k.  LSE: the caller
-// asks for the log-sum-exp (pipelined shapes: a variant with the fp32 row sum, see attn_bf16_pipe_body).
+// asks for the log-sum-exp (a variant of its own where the normaliser is not the fp32 sum, see attn_bf16_pipe_body).
 template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT = false, int DP = 0, bool NT = false, bool LSE = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NSTAGE == 2 && NW < 8 ? 2 : 1, 8)))
 void attn_bf16_kernel(const AttnArgs a)
 {
     static_assert(!NT || use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>(), "only the pipelined body has a non-temporal variant");
     static_assert(!(NT && CAUSAL), "a window's keys and values are read by several workgroups");
-    if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) attn_bf16_pipe_body<D, NW, DP, NT, LSE, CAUSAL>(a, blockIdx.x, gridDim.x);
+    if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) attn_bf16_pipe_body<D, NW, DP, NT, CAUSAL, LSE>(a, blockIdx.x, gridDim.x);
     else attn_bf16_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP>(a, blockIdx.x, gridDim.x);
-}
-
-// The pipelined shapes for callers of the log-sum-exp whose normaliser is the fp32 sum.
-template <int D, int NW, bool CAUSAL, int DP, bool NT>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW < 8 ? 2 : 1, 8)))
-void attn_bf16_lse_kernel(const AttnArgs a)
-{
-    attn_bf16_pipe_body<D, NW, DP, NT, true, CAUSAL>(a, blockIdx.x, gridDim.x);
 }
 
 // Resident key/value side with the in-wave pipeline (T1 key tiles, an even number; ODD: one less).
@@ -527,7 +519,7 @@ void attn_bf16_pair_kernel(const PairArgs f)
     int win_block = (int)blockIdx.x < f.n_hist_blocks ? -1 : xcd_remap(blockIdx.x - f.n_hist_blocks, f.n_win_blocks);
     if ((int)blockIdx.x < f.n_hist_blocks) {
         if constexpr (use_pipe_body<D, NW, 1, false, NSTAGE, false>()) {
-            attn_bf16_pipe_body<D, NW, DP, NT, false>(f.hist, blockIdx.x, f.n_hist_blocks);
+            attn_bf16_pipe_body<D, NW, DP, NT>(f.hist, blockIdx.x, f.n_hist_blocks);
             if (f.hist.fuse_window) {
                 // the workgroup of partition 0 goes on to the window's causal block of the same rows
                 // (causal blocks are numbered from the last query block down)

@@ -10,33 +10,34 @@
 // wave keeps TWO score accumulators and works on two tiles at once:
 //
 //     step n:   A   S(n+1)  = K(n+1) Q^T              16 matrix instructions
-//                   P(n)[keys 0..31]  = 2^(c S(n) - c m), rounded to bf16                 vector
-//               B1  O += V(n)[keys 0..31]^T P(n)       8 matrix instructions, 2 small ones for the row sums
-//                   P(n)[keys 32..63] likewise                                            vector
-//               B2  O += V(n)[keys 32..63]^T P(n)      8 matrix instructions, 2 small ones
+//                   P(n)[keys 0..31]  = 2^(c S(n) - c m), rounded to bf16, row sum       vector
+//               B1  O += V(n)[keys 0..31]^T P(n)       8 matrix instructions
+//                   P(n)[keys 32..63] likewise                                           vector
+//               B2  O += V(n)[keys 32..63]^T P(n)      8 matrix instructions
+//                   row maximum of S(n+1), reference point test                          vector
 //               (rare) the reference point m moves: O and l are rescaled
 //
 // In every phase the matrix instructions and the vector instructions are independent of each
 // other, and they are issued interleaved (one matrix instruction, its operand's LDS read a few
 // slots ahead, a few vector instructions), so both pipes of the SIMD are busy at the same time
-// within one wave, and the second wave of the SIMD fills what is left.
+// within one wave, and the second wave of the SIMD fills what is left.  The weights of tile n are
+// taken against the reference point that was fixed at the end of step n-1, which is the same
+// point the classic order uses.
 //
-// Vector instructions are what these loops are short of (head dimensions up to 64) or pay for in clock (128: the
-// chip is at its power limit), so a step holds none that can be had otherwise:
-//   * Row sums: the matrix unit adds up the rounded weights (sum_q: four small products per tile, 64 of its
-//     1024 cycles at D = 128), 36 vector adds less.  The normaliser is then the sum of the very numbers the value
-//     product uses: a row is a convex combination again.  (v_dot2_f32_bf16, two weights at a time, holds up the
-//     matrix pipe by 6 cycles each: slower than the adds.)  Callers that ask for the log-sum-exp (LSE) get the
-//     fp32 sum, whose error is not 2^-9 of single weights but that of fp32; stand-alone causal calls at head
-//     dimensions up to 64, where rows of few keys are common, keep both sums then.
-//   * Row maxima: none after the first tile.  The reference point of a row is its maximum over the first tile; from
-//     there it moves only when the row sum has passed 2^64, one comparison per tile.  Weights are fp32 and bf16
-//     numbers, which are as precise at 2^60 as at 1.  What can go wrong is an overflow inside a tile (a logit 44 to
-//     88 nats above all that the row has met, or values near the end of the range): it leaves something that is
-//     not finite in the row's sum or accumulator, which is looked for before the last tile (whose maximum is taken
-//     again), and the workgroup then goes over its partition a second time and follows every tile's maximum.
-// Together, against maxima and adds: 12 heads x 36, 256 rows over 999754: 854 -> 777 us; 64 heads x 128, 256 rows over
-// 32768: 294 -> 278; 32 heads x 128, 512 rows over 131072: 975 -> 957, 4096 causal rows 149 -> 146.
+// The row sum l is accumulated from the fp32 weights with plain adds, not with v_dot2_f32_bf16 on
+// the rounded ones as attn_bf16_body does: under a stream of matrix instructions a dot2 costs about
+// 6 cycles of the matrix pipe (it does not execute beside it), an add costs nothing (measured on a
+// single-wave stream: 42 against 34 cycles per matrix instruction with this softmax work in
+// between).  The normaliser is then the exact sum of the weights while the value product uses their
+// bf16 roundings, so a row is a convex combination only to within 2^-9 per weight; the difference
+// stays far inside the tolerance and the log-sum-exp output becomes exact to fp32 rounding.
+// The stand-alone causal kernel at head dimensions up to 64 (MATCHED) divides by the sum of the
+// rounded weights instead, in attn_bf16_body's order: rows of few keys, where nothing averages out,
+// are common there.  Largest |O - 1| over constant values 1.4e-3 -> 4e-7, 2-norm error over values of
+// mean 1, 4096 rows x 64, 1.3e-4 -> 9e-5.  With half as many products per tile as at head dimension 128
+// the dot2 costs no time here (32 heads x 64, 4096 rows: 104 us with the fp32 sum, 101 with this one).
+// The variant for callers that ask for the log-sum-exp (LSE) keeps the fp32 sum beside it, so that output
+// stays exact to fp32 rounding (109 us).
 //
 // Ring of two tiles for K and two for V; K runs one tile ahead of V.  Step n reads K(n+1) and
 // V(n); at its top (after the step's single barrier) every wave has finished K(n) and V(n-1),
@@ -66,10 +67,11 @@ __device__ __forceinline__ void static_for(F &&f) { static_for_seq(f, std::make_
 // the barriers and issues its share of the tile loads.  Leaving is the end of the wave's own loop, not a
 // branch inside the step: with the branch the causal kernel needed 256 registers and spilled, without
 // it takes 210 (4096 rows, 32 heads x 128: 0.179 -> 0.164 ms).
-template <int D, int NW, int DP, bool NT, bool LSE, bool CAUSAL = false>
+template <int D, int NW, int DP, bool NT, bool CAUSAL = false, bool LSE = false>
 __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, int nblocks)
 {
-    constexpr bool SUM_M = !LSE || (CAUSAL && D == 64);   // the normaliser is the sum of the rounded weights, by the matrix unit
+    constexpr bool MATCHED = CAUSAL && D == 64;    // the normaliser is the sum of the rounded weights
+    static_assert(MATCHED || !LSE, "elsewhere the row sum is the fp32 one already");
     constexpr int NSTAGE = 2;
     constexpr int BN = 64;                 // keys per tile
     constexpr int BM = NW * 32;            // query rows per workgroup
@@ -189,19 +191,13 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
 
     f32x16 oacc[DB];
     float m = -INFINITY, l = 0.f;
-    f32x4 lm = {0.f, 0.f, 0.f, 0.f};       // SUM_M: element 0, the row's sum (see sum_q)
-    bf16x8 sel;
+    float lr = 0.f;                        // MATCHED: rounded weights of the current tile
+    float l32 = 0.f, ls32 = 0.f;           // LSE: fp32 sum
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
-    for (int e = 0; e < 8; ++e) sel[e] = (__bf16)((lane & 3) == 0 && (lane >> 2 & 1) == (lane >> 4 & 1) ? 1.0f : 0.0f);
-    auto reset = [&]() __attribute__((always_inline)) {
-        m = -INFINITY;
-        l = 0.f;
-        lm = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
-    };
+        for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
     const float thr = 8.0f / a.c;          // reference point moves only beyond 2^8 (see attn_bf16_body)
     float mc = 0.f;                        // m * c of the current reference point
     bf16x8 pb[2][2];                       // weights of the current tile, B-operand order
@@ -220,7 +216,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         S[kk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], S[kk], 0, 0, 0);
     };
     // weights of the 16 keys of quarter (kb, t2) from S (against mc), rounded to bf16 for the value
-    // product; LSE: their fp32 values are summed into l
+    // product; their fp32 values (MATCHED: the rounded ones, a tile at a time) are summed into l
     auto weights_q = [&](const f32x16 (&S)[2], int kb, int t2) __attribute__((always_inline)) {
         float ls = 0.f;
 #pragma unroll
@@ -230,28 +226,25 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
             const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
             pb[kb][t2][e] = pp[0];
             pb[kb][t2][e + 1] = pp[1];
-            if (LSE) ls += p0 + p1;
+            if (MATCHED) lr = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, kb + t2 + e ? lr : 0.f, false);
+            if (LSE) ls32 = (kb + t2 + e ? ls32 : 0.f) + (p0 + p1);
+            else if (!MATCHED) ls += p0 + p1;
         }
-        if (LSE) l += ls;
-    };
-    // The row sums of a quarter's rounded weights.  A 32-column operand is read by the 16-column instruction as four
-    // groups of k: lanes 0..15 and 32..47 (queries 0..15, one half-wave each) and 16..31 and 48..63 (queries
-    // 16..31).  `sel` has ones against the first pair of groups in rows 0 and 8 and against the second in rows 4
-    // and 12, so that element 0 of the result is, in every lane, the sum of the lane's own query, both halves.
-    auto sum_q = [&](int kb, int t2) __attribute__((always_inline)) {
-        if (SUM_M) lm = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, pb[kb][t2], lm, 0, 0, 0);
+        if (!MATCHED) l += ls;
+        else if (kb + t2 == 2) l += lr;
+        if (LSE && kb + t2 == 2) l32 += ls32;
     };
     auto weights = [&](const f32x16 (&S)[2], int kb) __attribute__((always_inline)) {
         weights_q(S, kb, 0);
         weights_q(S, kb, 1);
     };
     // O^T += V^T P^T for the 32 keys of block kb
-    auto pv_half = [&](int kb, int off) __attribute__((always_inline)) {
+    auto pv_half = [&](int kb, int vstage) __attribute__((always_inline)) {
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                const unsigned ad = vaddr[db] + off + (kb * 32 + 16 * t2) * ROWB;
+                const unsigned ad = vaddr[db] + vstage * TILE_B + (kb * 32 + 16 * t2) * ROWB;
                 const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)ad);
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)(ad + 8 * ROWB));
                 const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -280,32 +273,19 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
             for (int v = 0; v < 16; ++v) mx = fmaxf(mx, S[kb][v]);
         return xhalf_max(mx);
     };
-    auto rescale = [&](float alpha) __attribute__((always_inline)) {
-        l *= alpha;
-        lm[0] *= alpha;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
-    };
     // the reference point moves to mx where some row's maximum exceeds it by more than the threshold
     auto move_reference = [&](float mx) __attribute__((always_inline)) {
         if (__builtin_amdgcn_ballot_w64(mx > m + thr) != 0) {
             const float mn = fmaxf(m, mx);
             const float alpha = (mn == -INFINITY) ? 1.f : fast_exp2((m - mn) * a.c);
-            rescale(alpha);
+            l *= alpha;
+            if (LSE) l32 *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
             m = mn;
             mc = (m == -INFINITY) ? 0.f : m * a.c;
-        }
-    };
-    // without the maximum: the reference point moves by the row sum's exponent where that has become large
-    auto move_by_sum = [&]() __attribute__((always_inline)) {
-        if (__builtin_amdgcn_ballot_w64((SUM_M ? lm[0] : l) > 0x1p64f) != 0) {
-            const float lt = SUM_M ? lm[0] : xhalf_sum(l);
-            const float mn = lt > 0x1p64f ? m + log2f(lt) / a.c : m, mcn = mn * a.c;
-            rescale(fast_exp2(mc - mcn));
-            m = mn;
-            mc = mcn;
         }
     };
 
@@ -328,7 +308,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
     constexpr int PIPE_VPF = 2;       // V operands (two reads each) requested ahead of their product
     constexpr int PIPE_WA = 2;        // quarters of the tile's weights computed in phase A (the rest in phase B)
     constexpr bool PIPE_PACED = true; // tile loads spread over phase A instead of a burst behind the barrier
-    constexpr int VPQ = LSE ? 29 : 20;   // vector instructions per quarter of a tile's weights: 8 fma, 8 exp2, 4 convert (and 9 add)
+    constexpr int VPQ = MATCHED ? (LSE ? 32 : 24) : 29;   // vector instructions per quarter of a tile's weights: 8 fma, 8 exp2, 4 convert, 9 add and/or 4 dot2
 
     // value product number i of a tile (i = 8 kb + 4 t2 + db): its V operand, and the product
     auto v_read = [&](int i, int vstage) __attribute__((always_inline)) {
@@ -344,8 +324,7 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
     };
 
     // One step with compile-time ring stages: reads K(n+1) from stage KST, V(n) from stage VST.
-    auto step = [&](const f32x16 (&Sc)[2], f32x16 (&Sn)[2], int n, auto kst, auto vst, auto tracked) __attribute__((always_inline)) {
-        constexpr bool TRACK = decltype(tracked)::value;
+    auto step = [&](const f32x16 (&Sc)[2], f32x16 (&Sn)[2], int n, auto kst, auto vst) __attribute__((always_inline)) {
         constexpr int KST = decltype(kst)::value, VST = decltype(vst)::value;
         wait_vmcnt<0>();
         scrub(KST);
@@ -371,7 +350,9 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         // the weights belong to this phase: without a use here they would sink behind the branch below
 #pragma unroll
         for (int q = 0; q < PIPE_WA; ++q) asm volatile("" : "+v"(pb[q >> 1][q & 1]));
-        if (LSE) asm volatile("" : "+v"(l));
+        if (MATCHED) asm volatile("" : "+v"(lr));
+        else asm volatile("" : "+v"(l));
+        if (LSE) asm volatile("" : "+v"(ls32));
         // (tried and within noise: the first value operands of phase B requested at the end of this
         // phase; some of the vector instructions ahead of the first product)
 #pragma unroll
@@ -387,45 +368,32 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         __builtin_amdgcn_sched_barrier(0);
         if (needs_mask(n + 1)) mask_ragged(Sn, (t0 + n + 1) * BN);
         // phase B
-        sum_q(0, 0);
-        sum_q(0, 1);
 #pragma unroll
         for (int i = 0; i < 2 * DB; ++i) pv_op(i, v_read(i, VST));
 #pragma unroll
         for (int q = PIPE_WA; q < 4; ++q) weights_q(Sc, q >> 1, q & 1);
-        sum_q(1, 0);
-        sum_q(1, 1);
 #pragma unroll
         for (int i = 2 * DB; i < 4 * DB; ++i) pv_op(i, v_read(i, VST));
-        float mx = 0.f;
-        if (TRACK) mx = row_max(Sn);
+        const float mx = row_max(Sn);
 #pragma unroll
         for (int i = 0; i < 2 * PIPE_VPF; ++i) __builtin_amdgcn_sched_group_barrier(SG_DSR, 1, 1);
         static_for<4 * DB>([&](auto ic) __attribute__((always_inline)) {
             constexpr int i = decltype(ic)::value;
-            // the row sums' products as their weights are there
-            constexpr bool with_sum = SUM_M && (i == DB - 1 || i == 2 * DB - 1 || i == 2 * DB + 1 || i == 3 * DB);
-            __builtin_amdgcn_sched_group_barrier(SG_MFMA, with_sum ? 2 : 1, 1);
+            __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 1);
             if (i + PIPE_VPF < 4 * DB) __builtin_amdgcn_sched_group_barrier(SG_DSR, 2, 1);
             // the remaining quarters' weights during the first half's products, the row maximum after them
-            constexpr int nv = i < 2 * DB ? (VPQ * (4 - PIPE_WA) * (i + 1)) / (2 * DB) - (VPQ * (4 - PIPE_WA) * i) / (2 * DB) : TRACK ? 3 : 0;
+            constexpr int nv = i < 2 * DB ? (VPQ * (4 - PIPE_WA) * (i + 1)) / (2 * DB) - (VPQ * (4 - PIPE_WA) * i) / (2 * DB) : 3;
             if (nv > 0) __builtin_amdgcn_sched_group_barrier(SG_VALU | SG_TRANS, nv, 1);
         });
         __builtin_amdgcn_sched_barrier(0);
-        if (TRACK) move_reference(mx);
-        else move_by_sum();
+        move_reference(mx);
     };
 
     using st0 = std::integral_constant<int, 0>;
     using st1 = std::integral_constant<int, 1>;
 
-    // One pass over the partition's tiles.  TRACK: the second one, with every tile's maximum.  `again` is the word behind
-    // the ring by which a wave that met an overflow asks for it.
-    int *const again = (int *)(tlin_smem + 2 * NSTAGE * TILE_B);
-    auto pass = [&](auto tracked) __attribute__((always_inline)) {
-        constexpr bool TRACK = decltype(tracked)::value;
+    if (nt > 0) {
         f32x16 S0[2], S1[2];
-        reset();
         // prologue: K(0), then K(1) and V(0); scores and reference point of tile 0
         issue_k(0, 0);
         if (nt > 1) issue_k(1, 1);
@@ -448,11 +416,11 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         // step n reads K(n+1) from stage (n+1) % 2 and V(n) from stage n % 2
         int n = 0;
         for (; n + 1 < tl; n += 2) {
-            step(S0, S1, n, st1{}, st0{}, tracked);
-            step(S1, S0, n + 1, st0{}, st1{}, tracked);
+            step(S0, S1, n, st1{}, st0{});
+            step(S1, S0, n + 1, st0{}, st1{});
         }
         if (n < tl) {
-            step(S0, S1, n, st1{}, st0{}, tracked);
+            step(S0, S1, n, st1{}, st0{});
             ++n;
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) S0[kk] = S1[kk];
@@ -469,48 +437,21 @@ __device__ __forceinline__ void attn_bf16_pipe_body(const AttnArgs &a, int bid, 
         };
         // the wave's last tile (n = tl, in S0): weights and value products only
         if (tl >= 0) {
-            if (!TRACK) {
-                // seen by every wave behind the last barrier; the last tile, whose maximum is taken, needs no such look
-                float nan = (SUM_M ? lm[0] : l) * 0.f;          // stays 0 unless something is not finite
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        if (!PAD || 32 * db + 8 * (v >> 2) + 4 * h < a.D) nan = fmaf(oacc[db][v], 0.f, nan);
-                if (__builtin_amdgcn_ballot_w64(!(nan == 0.f)) != 0) *again = 1;
-                if (n > 0) move_reference(row_max(S0));
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            }
             meet(n);
-            const int voff1 = (n & 1) * TILE_B;
-            weights(S0, 0);
-            pv_half(0, voff1);
-            weights(S0, 1);
-            pv_half(1, voff1);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) sum_q(q >> 1, q & 1);
+            for (int db = 0; db < DB; ++db) vaddr[db] += (n & 1) * TILE_B;
+            weights(S0, 0);
+            pv_half(0, 0);
+            weights(S0, 1);
+            pv_half(1, 0);
             ++n;
         }
         // tiles behind the wave's last one (causal), or of a wave that owns no rows
         for (; n < nt; ++n) meet(n);
-    };
-    reset();
-    if (nt > 0) {
-        // The common pass keeps the reference point of the first tile: weights are fp32 and bf16 numbers, which
-        // are as precise at 2^60 as at 1, and the row sum tells when they have grown.  Only where something
-        // overflowed on the way (a logit 88 nats above all of the row's earlier ones, or values near the end of
-        // the range) the workgroup goes over its tiles again and takes every tile's maximum into account.
-        if (tid == 0) *again = 0;
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // written before the pass's first barrier
-        pass(std::false_type{});
-        if (__builtin_amdgcn_readfirstlane(*(volatile int *)again) != 0) {
-            asm volatile("s_barrier" ::: "memory");      // every wave is past its reads of the first pass's tiles
-            pass(std::true_type{});
-        }
     }
 
     // ---- epilogue.  Accumulator register v of block db is d = 32*db + 8*(v/4) + 4*h + v%4.
-    const float lx = LSE ? xhalf_sum(l) : lm[0], lt = SUM_M ? lm[0] : lx;   // for the log-sum-exp, the normaliser
+    const float lt = xhalf_sum(l), lx = LSE ? xhalf_sum(l32) : lt;
     const int row = qrow0 + j;
     if (row >= Wq) return;
     if (a.direct) {

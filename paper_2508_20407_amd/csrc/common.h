@@ -48,7 +48,6 @@ struct AttnArgs {
     void *O;
     int64_t o_sb, o_sh, o_sr;
     float *lse;                 // nullable, dense [BH][W]
-    int32_t want_lse;           // the call returns the log-sum-exp (direct: in lse; partials: the merge's)
     int32_t out_bf16;
     int32_t direct;
     int32_t stream_once;        // host's choice: K/V rows are read by one workgroup only and exceed the caches

@@ -460,13 +460,9 @@ tlin_status with_columns(int dim, F &&f)
 template <int D, int NW, int QB, bool CAUSAL, int NSTAGE, bool RESIDENT, int DP, bool NT, bool LSE = false>
 tlin_status launch_bf16_kernel(const AttnArgs &a, int grid, hipStream_t st)
 {
-    // the ring and, in the pipelined body, one word behind it
-    constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2 + (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>() ? 16 : 0);
+    constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2;
     static_assert(lds_bytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a gfx950 compute unit");
-    const auto kernel = [] {
-        if constexpr (LSE && !(CAUSAL && D == 64)) return attn_bf16_lse_kernel<D, NW, CAUSAL, DP, NT>;
-        else return attn_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, NT, LSE>;
-    }();
+    auto kernel = attn_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, NT, LSE>;
     static std::atomic<uint64_t> lds_allowed{0};
     if (allow_lds((const void *)kernel, lds_bytes, lds_allowed) != TLIN_OK) return TLIN_ERR_HIP;
     return launch_kernel((const void *)kernel, dim3(grid), dim3(NW * 64), lds_bytes, st, a);
@@ -481,10 +477,10 @@ tlin_status launch_bf16_shape(const AttnArgs &a, int grid, hipStream_t st)
         constexpr int DP = decltype(dp)::value;
         if constexpr (use_pipe_body<D, NW, QB, CAUSAL, NSTAGE, RESIDENT>()) {
             if constexpr (!CAUSAL) {
-                if (a.stream_once) return a.want_lse ? launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, true, true>(a, grid, st)
-                                                     : launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, true, false>(a, grid, st);
+                if (a.stream_once) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, true>(a, grid, st);
+            } else if constexpr (D == 64) {
+                if (a.lse) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, false, true>(a, grid, st);
             }
-            if (a.want_lse) return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, false, true>(a, grid, st);
         }
         return launch_bf16_kernel<D, NW, QB, CAUSAL, NSTAGE, RESIDENT, DP, false>(a, grid, st);
     });
@@ -735,7 +731,6 @@ void set_direct(AttnArgs &a, const tlin_params *p, void *O, float *lse)
     a.direct = 1;
     a.O = O; a.o_sb = o.b; a.o_sh = o.h; a.o_sr = o.r;
     a.lse = lse;
-    a.want_lse = lse != nullptr;
     a.out_bf16 = p->out_dtype == TLIN_BF16;
 }
 
@@ -761,7 +756,7 @@ MergeArgs merge_args(const tlin_params *p, const Workspace &w, int nparts, int n
 template <int D, int NW, int NSTAGE, int DP, bool NT>
 tlin_status launch_pair_kernel(const PairArgs &f, hipStream_t st)
 {
-    constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2 + (use_pipe_body<D, NW, 1, false, NSTAGE, false>() ? 16 : 0);
+    constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2;
     static_assert(lds_bytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a gfx950 compute unit");
     auto kernel = attn_bf16_pair_kernel<D, NW, NSTAGE, DP, NT>;
     static std::atomic<uint64_t> lds_allowed{0};
@@ -812,9 +807,9 @@ tlin_status launch_partials(const tlin_params *p, const AttnArgs &ah, const Attn
             return launch_pair_shape<128, 2, 2>(f, hs);
         }
         if (s.nw == 4) return launch_pair_shape<64, 4, 2>(f, hs);
-        // (a ring of three tiles in the classic body was ahead of this one only until it lost its maxima and row
-        // sums: 32 heads x 64, 64 rows over 60000: 102 -> 86 us, 12 heads x 36, 40 rows over 999754: 401 -> 306, sliding
-        // schedule of 8 heads x 64, 8000 rows in chunks of 64: 131 -> 96)
+        // (ahead of the classic body with a ring of three tiles: 32 heads x 64, 64 rows over 60000: 103 -> 87 us, 12
+        // heads x 36, 64 rows over 999754: 409 -> 334, sliding schedule of 8 heads x 64, 8000 rows in chunks of 64:
+        // 135 -> 100)
         return launch_pair_shape<64, 2, 2>(f, hs);
     }
     tlin_status st;
@@ -953,7 +948,6 @@ tlin_status tlin_history_attn(const tlin_params *p, const void *Q_win, const voi
     if ((st = check_device())) return st;
     const Workspace w = carve(ws, p, pl.nsplit);
     set_partial(a, w, pl.nsplit, 0);
-    a.want_lse = lse != nullptr;
     if ((st = launch_attn(p, false, a, hs))) return st;
     return launch_merge(p, merge_args(p, w, pl.nsplit, pl.nsplit, false, true, O, lse), hs);
 }

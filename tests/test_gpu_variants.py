@@ -7,7 +7,7 @@ import torch
 import oracle
 import tlin_inputs as ti
 import paper_2508_20407_amd as tl
-from helpers import assert_close, f32_rel_bound
+from helpers import assert_close, f32_rel_bound, to_host64
 from test_gpu_parity import padded
 
 pytestmark = pytest.mark.gpu
@@ -251,9 +251,8 @@ def test_fp32_operands_in_parts(D, W):
 @pytest.mark.parametrize("jump,vexp", [(6.0, 0), (12.0, 0), (60.0, 0), (12.0, 85)])
 def test_logits_far_above_the_first_tiles(D, W, jump, vexp):
     """bf16 rows whose largest logits come late: keys from the fifth tile on are `jump` times as large, so that the
-    reference point of the first tile is left behind by some 20 (the row sum passes no threshold), 45 (it does)
-    and 200 nats (weights overflow), and values so large that the accumulator overflows although the weights do
-    not.  Unscaled outputs within the bf16 tolerance; scores of hundreds of nats are fp32 sums and carry their error
+    reference point of the first tile is left behind by some 20, 45 and 200 nats, and values near the end of the
+    range.  Unscaled outputs within the bf16 tolerance; scores of hundreds of nats are fp32 sums and carry their error
     (2^-22 of them) into the weights."""
     N = 700
     w = ti.Workload(f"late_{D}_{W}_{jump}", 1, 2, D, N, W, ti.BF16, 1.0, 1357 + D + W + int(jump))
@@ -325,3 +324,138 @@ def test_long_query_sides_over_few_keys(D, N):
         assert_close(o[:, h:h + 1, torch.from_numpy(rows).cuda()], ro, w.dtype, f"{w.name} head {h}")
         # (the classic body sums rounded weights: 2^-8)
         np.testing.assert_allclose(lse[:, h:h + 1, torch.from_numpy(rows).cuda()].cpu().numpy(), rl, rtol=0, atol=4.5e-3)
+
+
+def bf16_bits(x):
+    """The upper halves of fp32 values (what is cut off must be zero or not matter)."""
+    return (np.asarray(x, dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)
+
+
+def masked_inputs(name, D, W, N, dtype, hist, win, mask, seed):
+    """Inputs whose history keys `hist` and window keys `win` (slices) are masked through column 0: the keys that
+    stay have 0 there, the masked ones `mask`, and the queries 2 or (every third row) 4, so that a masked key's logit is
+    -inf, also where `mask` is the type's lowest number (the product overflows)."""
+    w = ti.Workload(name, 1, 2, D, N, W, dtype, 1.0, seed)
+    host = ti.make(w)
+    bits = bf16_bits if dtype == ti.BF16 else np.float32
+    host["Q"][..., 0] = bits(np.where(np.arange(W) % 3 == 0, 4.0, 2.0).astype(np.float32))
+    for k, s in (("Kh", hist), ("Kw", win)):
+        host[k][..., 0] = 0
+        host[k][:, :, s, 0] = bits(np.float32(mask))
+    return w, host
+
+
+LOWEST = {ti.BF16: -(2.0 - 2.0 ** -7) * 2.0 ** 127, ti.F32: -float(np.finfo(np.float32).max)}
+
+
+def check_masked(w, host, hist, win, splits_list=(1, 2)):
+    """History, causal and layer calls of masked inputs against the oracle over the visible keys alone.  Window rows
+    that see masked window keys only have no value (0 / 0) and are left out."""
+    H, W, N = w.H, w.W, w.N
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    vh, vw = np.ones(N, bool), np.ones(W, bool)
+    vh[hist], vw[win] = False, False
+    kh, vvh = (np.ascontiguousarray(host[k][:, :, vh]) for k in ("Kh", "Vh"))
+    seen = np.cumsum(vw)                              # visible window keys of each row
+    rows = np.flatnonzero(seen > 0)
+    f32_rel = f32_rel_bound(25.0)
+
+    def window(i):                                    # oracle of window row i over its visible keys
+        pick = np.flatnonzero(vw[:i + 1])
+        return [np.ascontiguousarray(host[k][:, :, r]) for k, r in (("Q", [i]), ("Kw", pick), ("Vw", pick))]
+
+    some = sorted({int(rows[0]), int(rows[-1])} | {int(i) for i in rows[:: max(1, len(rows) // 12)]})
+    if vh.any():
+        ro, rl = oracle.history(host["Q"], kh, vvh, w.dtype, w.scale)
+        for splits in splits_list:
+            o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, num_splits=splits, out_dtype=torch.float32, return_lse=True)
+            assert_close(o, ro, w.dtype, f"{w.name} history splits {splits}, both outputs", f32_rel=f32_rel)
+            np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+            o = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, num_splits=splits, out_dtype=torch.float32)
+            assert_close(o, ro, w.dtype, f"{w.name} history splits {splits}", f32_rel=f32_rel)
+    for lse in (False, True):
+        o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale, out_dtype=torch.float32, return_lse=lse)
+        o = o[0] if lse else o
+        for i in some:
+            assert_close(o[:, :, i:i + 1], oracle.history(*window(i), w.dtype, w.scale)[0], w.dtype, f"{w.name} window row {i} lse {lse}", f32_rel=f32_rel)
+    for splits in splits_list:
+        o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=tl.TLIN_COMBINE_JOINT, scale=w.scale, num_splits=splits, out_dtype=torch.float32)
+        for i in some:
+            q, kw, vv = window(i)
+            ro = oracle.history(q, np.ascontiguousarray(np.concatenate([kh, kw], 2)), np.ascontiguousarray(np.concatenate([vvh, vv], 2)), w.dtype, w.scale)[0]
+            assert_close(o[:, :, i:i + 1], ro, w.dtype, f"{w.name} layer joint row {i} splits {splits}", f32_rel=f32_rel)
+
+
+MASKS = [(slice(0, 64), slice(0, 0)), (slice(0, 300), slice(0, 70)), (slice(640, 700), slice(0, 130)), (slice(0, 637), slice(5, 64))]
+
+
+@pytest.mark.parametrize("D", [36, 64, 96, 128])
+@pytest.mark.parametrize("W", [40, 129, 300])
+@pytest.mark.parametrize("hist,win", MASKS)
+@pytest.mark.parametrize("kind", ["inf", "lowest"])
+def test_masked_keys_bf16(D, W, hist, win, kind):
+    """Keys masked by -inf or by the type's lowest number: whole first tiles, all but the last tile, last tiles, and
+    partitions of three tiles and more."""
+    mask = -np.inf if kind == "inf" else LOWEST[ti.BF16]
+    win = slice(min(win.start, W - 20), min(win.stop, W - 20))
+    w, host = masked_inputs(f"masked_{D}_{W}_{hist.start}_{hist.stop}_{kind}", D, W, 700, ti.BF16, hist, win, mask, 4242 + D + W)
+    check_masked(w, host, hist, win)
+
+
+@pytest.mark.parametrize("D,N,hist", [(128, 180, slice(0, 64)), (128, 256, slice(0, 200)), (128, 50, slice(9, 50)), (96, 250, slice(0, 130)),
+                                      (64, 200, slice(0, 70)), (36, 300, slice(0, 256))])
+def test_masked_keys_of_long_query_sides(D, N, hist):
+    """The same where keys stay in LDS and a workgroup walks over many query blocks."""
+    W = 22050
+    w = ti.Workload(f"masked_few_{D}_{N}", 1, 12, D, N, W, ti.BF16, 1.0, 515 + D + N)
+    host = ti.make(w)
+    host["Q"][..., 0] = bf16_bits(np.where(np.arange(W) % 3 == 0, 4.0, 2.0))
+    host["Kh"][..., 0] = 0
+    host["Kh"][:, :, hist, 0] = bf16_bits(LOWEST[ti.BF16])
+    seen = np.ones(N, bool)
+    seen[hist] = False
+    o = tl.tlin_history_attn(*(padded(host[k], w.dtype) for k in ("Q", "Kh", "Vh")), scale=w.scale)
+    rows = np.arange(0, W, 41)
+    for h in (0, 11):
+        sub = [np.ascontiguousarray(host[k][:, h:h + 1, r]) for k, r in (("Q", rows), ("Kh", seen), ("Vh", seen))]
+        assert_close(o[:, h:h + 1, torch.from_numpy(rows).cuda()], oracle.history(*sub, w.dtype, w.scale)[0], w.dtype, f"{w.name} head {h}")
+
+
+@pytest.mark.parametrize("dtype", [ti.BF16, ti.F32])
+@pytest.mark.parametrize("D", [36, 64, 96, 128])
+@pytest.mark.parametrize("W,N", [(40, 700), (300, 700), (300, 90)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_a_bad_query_row_stays_alone(dtype, D, W, N, bad):
+    """A query row that is not finite leaves every other row's bits as they are."""
+    w = ti.Workload(f"bad_row_{D}_{W}_{N}", 1, 2, D, N, W, dtype, 1.0, 99 + D + W)
+    host = ti.make(w)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    rows = [3, 21, W - 1]
+    q = dev["Q"].clone() if dev["Q"].is_contiguous() else padded(host["Q"], w.dtype)
+    q[:, :, rows, 0] = bad
+    keep = torch.ones(W, dtype=torch.bool, device="cuda")
+    keep[rows] = False
+    for call in (lambda x: tl.tlin_history_attn(x, dev["Kh"], dev["Vh"], scale=w.scale),
+                 lambda x: tl.tlin_history_attn(x, dev["Kh"], dev["Vh"], scale=w.scale, return_lse=True)[0],
+                 lambda x: tl.tlin_window_causal_attn(x, dev["Kw"], dev["Vw"], scale=w.scale),
+                 lambda x: tl.tlin_window_causal_attn(x, dev["Kw"], dev["Vw"], scale=w.scale, return_lse=True)[0],
+                 lambda x: tl.tlin_layer_attn(x, dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], scale=w.scale)):
+        good, got = call(dev["Q"]), call(q)
+        assert torch.isnan(got[:, :, rows].float()).any(-1).all()
+        if dtype == ti.BF16:
+            assert torch.equal(got[:, :, keep], good[:, :, keep])
+        else:
+            assert_close(got[:, :, keep], to_host64(good[:, :, keep]), w.dtype, w.name)
+
+
+@pytest.mark.parametrize("D", [36, 64, 96, 128])
+@pytest.mark.parametrize("W", [40, 129, 300])
+def test_outputs_do_not_depend_on_the_log_sum_exp(D, W):
+    """bf16: asking for the log-sum-exp changes no bit of O."""
+    w = ti.Workload(f"both_{D}_{W}", 1, 2, D, 1111, W, ti.BF16, 1.0, 77 + D + W)
+    host = ti.make(w)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    for call in (lambda lse: tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, return_lse=lse),
+                 lambda lse: tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, num_splits=1, return_lse=lse),
+                 lambda lse: tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale, return_lse=lse)):
+        assert torch.equal(call(False), call(True)[0])
