@@ -599,11 +599,16 @@ bool use_resident(const tlin_params *p, bool causal, const AttnArgs &a)
     if (p->W <= 128) return false;
     const int ntiles = (a.NK + 63) / 64;
     const int64_t blocks = (int64_t)p->B * p->H * ((p->W + 255) / 256);      // the resident kernels are eight-wave ones
-    // Head dimensions up to 64 run the unpipelined body here, which the pipelined ring has passed where a block has more
-    // than two tiles (four above 48 columns) to hide its start behind: 32 heads, 131072 rows over 400 keys, x 64 675
-    // -> 619 us, x 36 633 -> 538, over 200 keys x 36 391 -> 368, but x 64 419 -> 439, and over 128 x 36 250 -> 286.
-    const int most = dpad(p->D) == 128 || p->D > 48 ? 4 : 2;
-    return ntiles <= most && blocks >= 4 * (int64_t)kNumCU;
+    if (blocks < 4 * (int64_t)kNumCU) return false;
+    if (dpad(p->D) == 128) return ntiles <= 4;
+    // Head dimensions up to 64 run the unpipelined body here, which the pipelined ring passes where a block has more
+    // than two tiles (four above 48 columns) to hide its start behind: 32 heads, 131072 rows over 400 keys, x 64 698
+    // -> 629 us, x 36 649 -> 550, over 256 keys x 36 407 -> 375, but x 64 419 -> 439, and over 128 x 36 250 -> 286.
+    // Three tiles of 40 to 48 columns only where a workgroup has few blocks to walk over: over 192 keys x 48, 32 heads,
+    // 131072 rows (64 blocks) 305 against 358 us in the ring, 30000 rows (14) 71 against 74, 12 heads, 50000 rows
+    // (9) 49.7 against 48.5.
+    if (ntiles == 3 && p->D >= 40 && p->D <= 48) return blocks >= 14 * (int64_t)kNumCU;
+    return ntiles <= (p->D > 48 ? 4 : 2);
 }
 
 // K/V rows of a history are read by exactly one workgroup when the window is a single query block,
@@ -627,7 +632,7 @@ tlin_status launch_attn(const tlin_params *p, bool causal, AttnArgs a, hipStream
         a.nqb = (p->W + 255) / 256;
         const int64_t bh = (int64_t)p->B * p->H;
         // (rounded down: twelve heads in 264 workgroups left eight for a second round; 50000 rows over 256 keys of 12
-        // heads x 128: 125 -> 66 us)
+        // heads x 128: 129 -> 93 us)
         int64_t g = kNumCU / bh;
         if (g < 1) g = 1;
         if (g > a.nqb) g = a.nqb;
