@@ -264,9 +264,11 @@ Plan plan_for_shape(const tlin_params *p, Shape s, int64_t target, int round_dow
         const int min_tiles = base <= 4 ? 2 : 8;
         const int cap = ntiles / min_tiles > 1 ? ntiles / min_tiles : 1;
         if (want > cap) want = cap;
-        // (fp32 windows of many rows and heads, two partitions at most: their four-wave workgroups ask for more than
-        // one where a single one does, and a layer call stays in the library's own array)
-        while (p->in_dtype == TLIN_F32 && s.nw == 4 && p->W > 128 && want > 1 && ws_bytes_for(p, want + 1) > TLIN_STATIC_WS_BYTES) --want;
+        // (fp32 in four-wave workgroups, three to a compute unit up to 64 columns and at any head dimension where
+        // history_shape chooses them: many heads would be cut into more partitions than a layer call has room for in the
+        // library's own array; they are cut into as many as fit, 664 heads x 64, 128 rows into one)
+        const bool more_places = p->in_dtype == TLIN_F32 && s.nw == 4 && (dpad(p->D) == 64 || p->W > 128);
+        while (more_places && want > 1 && ws_bytes_for(p, want + 1) > TLIN_STATIC_WS_BYTES) --want;
     }
     if (want < 1) want = 1;
     if (want > ntiles) want = ntiles;

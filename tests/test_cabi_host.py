@@ -180,6 +180,20 @@ def test_static_workspace_entry_point_checks_arguments_and_its_limit_on_the_host
     assert "#define TLIN_STATIC_WS_BYTES ((size_t)64 << 20)" in text and b.STATIC_WS_BYTES == 64 << 20
 
 
+@pytest.mark.parametrize("W", [65, 100, 128, 200])
+@pytest.mark.parametrize("D", [16, 64])
+def test_calls_of_many_heads_are_not_cut_out_of_the_static_workspace(W, D):
+    """fp32 layer calls that fit the library's own array in one partition are not refused for their second one."""
+    seen = 0
+    for H in range(8, 1601, 8):
+        for N in (300, 20000, 200000):
+            p = P(H=H, W=W, N=N, D=D, in_dtype=b.TLIN_F32, out_dtype=b.TLIN_F32)
+            if H * W * 2 * (64 * 4 + 8) <= b.STATIC_WS_BYTES:        # one partition and the window
+                assert b.workspace_bytes(p) <= b.STATIC_WS_BYTES, (H, N)
+                seen += 1
+    assert seen > 100
+
+
 def test_slide_planning_and_argument_checks():
     # 256 chunks of 512 rows, 32 heads: plenty of work items, so one partition per chunk history
     # plus the window partial = 2 fp32 partial slots per output row
