@@ -35,7 +35,9 @@
  *   - Errors are reported by return code only.  Argument validation runs on the host before
  *     any HIP call, so it behaves the same on a machine without a GPU.
  *   - Each (b, h) is an independent attention problem; there is no positional term, bias,
- *     dropout or key/value head sharing.  Non-finite inputs give unspecified outputs.
+ *     dropout or key/value head sharing.  Keys whose logit is -infinity (an element of -infinity, or of the
+ *     type's lowest number whose product overflows) have weight 0.  Other non-finite inputs give unspecified
+ *     outputs in the rows that meet them, and in no others.
  *   - Results are exact softmax attention up to rounding.  bf16 inputs are multiplied with fp32
  *     accumulation on the matrix cores, softmax weights rounded to bf16 before the second product.
  *     Where one or two query rows meet a history of 1024 rows or more, tlin_history_attn may run on the
@@ -43,7 +45,8 @@
  *     are fp32.  fp32 inputs: every operand of a product, the weights included, enters with its 24 bits (as three
  *     bf16 parts on the matrix cores, six exact products of parts per product summed in fp32, the three below
  *     2^-23 of it left out; or fp32 multiply-adds of the vector unit for up to eight query rows over a long history).
- *     Parts below bf16's subnormals count as zero: values below 2^-110 keep an absolute precision of 2^-134.
+ *     Rows that meet something that is not finite, queries beyond 2^100 or below 2^-100 and values below 2^-110
+ *     are computed a second time, by fp32 matrix instructions, in about three times the time.
  *   - Accuracy envelope.  bf16 inputs: |O - exact| <= 2e-2 (mean <= 5e-3) for inputs of unit
  *     scale.  fp32 inputs: a logit is an fp32 sum of D products and carries an absolute error of
  *     a few 2^-24 of its own size, which the exponential turns into the same RELATIVE error of

@@ -6,13 +6,10 @@
 // sum of three bf16 numbers without a remainder (8 + 8 + 8 bits of significand, the exponents have the same
 // range).  Every operand (Q, K, V and the weights) is split that way, and a product is the six bf16 products of
 // parts whose indices add up to at most two, exact in the fp32 accumulator; the three that are left out are
-// below 2^-23 of the product, of either sign, 2^-26 as a rule (the middle part is rounded to nearest).  Measured
-// against 64 bits the results are nearer than those of a chain of fp32 matrix instructions (32 heads x 128, 512
-// rows over 32768: 2-norm 1.3e-7 against 1.7e-7, largest 1.1e-6 against 1.6e-6; the same order at every size
-// tried): an accumulator is rounded once per sixteen products instead of once per two.
-//   32 heads x 128, 512 rows over 32768 history rows: 2398 -> 1395 us (199 TFLOP/s, 1.19 PFLOP/s of bf16
+// below 2^-23 of the product, of either sign, 2^-26 as a rule (the middle part is rounded to nearest).
+//   32 heads x 128, 512 rows over 32768 history rows: 2451 -> 1298 us (215 TFLOP/s, 1.29 PFLOP/s of bf16
 //   products; the library's bf16 matrix product reaches 1.33 on this card, the power limit), 32 heads x 36, 64
-//   rows over 20000: 104 -> 72, causal, 16 heads x 128, 4096 rows: 1030 -> 436.
+//   rows over 32768: 170 -> 116, causal, 16 heads x 128, 4096 rows: 1032 -> 379.
 //
 // Mapping (wave64; a wave owns 32 query rows; operand layouts as in attn_bf16_pipe_body):
 //   * Tiles of 32 keys.  A lane loads its share of a tile into registers (the tile after the next step's), splits
@@ -31,7 +28,8 @@
 namespace tlin {
 
 // x = p[0] + p[1] + p[2] exactly, each part four bf16 values: the leading 8 bits as they stand, the next 8 rounded
-// to nearest (so that what lies below them carries no common sign), and the rest.
+// to nearest (so that what lies below them carries no common sign), and the rest.  Not for infinities, whose p[1] is
+// NaN: see the end of attn_f32_body.
 __device__ __forceinline__ void split4(f32x4 x, u32x2 (&p)[3])
 {
 #pragma unroll
@@ -41,11 +39,19 @@ __device__ __forceinline__ void split4(f32x4 x, u32x2 (&p)[3])
         p[0][e] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
         const float r0 = x0 - __builtin_bit_cast(float, u0 & 0xffff0000u), r1 = x1 - __builtin_bit_cast(float, u1 & 0xffff0000u);
         const bf16x2 b = {(__bf16)r0, (__bf16)r1};
-        const unsigned ub = __builtin_bit_cast(unsigned, b);
+        unsigned ub = __builtin_bit_cast(unsigned, b);
+        asm("" : "+v"(ub));                    // (or both are converted once more for their remainders)
         p[1][e] = ub;
         const bf16x2 c = {(__bf16)(r0 - __builtin_bit_cast(float, ub << 16)), (__bf16)(r1 - __builtin_bit_cast(float, ub & 0xffff0000u))};
         p[2][e] = __builtin_bit_cast(unsigned, c);
     }
+}
+
+// The smallest magnitude among values that are not zero, as an ordered number (the bits without the sign, doubled,
+// less one: zeros come out last).
+__device__ __forceinline__ unsigned least_nonzero(unsigned least, float x)
+{
+    return min(least, (__builtin_bit_cast(unsigned, x) << 1) - 1u);
 }
 
 // Order of a region's instructions: M products, with the next region's R operand reads and V vector instructions
@@ -112,19 +118,30 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
     // 0 and 1 stay in registers, part 2 (one product in six) in LDS, each wave its own.
     const int qrow0 = qb * BM + wave * 32;
     bf16x8 q0[DS], q1[DS];
+    uint64_t far;                          // lanes whose queries leave 2^-100 .. 2^100 (see below)
     {
-        const int r = min(qrow0 + j, Wq - 1);
-        const float *qp = Qg + (int64_t)r * a.q_sr + 8 * h;
+        float q_most[2] = {0.f, 0.f};
+        unsigned q_least[2] = {0xffffffffu, 0xffffffffu};
+        const float *const qp = Qg + (int64_t)min(qrow0 + j, Wq - 1) * a.q_sr + 8 * h;
 #pragma unroll
         for (int s = 0; s < DS; ++s) {
             u32x2 p[2][3];
 #pragma unroll
-            for (int e = 0; e < 2; ++e)
-                split4(16 * s + 8 * h + 4 * e < a.D ? *(const f32x4 *)(qp + 16 * s + 4 * e) : f32x4{0.f, 0.f, 0.f, 0.f}, p[e]);
+            for (int e = 0; e < 2; ++e) {
+                const f32x4 x = 16 * s + 8 * h + 4 * e < a.D ? *(const f32x4 *)(qp + 16 * s + 4 * e) : f32x4{0.f, 0.f, 0.f, 0.f};
+                split4(x, p[e]);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    q_most[e] = fmaxf(q_most[e], fabsf(x[v]));
+                    q_least[e] = least_nonzero(q_least[e], x[v]);
+                }
+            }
             q0[s] = __builtin_bit_cast(bf16x8, u32x4{p[0][0][0], p[0][0][1], p[1][0][0], p[1][0][1]});
             q1[s] = __builtin_bit_cast(bf16x8, u32x4{p[0][1][0], p[0][1][1], p[1][1][0], p[1][1][1]});
             *(u32x4 *)(Q2 + s * 1024 + lane * 16) = u32x4{p[0][2][0], p[0][2][1], p[1][2][0], p[1][2][1]};
         }
+        far = __builtin_amdgcn_ballot_w64(fmaxf(q_most[0], q_most[1]) > 0x1p100f || min(q_least[0], q_least[1]) < least_nonzero(0xffffffffu, 0x1p-100f));
+        asm volatile("" : "+s"(far));          // here, where the queries are at hand
     }
 
     // ---- tile loads: load i of this lane is piece `lc` of tile row i * LROWS + lr, in memory and in LDS
@@ -165,7 +182,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
     // The running maximum only moves when a tile maximum exceeds it by more than 2^8 in the
     // exponent: weights stay <= 256 and the accumulator is rescaled rarely.  Any reference point
     // gives the same normalised result.
-    const float thr = 8.0f / a.c;
+    const float thr = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, 8.0f / a.c)));
 
     // LDS addresses: K fragment of step s, key j, columns 16 s + 8 h .. + 7; V operand of column block db, see
     // attn_bf16_pipe_body
@@ -190,10 +207,110 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
     };
     auto mma = [](bf16x8 x, bf16x8 y, f32x16 c) __attribute__((always_inline)) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0); };
 
+    // ---- mask of a tile's scores (keys past the end of the tensor, and (causal) keys after the query row) and its
+    // maximum, and the reference point's move to it
+    auto mask_and_reference = [&](f32x16 &s, int key0, int j, int h) __attribute__((always_inline)) {
+        const int row = qrow0 + j;
+        if (key0 + BN > NK || (CAUSAL && key0 + BN - 1 > qrow0)) {
+            const int lim = CAUSAL ? min(row, NK - 1) : NK - 1;   // last visible key
+            const int rel = lim - key0 - 4 * h;                    // the same, counted from this lane's first key
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (8 * (v >> 2) + (v & 3) > rel) s[v] = -INFINITY;
+        }
+
+        float mx = s[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+        mx = xhalf_max(mx);
+        if (__builtin_amdgcn_ballot_w64(mx > m + thr) != 0) {
+            const float mn = fmaxf(m, mx);
+            const float alpha = (mn == -INFINITY) ? 1.f : fast_exp2((m - mn) * a.c);
+            l *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
+            m = mn;
+        }
+    };
+
     // Tiles after every row this wave owns (causal), and all tiles where the window ends before its first
     // row, are not computed by it, but the wave still loads and splits its share of them for the others and meets
     // them at the barriers: the waves that have rows get the matrix cores for themselves.
     const int t1w = qrow0 >= Wq ? t0 : CAUSAL ? min(t1, (qrow0 + 31) / BN + 1) : t1;
+
+    // ---- The same over the partition by fp32 matrix instructions, a wave for itself, its operands straight from memory.
+    // A 32x32x2 product contracts over two indices, one per half-wave; which two is free as long as both operands agree:
+    //   scores  step (t, e) pairs columns 8 t + e (h = 0) and 8 t + 4 + e (h = 1): a lane needs K[key j][8 t + 4 h ..
+    //           + 3], one 16-byte load per four products, and its query's same columns, which it keeps in registers.
+    //   values  step (g, e) pairs keys 8 g + e and 8 g + 4 + e: the weight operand is the score accumulator's register
+    //           4 g + e as it stands, the other V[key 8 g + 4 h + e][32 db + j].
+    // Sums over columns run as chains of 32 terms, a tile's value product on its own: short chains round less.
+    auto fp32_pass = [&]() __attribute__((always_inline)) {
+        // (what depends on the lane is computed again instead of being kept through the first pass)
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int j = lane & 31, h = lane >> 5;
+        const float *const qp = Qg + (int64_t)min(qrow0 + j, Wq - 1) * a.q_sr + 4 * h;
+        f32x4 qf[4 * DB];
+#pragma unroll
+        for (int t8 = 0; t8 < 4 * DB; ++t8) qf[t8] = 8 * t8 + 4 * h < a.D ? *(const f32x4 *)(qp + 8 * t8) : f32x4{0.f, 0.f, 0.f, 0.f};
+        m = -INFINITY;
+        l = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
+        for (int t = t0; t < t1w; ++t) {
+            const int key0 = t * BN, rows = min(BN, NK - key0);      // as in load_tile
+            auto kr = __builtin_amdgcn_make_buffer_rsrc((void *)(Kg + key0 * k_rb), 0, (int)(rows * k_rb), 0x00020000);
+            auto vr = __builtin_amdgcn_make_buffer_rsrc((void *)(Vg + key0 * v_rb), 0, (int)(rows * v_rb), 0x00020000);
+            const unsigned ko = (unsigned)(j * k_rb) + 16 * h, vo = (unsigned)(4 * h * v_rb) + 4 * j;
+            f32x16 s;
+#pragma unroll
+            for (int c = 0; c < DB; ++c) {
+                f32x16 part;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) part[v] = 0.f;
+#pragma unroll
+                for (int t8 = 4 * c; t8 < 4 * c + 4; ++t8) {
+                    const f32x4 kf = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(kr, 8 * t8 + 4 * h < a.D ? ko + 32 * t8 : 0x80000000u, 0, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) part = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[t8][e], part, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) s[v] = c == 0 ? part[v] : s[v] + part[v];
+            }
+            mask_and_reference(s, key0, j, h);
+            const float mref = (m == -INFINITY) ? 0.f : m;
+            float ls = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                s[v] = fast_exp2((s[v] - mref) * a.c);
+                ls += s[v];
+            }
+            l += ls;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                f32x16 pv;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) pv[v] = 0.f;
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const unsigned off = 32 * db + j < a.D ? vo + (unsigned)((8 * g + e) * v_rb) + 128 * db : 0x80000000u;
+                        const float vf = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vr, off, 0, 0));
+                        pv = __builtin_amdgcn_mfma_f32_32x32x2f32(vf, s[4 * g + e], pv, 0, 0, 0);
+                    }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) oacc[db][v] += pv[v];
+                __builtin_amdgcn_sched_barrier(0);     // keeps the next block's loads (registers) behind this block
+            }
+        }
+    };
+
     if (t0 < t1) {
         load_k(t0);
 #pragma unroll
@@ -236,31 +353,9 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
 #pragma unroll
         for (int v = 0; v < 16; ++v) s[v] += lo[v];
 
-        // ---- mask: keys past the end of the tensor, and (causal) keys after the query row
-        const int row = qrow0 + j;
-        if (key0 + BN > NK || (CAUSAL && key0 + BN - 1 > qrow0)) {
-            const int lim = CAUSAL ? min(row, NK - 1) : NK - 1;   // last visible key
-            const int rel = lim - key0 - 4 * h;                    // the same, counted from this lane's first key
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (8 * (v >> 2) + (v & 3) > rel) s[v] = -INFINITY;
-        }
+        mask_and_reference(s, key0, j, h);
 
-        // ---- online softmax
-        float mx = s[0];
-#pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-        mx = xhalf_max(mx);
-        if (__builtin_amdgcn_ballot_w64(mx > m + thr) != 0) {
-            const float mn = fmaxf(m, mx);
-            const float alpha = (mn == -INFINITY) ? 1.f : fast_exp2((m - mn) * a.c);
-            l *= alpha;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
-            m = mn;
-        }
+        // ---- weights.
         // (s - m) * c rather than fma(s, c, -m*c): the key that holds the maximum gets weight exactly 1
         const float mref = (m == -INFINITY) ? 0.f : m;
         float ls = 0.f;
@@ -273,8 +368,9 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
                 f32x4 w;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    w[v] = fast_exp2((s[8 * t2 + 4 * e + v] - mref) * a.c);
-                    ls += w[v];
+                    const float p = fast_exp2((s[8 * t2 + 4 * e + v] - mref) * a.c);
+                    ls += p;
+                    w[v] = p;
                 }
                 split4(w, p[e]);
             }
@@ -337,9 +433,35 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
         meet();
     }
 
+
+    // ---- inputs that three bf16 parts cannot hold.  Infinities (and NaN) in Q, K or V and products that overflow leave
+    // something that is not finite in a row's sum or accumulator.  Parts below bf16's range are lost: an element of Q, K
+    // or V keeps an absolute precision of 2^-134, which matters only where it meets something very large or where a
+    // column is as small throughout: queries beyond 2^100 or (not zero) below 2^-100, outputs (not zero) below 2^-110
+    // in several rows (in one it is sums that cancel; a wave of fewer than four rows: below 2^-116).  The wave then goes
+    // over its partition again with fp32 matrix instructions.
+    if (t0 < t1w) {
+        float nan[4] = {l * 0.f, 0.f, 0.f, 0.f};        // stay 0 unless something is not finite (four: short chains)
+        unsigned least[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                nan[v & 3] = fmaf(oacc[db][v], 0.f, nan[v & 3]);
+                least[v & 3] = least_nonzero(least[v & 3], oacc[db][v]);
+            }
+        const uint64_t odd = far | __builtin_amdgcn_ballot_w64(!((nan[0] + nan[1]) + (nan[2] + nan[3]) == 0.f));
+        const bool few = Wq - qrow0 < 4;
+        const unsigned limit = least_nonzero(0xffffffffu, xhalf_sum(l) * (few ? 0x1p-116f : 0x1p-110f));
+        const uint64_t small = __builtin_amdgcn_ballot_w64(qrow0 + j < Wq && min(min(least[0], least[1]), min(least[2], least[3])) < limit);
+        if (odd != 0 || __builtin_popcountll(small) >= (few ? 1 : 4)) fp32_pass();
+    }
+
     // ---- epilogue.  Accumulator register v of block db is d = 32*db + 8*(v/4) + 4*h + v%4.
     const float lt = xhalf_sum(l);
-    const int row = qrow0 + j;
+    int lane_e = threadIdx.x & 63;             // (computed again, as in fp32_pass)
+    asm volatile("" : "+v"(lane_e));
+    const int row = qrow0 + (lane_e & 31), half = lane_e >> 5;
     if (row >= Wq) return;
     if (a.direct) {
         const float inv = 1.0f / lt;
@@ -348,7 +470,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int d = 32 * db + 8 * g + 4 * h;
+                const int d = 32 * db + 8 * g + 4 * half;
                 if (DP && d >= a.D) continue;      // column beyond the tensors' head dimension
                 f32x4 o;
 #pragma unroll
@@ -362,7 +484,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
                     *(f32x4 *)((float *)a.O + off + d) = o;
                 }
             }
-        if (a.lse && h == 0) a.lse[(int64_t)bh * a.W + row] = m * a.scale + logf(lt);
+        if (a.lse && half == 0) a.lse[(int64_t)bh * a.W + row] = m * a.scale + logf(lt);
     } else {
         const int64_t slot = pr.slot + a.part0 + (CAUSAL ? 0 : split);
         float *op = a.Opart + (slot * a.W + row) * D;
@@ -373,9 +495,9 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
                 f32x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = oacc[db][4 * g + e];
-                *(f32x4 *)(op + 32 * db + 8 * g + 4 * h) = o;
+                *(f32x4 *)(op + 32 * db + 8 * g + 4 * half) = o;
             }
-        if (h == 0) {
+        if (half == 0) {
             a.Mpart[slot * a.W + row] = m * a.c;
             a.Lpart[slot * a.W + row] = lt;
         }

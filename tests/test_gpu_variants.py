@@ -402,6 +402,63 @@ def test_masked_keys_bf16(D, W, hist, win, kind):
     check_masked(w, host, hist, win)
 
 
+@pytest.mark.parametrize("D", [36, 64, 96, 128])
+@pytest.mark.parametrize("W", [12, 129, 300])
+@pytest.mark.parametrize("hist,win", MASKS)
+@pytest.mark.parametrize("kind", ["inf", "lowest"])
+def test_masked_keys_fp32(D, W, hist, win, kind):
+    """The same in fp32, whose operands are split into parts that an infinity does not have."""
+    mask = -np.inf if kind == "inf" else LOWEST[ti.F32]
+    win = slice(min(win.start, max(0, W - 20)), min(win.stop, max(0, W - 20)))
+    w, host = masked_inputs(f"masked_f32_{D}_{W}_{hist.start}_{hist.stop}_{kind}", D, W, 700, ti.F32, hist, win, mask, 2424 + D + W)
+    check_masked(w, host, hist, win)
+
+
+@pytest.mark.parametrize("D", [36, 64, 96, 128])
+@pytest.mark.parametrize("W", [12, 129, 300])
+def test_infinite_values_fp32(D, W):
+    """An infinite value makes its column infinite in the rows that see it, and no other column."""
+    w = ti.Workload(f"inf_value_{D}_{W}", 1, 2, D, 700, W, ti.F32, 1.0, 31 + D + W)
+    host = ti.make(w)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    f32_rel = f32_rel_bound(10.0)
+    for k, call, ref in (("h", tl.tlin_history_attn, oracle.history), ("w", tl.tlin_window_causal_attn, oracle.window_causal)):
+        v = dev["V" + k].clone() if dev["V" + k].is_contiguous() else padded(host["V" + k], w.dtype)
+        v[:, :, 7, 3], v[:, :, 9, 5] = float("inf"), float("-inf")
+        o = call(dev["Q"], dev["K" + k], v, scale=w.scale)
+        ro = ref(host["Q"], host["K" + k], host["V" + k], w.dtype, w.scale)[0]
+        assert (o[:, :, 9:, 3] == float("inf")).all() and (o[:, :, 9:, 5] == float("-inf")).all()
+        cols = [c for c in range(D) if c not in (3, 5)]
+        assert_close(o[..., cols], ro[..., cols], w.dtype, f"{w.name} {k}", f32_rel=f32_rel)
+
+
+@pytest.mark.parametrize("D", [36, 64, 96, 128])
+@pytest.mark.parametrize("W", [12, 129, 300])
+@pytest.mark.parametrize("eq,ek,ev,columns", [(115, -115, 0, 1), (-115, 115, 0, 1), (110, -110, 0, 2), (0, 0, -115, 1), (0, 0, -122, 2), (0, 0, 110, 1)])
+def test_far_ends_of_the_range_fp32(D, W, eq, ek, ev, columns):
+    """Queries, keys and values (every one, or every second column) near the ends of fp32's range: their parts leave
+    bf16's, the results keep fp32's accuracy."""
+    w = ti.Workload(f"far_{D}_{W}_{eq}_{ev}_{columns}", 1, 2, D, 700, W, ti.F32, 1.0, 63 + D + W)
+    host = ti.make(w)
+    for k, e in (("Q", eq), ("Kh", ek), ("Kw", ek), ("Vh", ev), ("Vw", ev)):
+        host[k][..., ::columns] *= np.float32(2.0 ** e)
+    dev = {k: padded(v, w.dtype) for k, v in host.items()}
+    for splits in (1, 2):
+        o, lse = tl.tlin_history_attn(dev["Q"], dev["Kh"], dev["Vh"], scale=w.scale, num_splits=splits, return_lse=True)
+        ro, rl = oracle.history(host["Q"], host["Kh"], host["Vh"], w.dtype, w.scale)
+        for c in range(columns):
+            assert_close(to_host64(o)[..., c::columns], ro[..., c::columns], w.dtype, f"{w.name} history splits {splits}")
+        np.testing.assert_allclose(lse.cpu().numpy(), rl, rtol=1e-5, atol=1e-5)
+    o = tl.tlin_window_causal_attn(dev["Q"], dev["Kw"], dev["Vw"], scale=w.scale)
+    ro = oracle.window_causal(host["Q"], host["Kw"], host["Vw"], w.dtype, w.scale)[0]
+    for c in range(columns):
+        assert_close(to_host64(o)[..., c::columns], ro[..., c::columns], w.dtype, f"{w.name} window")
+    o = tl.tlin_layer_attn(dev["Q"], dev["Kh"], dev["Vh"], dev["Kw"], dev["Vw"], combine=tl.TLIN_COMBINE_JOINT, scale=w.scale)
+    ro = oracle.layer(host["Q"], host["Kh"], host["Vh"], host["Kw"], host["Vw"], w.dtype, w.scale, oracle.JOINT)
+    for c in range(columns):
+        assert_close(to_host64(o)[..., c::columns], ro[..., c::columns], w.dtype, f"{w.name} layer")
+
+
 @pytest.mark.parametrize("D,N,hist", [(128, 180, slice(0, 64)), (128, 256, slice(0, 200)), (128, 50, slice(9, 50)), (96, 250, slice(0, 130)),
                                       (64, 200, slice(0, 70)), (36, 300, slice(0, 256))])
 def test_masked_keys_of_long_query_sides(D, N, hist):
