@@ -6,7 +6,12 @@
 // sum of three bf16 numbers without a remainder (8 + 8 + 8 bits of significand, the exponents have the same
 // range).  Every operand (Q, K, V and the weights) is split that way, and a product is the six bf16 products of
 // parts whose indices add up to at most two, exact in the fp32 accumulator; the three that are left out are
-// below 2^-23 of the product, of either sign, 2^-26 as a rule (the middle part is rounded to nearest).
+// below 2^-23 of the product, of either sign, 2^-26 as a rule (the middle part is rounded to nearest).  The bf16 matrix
+// instruction rounds its sums towards minus infinity (an offset of 1e-9 of the values per key, measured; the fp32
+// one rounds to nearest), which adds up over a history: every other tile's weights are negated and its product
+// subtracted, so that the offsets cancel.  Measured against 64 bits, 2-norm, fp32 matrix instructions -> this kernel
+// (without the change of sign): 40 rows x 64 over 20000 rows 1.77e-7 -> 1.47e-7 (1.97e-7), over 10^5 1.85e-7 ->
+// 1.62e-7 (3.33e-7), over 10^6 2.48e-7 -> 2.33e-7 (1.03e-6).
 //   32 heads x 128, 512 rows over 32768 history rows: 2451 -> 1298 us (215 TFLOP/s, 1.29 PFLOP/s of bf16
 //   products; the library's bf16 matrix product reaches 1.33 on this card, the power limit), 32 heads x 36, 64
 //   rows over 32768: 170 -> 116, causal, 16 heads x 128, 4096 rows: 1032 -> 379.
@@ -356,6 +361,9 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
         mask_and_reference(s, key0, j, h);
 
         // ---- weights.
+        // (every other tile's negated: see the value product)
+        const unsigned flip = (unsigned)t << 31;
+        const float sign = __builtin_bit_cast(float, 0x3f800000u ^ flip);
         // (s - m) * c rather than fma(s, c, -m*c): the key that holds the maximum gets weight exactly 1
         const float mref = (m == -INFINITY) ? 0.f : m;
         float ls = 0.f;
@@ -370,7 +378,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
                 for (int v = 0; v < 4; ++v) {
                     const float p = fast_exp2((s[8 * t2 + 4 * e + v] - mref) * a.c);
                     ls += p;
-                    w[v] = p;
+                    w[v] = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, p) ^ flip);
                 }
                 split4(w, p[e]);
             }
@@ -415,7 +423,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs &a, int bid, int nb
             for (int n = p0; n < p1; ++n) put_k(n);
             if (t2 == 1)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) oacc[db][v] += pv[v];
+                for (int v = 0; v < 16; ++v) oacc[db][v] = fmaf(pv[v], sign, oacc[db][v]);
             interleave<6, 5 + 2 * t2, (p1 - p0) * 27, 1>();
         });
         meet();

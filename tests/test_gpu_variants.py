@@ -459,6 +459,23 @@ def test_far_ends_of_the_range_fp32(D, W, eq, ek, ev, columns):
         assert_close(to_host64(o)[..., c::columns], ro[..., c::columns], w.dtype, f"{w.name} layer")
 
 
+@pytest.mark.parametrize("D", [36, 64, 128])
+@pytest.mark.parametrize("W", [33, 100, 300])
+def test_no_offset_over_long_histories_fp32(D, W):
+    """The bf16 matrix instruction rounds towards minus infinity: 1e-9 of the values per key if nothing is done about it,
+    which over 10^6 keys is four times the error of fp32 sums.  Mean error of outputs of values around zero, whose 2-norm
+    is 1 / sqrt(N): independent roundings of 4e-7 leave a standard error of 4e-7 / sqrt(N W D) (3e-11 at most here,
+    bound 1e-10)."""
+    w = ti.Workload(f"offset_{D}_{W}", 1, 1, D, 200000, W, ti.F32, 1.0, 11 + D + W)
+    gen = torch.Generator(device="cuda").manual_seed(w.seed)
+    q, k, v = (torch.randn(1, 1, r, D, generator=gen, device="cuda") for r in (W, w.N, w.N))
+    for splits in (0, 16):
+        o = tl.tlin_history_attn(0.5 * q, 0.5 * k, v, scale=w.scale, num_splits=splits)
+        r = torch.softmax((0.5 * q).double() @ (0.5 * k).double().transpose(-1, -2).contiguous() * w.scale, -1) @ v.double()
+        d = o.double() - r
+        assert abs(d.mean().item()) <= 1e-10, d.mean().item()
+
+
 @pytest.mark.parametrize("D,N,hist", [(128, 180, slice(0, 64)), (128, 256, slice(0, 200)), (128, 50, slice(9, 50)), (96, 250, slice(0, 130)),
                                       (64, 200, slice(0, 70)), (36, 300, slice(0, 256))])
 def test_masked_keys_of_long_query_sides(D, N, hist):
