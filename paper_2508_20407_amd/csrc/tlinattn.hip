@@ -294,21 +294,21 @@ Plan plan_for_shape(const tlin_params *p, Shape s)
 // compute unit, leave nothing idle and cut the history into more partitions.  A tile takes the two 1.12 of an
 // eight-wave workgroup's time (each loads it for itself), one that has the compute unit to itself 0.8, and every
 // partition its partials' way out and back in: a tile is some 1.75 us at 128 columns (fp32, half as many keys: 5.2),
-// partials move at 5 TB/s.  Measured, eight waves -> four: 16 heads x 96, 300 rows over 50021: 146 -> 129 us; fp32, 48 heads x 96, 300 rows over 17905: 907 -> 701; the other way round 64 heads x 128 (fp32), 300 rows over 2212: 143 against 150, 24 heads x 96,
-// 384 rows over 6280: 42.5 against 44.7.
+// partials move at 5 TB/s.  Measured, eight waves -> four: 16 heads x 96, 300 rows over 50021: 146 -> 129 us; 48 heads x
+// 128, 300 rows over 33996 405 -> 327, 32 heads, 260 rows over 131072 857 -> 743; fp32, 48 heads x 96, 300 rows over
+// 17905: 907 -> 701; the other way round 64 heads x 128 (fp32), 300 rows over 2212: 143 against 150, 24 heads x 128, 384
+// rows over 6280: 43.7 against 44.6, x 96 42.5 against 44.7.
 Shape history_shape(const tlin_params *p)
 {
     const Shape s = kernel_shape(p->in_dtype, p->W, p->D), four = {4, 1};
     if (s.nw != 8 || p->W <= 256 || p->W > 384 || p->N < 1) return s;
-    // (bf16 at 128 columns stays: its partitions are counted on to fill the chip once in blocks of 256 rows)
-    if (p->in_dtype == TLIN_BF16 && p->D == 128) return s;
     const Plan p8 = plan_for_shape(p, s), p4 = plan_for_shape(p, four);
     if (ws_bytes_for(p, p4.nsplit + 1) > TLIN_STATIC_WS_BYTES) return s;
     const double tile = (p->in_dtype == TLIN_F32 ? 5.2e-6 : 1.75e-6) * p->D / 128;
     const double partial = p->B * p->H * (double)p->W * dpad(p->D) * 8 / 5e12;
     const double factor = query_items(p, four) * p4.nsplit <= kNumCU ? 0.8 : 1.12;
     const double t8 = p8.tiles_per_split * tile + p8.nsplit * partial, t4 = factor * p4.tiles_per_split * tile + p4.nsplit * partial;
-    return t4 < 0.96 * t8 ? four : s;
+    return t4 < 0.95 * t8 ? four : s;
 }
 
 Plan plan_history(const tlin_params *p) { return plan_for_shape(p, history_shape(p)); }

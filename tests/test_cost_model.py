@@ -53,10 +53,11 @@ def test_library_flop_accounting_is_the_history_term_of_the_model():
 
 
 def test_partitions_fill_the_chip_once():
-    """Twelve heads do not divide 256 compute units: the history workgroups stay within what the chip holds."""
+    """Twelve heads do not divide 256 compute units: the history workgroups stay within what the chip holds (one of
+    eight waves and 256 rows to a compute unit at 128 columns, or two of four waves and 128 rows; three at 64)."""
     from paper_2508_20407_amd import binding as b
-    for B, H, W, D, wgs in ((1, 12, 300, 128, 256), (4, 12, 256, 128, 256), (1, 12, 300, 64, 768), (2, 12, 100, 128, 512)):
+    for B, H, W, D, rows, wgs in ((1, 12, 300, 128, 128, 512), (1, 12, 400, 128, 256, 256), (4, 12, 256, 128, 256, 256),
+                                  (1, 12, 300, 64, 128, 768), (2, 12, 100, 128, 128, 512)):
         n = b.num_splits(b.make_params(B, H, W, 300000, D, b.TLIN_BF16, b.TLIN_BF16, D ** -0.5))
-        rows = {128: 256 if W > 128 else 128, 64: 128}[D]
         blocks = B * H * (-(-W // rows)) * n
         assert 0.75 * wgs <= blocks <= wgs
