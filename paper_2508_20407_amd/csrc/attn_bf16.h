@@ -20,8 +20,8 @@
 //     lane, which is what ds_read_b64_tr_b16 returns (16 lanes read a 4x16 patch and get its
 //     transpose).  Two such reads form one 8-element operand.
 //   * K/V tiles of 64 keys go HBM -> LDS directly (buffer_load_dwordx4 ... lds: each wave
-//     instruction moves 1 KB, lane i landing at base + 16*i) through a ring of NSTAGE tiles,
-//     the loads of the following tiles being in flight during compute.  One barrier per tile;
+//     instruction moves 1 KB, lane i landing at base + 16*i) through a ring of two tiles,
+//     the loads of the following tile being in flight during compute.  One barrier per tile;
 //     completion is tracked by hand with s_waitcnt vmcnt.  (A compute unit keeps only some
 //     16-32 KB of such loads in flight; a wave that issues into a full queue waits there, so
 //     the ring depth beyond two tiles buys little.)
@@ -73,9 +73,8 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs &a, int bid, int n
     constexpr int DU = PAD ? DP : D;       // columns computed
     constexpr int DS = DU / 16;            // contraction steps of Q K^T
     constexpr int DB = (DU + 31) / 32;     // 32-row blocks of O^T
-    constexpr int PD = NSTAGE - 1;         // prefetch distance in tiles
-    static_assert(PD >= 1, "ring too shallow");
-    static_assert(PD * 2 * NDMA < 64, "too many loads in flight for vmcnt");
+    static_assert(RESIDENT || NSTAGE == 2, "a ring of two tiles");
+    static_assert(2 * NDMA < 64, "too many loads in flight for vmcnt");
 
     char *const Ks = tlin_smem;
     char *const Vs = tlin_smem + NSTAGE * TILE_B;
@@ -358,11 +357,10 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs &a, int bid, int n
     // owns no rows (the window's end lies before its first one).
     auto active = [&](int t) { return qrow0 < Wq && (!CAUSAL || t * BN <= qrow0 + QB * 32 - 1); };
 
-    // Ring protocol.  Before the loop the loads of tiles t0 .. t0+PD-1 are issued.  Iteration t
+    // Ring protocol.  Before the loop the loads of tile t0 are issued.  Iteration t
     // waits until this wave's loads of tile t have landed, meets the other waves at the barrier
-    // (now the whole tile is visible, and every wave has finished reading tile t-1), then issues the loads of tile t+PD into the
+    // (now the whole tile is visible, and every wave has finished reading tile t-1), then issues the loads of tile t+1 into the
     // stage that was released, and computes on tile t.
-    constexpr int PER_TILE = 2 * NDMA;
     if (RESIDENT) {
         // the partition has at most NSTAGE tiles (checked by the host): tile t lives in stage t
 #pragma unroll
@@ -374,10 +372,8 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs &a, int bid, int n
         for (int s = 0; s < NSTAGE; ++s)
             if (s < t1) scrub(s);
         __builtin_amdgcn_s_barrier();
-    } else {
-#pragma unroll
-        for (int s = 0; s < PD; ++s)
-            if (t0 + s < t1) issue(t0 + s, s);
+    } else if (t0 < t1) {
+        issue(t0, 0);
     }
   do {
     bf16x8 qn[QB][DS];   // resident variant: the next block's queries, requested before this block's work
@@ -399,14 +395,13 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs &a, int bid, int n
     } else {
         for (int t = t0; t < t1; ++t) {
             const int n = t - t0;
-            if (t + PD - 1 < t1) wait_vmcnt<(PD - 1) * PER_TILE>();   // PD-1 younger tiles may still fly
-            else wait_vmcnt<0>();
-            scrub(n % NSTAGE);
+            wait_vmcnt<0>();
+            scrub(n & 1);
             __builtin_amdgcn_s_barrier();
-            if (t + PD < t1) issue(t + PD, (n + PD) % NSTAGE);
+            if (t + 1 < t1) issue(t + 1, (n + 1) & 1);
             if (active(t)) {
-                scores_softmax(Ks + (n % NSTAGE) * TILE_B, t * BN);
-                accumulate(Vs + (n % NSTAGE) * TILE_B);
+                scores_softmax(Ks + (n & 1) * TILE_B, t * BN);
+                accumulate(Vs + (n & 1) * TILE_B);
             }
         }
     }
@@ -510,30 +505,25 @@ void attn_bf16_resident_pipe_kernel(const AttnArgs a)
 }
 
 // History partition blocks and window causal blocks of one call in a single launch.
-template <int D, int NW, int NSTAGE, int DP = 0, bool NT = false>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NSTAGE == 2 && NW < 8 ? 2 : 1, 8)))
+template <int D, int NW, int DP = 0, bool NT = false>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW < 8 ? 2 : 1, 8)))
 void attn_bf16_pair_kernel(const PairArgs f)
 {
-    static_assert(!NT || use_pipe_body<D, NW, 1, false, NSTAGE, false>(), "only the pipelined body has a non-temporal variant");
     // logical index of the window block this workgroup computes, or -1
     int win_block = (int)blockIdx.x < f.n_hist_blocks ? -1 : xcd_remap(blockIdx.x - f.n_hist_blocks, f.n_win_blocks);
     if ((int)blockIdx.x < f.n_hist_blocks) {
-        if constexpr (use_pipe_body<D, NW, 1, false, NSTAGE, false>()) {
-            attn_bf16_pipe_body<D, NW, DP, NT>(f.hist, blockIdx.x, f.n_hist_blocks);
-            if (f.hist.fuse_window) {
-                // the workgroup of partition 0 goes on to the window's causal block of the same rows
-                // (causal blocks are numbered from the last query block down)
-                const Problem pr = decode_problem<NW * 32, 64, false>(f.hist, xcd_remap(blockIdx.x, f.n_hist_blocks), f.hist.nqb);
-                if (pr.split == 0) {
-                    win_block = pr.bh * f.win.nqb + (f.win.nqb - 1 - pr.qb);
-                    __syncthreads();      // every wave is done with the history tiles in LDS
-                }
+        attn_bf16_pipe_body<D, NW, DP, NT>(f.hist, blockIdx.x, f.n_hist_blocks);
+        if (f.hist.fuse_window) {
+            // the workgroup of partition 0 goes on to the window's causal block of the same rows
+            // (causal blocks are numbered from the last query block down)
+            const Problem pr = decode_problem<NW * 32, 64, false>(f.hist, xcd_remap(blockIdx.x, f.n_hist_blocks), f.hist.nqb);
+            if (pr.split == 0) {
+                win_block = pr.bh * f.win.nqb + (f.win.nqb - 1 - pr.qb);
+                __syncthreads();      // every wave is done with the history tiles in LDS
             }
-        } else {
-            attn_bf16_body<D, NW, 1, false, NSTAGE, false, DP>(f.hist, blockIdx.x, f.n_hist_blocks);
         }
     }
-    if (win_block >= 0) attn_bf16_body<D, NW, 1, true, NSTAGE, false, DP, false>(f.win, win_block, 0);
+    if (win_block >= 0) attn_bf16_body<D, NW, 1, true, 2, false, DP, false>(f.win, win_block, 0);
 }
 
 }  // namespace tlin

@@ -760,34 +760,29 @@ MergeArgs merge_args(const tlin_params *p, const Workspace &w, int nparts, int n
     return m;
 }
 
-template <int D, int NW, int NSTAGE, int DP, bool NT>
+template <int D, int NW, int DP, bool NT>
 tlin_status launch_pair_kernel(const PairArgs &f, hipStream_t st)
 {
-    constexpr int lds_bytes = 2 * NSTAGE * 64 * D * 2;
+    constexpr int lds_bytes = 2 * 2 * 64 * D * 2;
     static_assert(lds_bytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a gfx950 compute unit");
-    auto kernel = attn_bf16_pair_kernel<D, NW, NSTAGE, DP, NT>;
+    auto kernel = attn_bf16_pair_kernel<D, NW, DP, NT>;
     static std::atomic<uint64_t> lds_allowed{0};
     if (allow_lds((const void *)kernel, lds_bytes, lds_allowed) != TLIN_OK) return TLIN_ERR_HIP;
-    if constexpr (use_pipe_body<D, NW, 1, false, NSTAGE, false>()) {
-        if (fuses_window(TLIN_BF16, f, Shape{NW, 1}, 64, 5)) {
-            PairArgs g = f;
-            g.hist.fuse_window = 1;
-            g.n_win_blocks = 0;
-            return launch_kernel((const void *)kernel, dim3(g.n_hist_blocks), dim3(NW * 64), lds_bytes, st, g);
-        }
+    if (fuses_window(TLIN_BF16, f, Shape{NW, 1}, 64, 5)) {
+        PairArgs g = f;
+        g.hist.fuse_window = 1;
+        g.n_win_blocks = 0;
+        return launch_kernel((const void *)kernel, dim3(g.n_hist_blocks), dim3(NW * 64), lds_bytes, st, g);
     }
     return launch_kernel((const void *)kernel, dim3(f.n_hist_blocks + f.n_win_blocks), dim3(NW * 64), lds_bytes, st, f);
 }
 
-template <int D, int NW, int NSTAGE>
+template <int D, int NW>
 tlin_status launch_pair_shape(const PairArgs &f, hipStream_t st)
 {
     return with_columns<D>(f.hist.D, [&](auto dp) {
         constexpr int DP = decltype(dp)::value;
-        if constexpr (use_pipe_body<D, NW, 1, false, NSTAGE, false>()) {
-            if (f.hist.stream_once) return launch_pair_kernel<D, NW, NSTAGE, DP, true>(f, st);
-        }
-        return launch_pair_kernel<D, NW, NSTAGE, DP, false>(f, st);
+        return f.hist.stream_once ? launch_pair_kernel<D, NW, DP, true>(f, st) : launch_pair_kernel<D, NW, DP, false>(f, st);
     });
 }
 
@@ -809,15 +804,15 @@ tlin_status launch_partials(const tlin_params *p, const AttnArgs &ah, const Attn
         LaunchTimer timer(KC_HISTORY, hs);
         if (p->in_dtype == TLIN_F32) return dpad(p->D) == 128 ? launch_f32_pair<128>(f, s, hs) : launch_f32_pair<64>(f, s, hs);
         if (dpad(p->D) == 128) {
-            if (s.nw == 8) return launch_pair_shape<128, 8, 2>(f, hs);
-            if (s.nw == 4) return launch_pair_shape<128, 4, 2>(f, hs);
-            return launch_pair_shape<128, 2, 2>(f, hs);
+            if (s.nw == 8) return launch_pair_shape<128, 8>(f, hs);
+            if (s.nw == 4) return launch_pair_shape<128, 4>(f, hs);
+            return launch_pair_shape<128, 2>(f, hs);
         }
-        if (s.nw == 4) return launch_pair_shape<64, 4, 2>(f, hs);
+        if (s.nw == 4) return launch_pair_shape<64, 4>(f, hs);
         // (ahead of the classic body with a ring of three tiles: 32 heads x 64, 64 rows over 60000: 103 -> 87 us, 12
         // heads x 36, 64 rows over 999754: 409 -> 334, sliding schedule of 8 heads x 64, 8000 rows in chunks of 64:
         // 135 -> 100)
-        return launch_pair_shape<64, 2, 2>(f, hs);
+        return launch_pair_shape<64, 2>(f, hs);
     }
     tlin_status st;
     if ((st = launch_attn(p, false, ah, hs))) return st;

@@ -223,6 +223,8 @@ def test_no_kernel_is_compiled_that_the_dispatch_cannot_reach():
     names = subprocess.run(["nm", "-C", b.LIB_PATH], capture_output=True, text=True, check=True).stdout
     kernels = {tuple(k.split(", ")) for k in re.findall(r"attn_bf16_kernel<([^>]*)>", names)}
     assert len(kernels) >= 20
+    assert set(re.findall(r"\b(attn_\w+_kernel)\b", names)) == {"attn_bf16_kernel", "attn_bf16_pair_kernel", "attn_bf16_resident_pipe_kernel",
+                                                              "attn_f32_kernel", "attn_f32_pair_kernel"}
     for d, nw, qb, causal, nstage, resident, columns, nt, lse in kernels:
         assert not (causal == "true" and nt == "true"), (d, nw, columns)
         assert lse == "false" or (causal == "true" and d == "64"), (d, nw, columns)
