@@ -322,8 +322,9 @@ def test_long_query_sides_over_few_keys(D, N):
         sub = [np.ascontiguousarray(host["Q"][:, h:h + 1, rows]), np.ascontiguousarray(host["Kh"][:, h:h + 1]), np.ascontiguousarray(host["Vh"][:, h:h + 1])]
         ro, rl = oracle.history(*sub, w.dtype, w.scale)
         assert_close(o[:, h:h + 1, torch.from_numpy(rows).cuda()], ro, w.dtype, f"{w.name} head {h}")
-        # (the classic body sums rounded weights: 2^-8)
-        np.testing.assert_allclose(lse[:, h:h + 1, torch.from_numpy(rows).cuda()].cpu().numpy(), rl, rtol=0, atol=4.5e-3)
+        # (the unpipelined resident body, for up to 64 columns and for odd tile counts, sums rounded weights: 2^-8)
+        rounded = N <= (256 if D > 48 else 128) if D <= 64 else -(-N // 64) == 3 or D < 128 and -(-N // 64) == 1
+        np.testing.assert_allclose(lse[:, h:h + 1, torch.from_numpy(rows).cuda()].cpu().numpy(), rl, rtol=0 if rounded else 1e-5, atol=4.5e-3 if rounded else 1e-5)
 
 
 def bf16_bits(x):
