@@ -280,7 +280,7 @@ Plan plan_for_shape(const tlin_params *p, Shape s, int64_t target, int round_dow
 Plan plan_for_shape(const tlin_params *p, Shape s)
 {
     // (two-wave workgroups of at most 32 columns, half of whose tiles' places are not loaded: a fourth one per
-    // compute unit; 12 heads x 16, 40 rows over 999754: 225 -> 181 us, 100 heads, 40 rows over 9000: 25.8 -> 23.2; 36 and
+    // compute unit; 12 heads x 16, 40 rows over 999754: 246 -> 206 us, 100 heads, 40 rows over 9000: 27.6 -> 24.8; 36 and
     // more columns lose up to 4 % with it)
     const bool narrow = p->in_dtype == TLIN_BF16 && s.nw == 2 && p->D <= 32;
     const int64_t target = narrow ? 4 * kNumCU : resident_wgs(p->in_dtype, s, p->D);
@@ -294,7 +294,7 @@ Plan plan_for_shape(const tlin_params *p, Shape s)
 // compute unit, leave nothing idle and cut the history into more partitions.  A tile takes the two 1.12 of an
 // eight-wave workgroup's time (each loads it for itself), one that has the compute unit to itself 0.8, and every
 // partition its partials' way out and back in: a tile is some 1.75 us at 128 columns (fp32, half as many keys: 5.2),
-// partials move at 5 TB/s.  Measured, eight waves -> four: 16 heads x 96, 300 rows over 50021: 146 -> 129 us; 48 heads x
+// partials move at 5 TB/s.  Measured, eight waves -> four: 16 heads x 96, 300 rows over 50021: 147 -> 132 us; 48 heads x
 // 128, 300 rows over 33996 405 -> 327, 32 heads, 260 rows over 131072 857 -> 743; fp32, 48 heads x 96, 300 rows over
 // 17905: 907 -> 701; the other way round 64 heads x 128 (fp32), 300 rows over 2212: 143 against 150, 24 heads x 128, 384
 // rows over 6280: 43.7 against 44.6, x 96 42.5 against 44.7.
@@ -316,7 +316,7 @@ Plan plan_history(const tlin_params *p) { return plan_for_shape(p, history_shape
 // The cache-hit shape (a few query rows over a long history) runs in the streaming kernel of
 // decode.h when called through tlin_history_attn.
 //   fp32 inputs: the matrix-core path pays for a whole 32-row tile of products, and for splitting every key and
-// value, whatever W is (16 rows over 32768 rows of 32 heads x 128: 221 us; eight rows over four times as many take
+// value, whatever W is (16 rows over 32768 rows of 32 heads x 128: 223 us; eight rows over four times as many take
 // 655 us here, one row 610).
 //   bf16: three and four rows are a little faster in the two-wave matrix-core shape at head dimension
 // 128 (0.309 against 0.323 ms over 131072 rows of 32 heads; both read at the rate of a plain
