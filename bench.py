@@ -273,7 +273,7 @@ def main():
                 "tlin_history_attn = history partitions + merge (cache-hit step)")
     elif args.workload == "f32":
         w = ti.f32_point(args.N or 32768, args.W or 512)
-        metric = "layer call with fp32 inputs (fp32 matrix-core products); % fp32 MFMA peak"
+        metric = "layer call with fp32 inputs (six bf16 products of parts per product); % of a sixth of the bf16 MFMA peak"
         what = "tlin_layer_attn = history partitions + window causal (one launch) + merge"
     elif args.workload == "decode":
         w = ti.decode_point(args.N or 131072, args.W or 1)
@@ -377,7 +377,7 @@ def main():
     hist_gbs = kv_bytes / (hist_ms * 1e-3) / 1e9
     # Arithmetic intensity of the history kernel is W flop/byte (bf16; W/2 for fp32): it is
     # matrix-core bound when that exceeds the ridge point peak_flops/peak_bw of its operand type
-    # (fp32 inputs are multiplied by the fp32 matrix instructions), else HBM bound.
+    # (fp32 inputs: a sixth of the bf16 rate, see PEAK_F32_MFMA_TFLOPS), else HBM bound.
     peak_mfma = PEAK_F32_MFMA_TFLOPS if w.dtype == ti.F32 else PEAK_BF16_MFMA_TFLOPS
     if flops_h / kv_bytes >= peak_mfma * 1e12 / (PEAK_HBM_GBS * 1e9):
         roof = {"bound": "mfma", "achieved": hist_tflops, "peak": peak_mfma, "unit": "TFLOP/s"}
@@ -455,22 +455,22 @@ def main():
 # two counters are in the profile files named here).  A figure is only reported while the kernel
 # sources are the ones it was measured on (csrc_sha16 below = kernel_sources_sha16() at that time);
 # otherwise `traffic` is null and `traffic_source` says why.
-_SHA = "9981e454e1b9a560"      # kernel_sources_sha16() when the counters below were read
+_SHA = "bef3f1c7d2e149a0"      # kernel_sources_sha16() when the counters below were read
 MEASURED_TRAFFIC = {
     # workload: (FETCH_SIZE KiB x 2.0 + WRITE_SIZE KiB x 1.0) x 1024, profile file with the raw readings
-    "cfg4_bf16_N131072_W512": {"bytes": int(1_056_988.4 * 2.0 * 1024) + int(41_600.0 * 1024),   # 2.016 GiB fetched + 40.6 MiB written
+    "cfg4_bf16_N131072_W512": {"bytes": int(1_056_999.2 * 2.0 * 1024) + int(41_600.0 * 1024),   # 2.016 GiB fetched + 40.6 MiB written
                                "profile": "profiles/attn_bf16_pair_cfg4_pmc.md", "csrc_sha16": _SHA},
-    "decode_bf16_N131072_W1": {"bytes": int(1_055_857.0 * 2.0 * 1024) + int(576.3 * 1024),      # 2.014 GiB fetched + 0.6 MiB written
+    "decode_bf16_N131072_W1": {"bytes": int(1_055_815.8 * 2.0 * 1024) + int(576.2 * 1024),      # 2.014 GiB fetched + 0.6 MiB written
                                "profile": "profiles/decode_bf16_w1.md", "csrc_sha16": _SHA},
-    "cfg3_bf16_N32768_W256_peaky": {"bytes": int(532_231.1 * 2.0 * 1024) + int(41_600.0 * 1024),    # 1.015 GiB + 40.6 MiB
+    "cfg3_bf16_N32768_W256_peaky": {"bytes": int(532_223.2 * 2.0 * 1024) + int(41_600.0 * 1024),    # 1.015 GiB + 40.6 MiB
                                     "profile": "profiles/attn_bf16_pair_cfg3_kernel_trace.md", "csrc_sha16": _SHA},
     "restore_bf16_Q131072_K256": {"bytes": int(526_450.9 * 2.0 * 1024) + int(1_048_576.0 * 1024),    # 1.004 GiB (Q) + 1 GiB (O)
                                   "profile": "profiles/attn_bf16_resident_restore_kernel_trace.md", "csrc_sha16": _SHA},
-    "f32_N131072_W1": {"bytes": int(2_108_624.8 * 2.0 * 1024) + int(576.4 * 1024),                  # 4.022 GiB + 0.6 MiB
+    "f32_N131072_W1": {"bytes": int(2_108_635.7 * 2.0 * 1024) + int(576.4 * 1024),                  # 4.022 GiB + 0.6 MiB
                        "profile": "profiles/decode_f32_w1.md", "csrc_sha16": _SHA},
-    "f32_N32768_W512": {"bytes": int(540_852.8 * 2.0 * 1024) + int(41_600.0 * 1024),                # 1.032 GiB + 40.6 MiB
+    "f32_N32768_W512": {"bytes": int(541_014.4 * 2.0 * 1024) + int(41_600.2 * 1024),                # 1.032 GiB + 40.6 MiB
                         "profile": "profiles/attn_f32_pair_N32768_W512.md", "csrc_sha16": _SHA},
-    "paper_bf16_H12_D36_N999754_W256": {"bytes": int(949_160.8 * 2.0 * 1024) + int(26_136.0 * 1024),   # 1.810 GiB + 25.5 MiB
+    "paper_bf16_H12_D36_N999754_W256": {"bytes": int(950_879.2 * 2.0 * 1024) + int(26_136.0 * 1024),   # 1.810 GiB + 25.5 MiB
                                         "profile": "profiles/attn_bf16_pair_paper_hd36_N999754.md", "csrc_sha16": _SHA},
 }
 
