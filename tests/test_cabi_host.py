@@ -230,6 +230,23 @@ def test_no_kernel_is_compiled_that_the_dispatch_cannot_reach():
         assert lse == "false" or (causal == "true" and d == "64"), (d, nw, columns)
 
 
+LLVM = "/opt/rocm/llvm/bin"
+
+
+@pytest.mark.skipif(not all(os.path.exists(f"{LLVM}/{t}") for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf")), reason="ROCm's LLVM tools not found")
+def test_registers_spilled(tmp_path):
+    """No bf16 kernel spills; the fp32 ones a few registers (at most 18 are)."""
+    fat, code = str(tmp_path / "fat"), str(tmp_path / "code")
+    subprocess.run([f"{LLVM}/llvm-objcopy", "-O", "binary", "--only-section=.hip_fatbin", b.LIB_PATH, fat], check=True)
+    subprocess.run([f"{LLVM}/clang-offload-bundler", "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950",
+                    f"--input={fat}", f"--output={code}"], check=True)
+    notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", code], capture_output=True, text=True, check=True).stdout
+    kernels = dict(re.findall(r"\.name:\s+(_ZN4tlin\S+).*?\.vgpr_spill_count:\s+(\d+)", notes, flags=re.S))
+    assert len(kernels) > 100
+    spilled = {k: int(n) for k, n in kernels.items() if int(n)}
+    assert all("attn_f32" in k for k in spilled) and max(spilled.values(), default=0) <= 20, spilled
+
+
 def test_inline_assembly_loads_no_registers():
     """The compiler takes the output of an assembly load as there at once: only the direct loads into LDS,
     whose arrival is waited for by hand, are written that way."""
